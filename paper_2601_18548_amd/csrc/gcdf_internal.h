@@ -201,6 +201,11 @@ struct ServeDev {
   unsigned long long claim[kMaxSlots];  // (seq << 32) | tiles claimed of request seq
   unsigned long long done[kMaxSlots];   // tiles finished in the slot, cumulative over its requests
   uint32_t drain;                       // epoch of the launch that is draining (0: none yet)
+  unsigned long long pub;               // the largest ServeCtl::published any workgroup has seen
+  // device copies of the descriptors: ready[slot] = seq + 1 of the request in
+  // desc[slot], 0 while it is being written (see store_copy)
+  unsigned long long ready[kMaxSlots];
+  ServeDesc desc[kMaxSlots];
 };
 
 // Launch the persistent serving kernel; it processes published requests from

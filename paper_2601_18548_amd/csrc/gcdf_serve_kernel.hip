@@ -28,6 +28,78 @@ __device__ __forceinline__ T sys_relaxed(const T* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// A value that is the same for the whole workgroup (read from LDS), as a scalar.
+template <class T>
+__device__ __forceinline__ T uniform(T v) {
+  static_assert(sizeof(T) == 8, "64-bit values");
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(u >> 32));
+  return __builtin_bit_cast(T, ((uint64_t)hi << 32) | lo);
+}
+
+template <class T>
+__device__ __forceinline__ T dev_relaxed(const T* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A request's descriptor, field by field, with relaxed loads of the given kind.
+template <class L>
+__device__ __forceinline__ void load_desc(ServeDesc& o, const ServeDesc* d, uint64_t seq, L&& ld) {
+  o.knots = ld(&d->knots);
+  o.points = ld(&d->points);
+  o.K = ld(&d->K);
+  o.Np = ld(&d->Np);
+  o.nblk = ld(&d->nblk);
+  o.ntiles = ld(&d->ntiles);
+  o.done_target = ld(&d->done_target);
+  o.d = ld(&d->d);
+  o.J = ld(&d->J);
+  o.minkey = ld(&d->minkey);
+  o.dmin = ld(&d->dmin);
+  o.argmin = ld(&d->argmin);
+  o.Jmin = ld(&d->Jmin);
+  o.want_grad = ld(&d->want_grad);
+  o.seq = seq;
+}
+
+// Device copies of the descriptors.  Every workgroup reading a request's fields from
+// host memory cost a few hundred microseconds per request (256-512 workgroups times
+// 18 reads over the host link, all at once), so the workgroup that claims a request's
+// first tile reads them, stores this copy and then the request's number; the others
+// read the copy.  A copy has one writer at a time: the next request in the slot is
+// claimed only after this one has completed, which needs the writer's own tile.
+// Readers check the number before and after, as with the host's descriptors.
+__device__ __forceinline__ void store_copy(ServeDev* dev, uint32_t s, const ServeDesc& o) {
+  __hip_atomic_store(&dev->ready[s], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // the marker before the fields
+  ServeDesc* d = &dev->desc[s];
+  auto put = [](auto* p, auto v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  put(&d->knots, o.knots);
+  put(&d->points, o.points);
+  put(&d->K, o.K);
+  put(&d->Np, o.Np);
+  put(&d->nblk, o.nblk);
+  put(&d->ntiles, o.ntiles);
+  put(&d->done_target, o.done_target);
+  put(&d->d, o.d);
+  put(&d->J, o.J);
+  put(&d->minkey, o.minkey);
+  put(&d->dmin, o.dmin);
+  put(&d->argmin, o.argmin);
+  put(&d->Jmin, o.Jmin);
+  put(&d->want_grad, o.want_grad);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");  // the fields before the number
+  __hip_atomic_store(&dev->ready[s], (unsigned long long)(o.seq + 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool load_copy(const ServeDev* dev, uint32_t s, uint64_t want, ServeDesc& o) {
+  if (dev_relaxed(&dev->ready[s]) != want + 1) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  load_desc(o, &dev->desc[s], want, [](auto* p) { return dev_relaxed(p); });
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // the fields precede the re-check
+  return dev_relaxed(&dev->ready[s]) == want + 1;
+}
+
 // Tile count of request `want` from its slot's descriptor, read seqlock-style:
 // the descriptor's seq before and after the read must both be `want`.  Returns
 // false if the slot no longer holds `want` (it has completed and the host is
@@ -47,21 +119,39 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
   __shared__ __attribute__((aligned(16))) char lds[Geo<W, MODE>::LDS_BYTES];
   __shared__ int64_t claim_info[3];  // claimed seq (or -1: exit, -2: none), tile, seq to finalize (or -1)
   __shared__ ServeDesc cur;          // the request this workgroup is working on
+  __shared__ ServeDesc nxt;          // the request it claims next, once read
   __shared__ ServeDesc fin;          // a request this workgroup completes
   __shared__ uint32_t ovf;
   TileCtx<W, MODE> tc(lds, &ovf, net, threadIdx.x);
   const int tid = threadIdx.x;
-  uint64_t seq = first_seq;  // this workgroup's cursor in the request sequence
-  uint64_t cur_seq = ~0ull;
-  uint64_t idle_since = __builtin_amdgcn_s_memrealtime();
-  const uint32_t slots = sys_relaxed(&ctl->slots);
-  // thread 0's view of the queue
-  uint64_t pub = 0, nt_seq = ~0ull;
-  int64_t ntiles = 0;
-  uint64_t open_count = 0;  // tiles of request cur_seq run here and not yet reported
-  int backoff = 1;
+  // thread 0's view of the queue, kept in LDS between its claims: held in registers it
+  // would take them from every lane of the tiles
+  struct Cursor {
+    uint64_t seq;         // this workgroup's place in the request sequence
+    uint64_t cur_seq;     // the request in cur
+    uint64_t nxt_seq;     // the request in nxt
+    uint64_t pub, nt_seq;
+    int64_t ntiles;
+    uint64_t open_count;  // tiles of request cur_seq run here and not yet reported
+    uint64_t idle_since;
+    uint32_t slots;
+  };
+  __shared__ Cursor kept;
+  if (tid == 0)
+    kept = Cursor{first_seq, ~0ull, ~0ull, 0, ~0ull, 0, 0, __builtin_amdgcn_s_memrealtime(), sys_relaxed(&ctl->slots)};
   while (true) {
     if (tid == 0) {
+      uint64_t nxt_seq = kept.nxt_seq;
+      uint64_t seq = kept.seq, cur_seq = kept.cur_seq, pub = kept.pub, nt_seq = kept.nt_seq, open_count = kept.open_count;
+      int64_t ntiles = kept.ntiles;
+      const uint64_t idle_since = kept.idle_since;
+      const uint32_t slots = kept.slots;
+      int backoff = 1;
+      // One workgroup in 64 reads the host's words each time round and passes what it
+      // finds on through device memory; the others do so only now and then (all of them
+      // polling host memory kept the link busy for the reads that matter).
+      const bool leader = (blockIdx.x & 63) == 0;
+      uint32_t idle_rounds = 0;
       int64_t got_seq = -1, got_tile = 0, fin_seq = -1;
       bool leave = false;
       // Report the tiles of request cur_seq run here (the caller has established that
@@ -87,7 +177,11 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
           break;
         }
         if (seq >= pub) {
-          const uint64_t p = sys_relaxed(&ctl->published);
+          uint64_t p = dev_relaxed(&dev->pub);
+          if (p <= pub && (leader || (idle_rounds & 7) == 7)) {
+            p = sys_relaxed(&ctl->published);
+            if (p > pub) __hip_atomic_fetch_max(&dev->pub, (unsigned long long)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
           if (p > pub) {
             pub = p;
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "");  // system scope: the new descriptors
@@ -95,6 +189,35 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
         }
         if (seq < pub) {
           const uint32_t s = (uint32_t)(seq % slots);
+          const uint64_t s32 = seq & 0xffffffffull;
+          // Not read yet: if nobody has claimed a tile of it (an older tag), it cannot
+          // have completed: the workgroup whose compare-and-swap re-tags the word has
+          // its tile 0 and reads the host's descriptor; the others wait for its copy,
+          // and read the host's themselves should it be long in coming.  (Request 0
+          // finds its own tag, and no copy.)
+          if (nt_seq != seq) {
+            unsigned long long v = dev_relaxed(&dev->claim[s]);
+            if ((v >> 32) < s32 &&
+                __hip_atomic_compare_exchange_strong(&dev->claim[s], &v, (s32 << 32) | 1ull, __ATOMIC_RELAXED,
+                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+              load_desc(nxt, &ctl->desc[s], seq, [](auto* p) { return sys_relaxed(p); });
+              store_copy(dev, s, nxt);
+              nt_seq = nxt_seq = seq;
+              ntiles = nxt.ntiles;
+              got_seq = (int64_t)seq;
+              got_tile = 0;
+              break;
+            }
+            for (int tries = 0; seq != 0 && tries < 64; ++tries) {
+              if (load_copy(dev, s, seq, nxt)) {
+                nt_seq = nxt_seq = seq;
+                ntiles = nxt.ntiles;
+                break;
+              }
+              if ((dev_relaxed(&dev->claim[s]) >> 32) != s32) break;  // the slot has moved on
+              __builtin_amdgcn_s_sleep(8);
+            }
+          }
           if (nt_seq != seq) {
             // A cursor behind the others can reach a request that has completed and
             // whose slot the host has already given to a later request: the
@@ -109,23 +232,13 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
             nt_seq = seq;
           }
           // Claim word of the slot: (request tag << 32) | tiles handed out.  The first
-          // claimant of a request re-tags the word with a compare-and-swap; every other
-          // claim is a fetch_add, which never has to be retried.
-          unsigned long long v = __hip_atomic_load(&dev->claim[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          const uint64_t s32 = seq & 0xffffffffull;
+          // claimant of a request has re-tagged the word (above); every other claim is a
+          // fetch_add, which never has to be retried.
+          const unsigned long long v = dev_relaxed(&dev->claim[s]);
           bool moved_on = false;
-          while (true) {
+          do {
             const uint64_t vs = v >> 32, vc = v & 0xffffffffull;
             if (vs > s32) { moved_on = true; break; }  // slot already reused: seq is complete
-            if (vs < s32) {                            // first claim of request seq
-              if (__hip_atomic_compare_exchange_strong(&dev->claim[s], &v, (s32 << 32) | 1ull, __ATOMIC_RELAXED,
-                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-                got_seq = (int64_t)seq;
-                got_tile = 0;
-                break;
-              }
-              continue;  // v now holds the current word
-            }
             if ((int64_t)vc >= ntiles) { moved_on = true; break; }
             const unsigned long long w =
                 __hip_atomic_fetch_add(&dev->claim[s], 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -168,8 +281,7 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
             ntiles = held ? lnt : 0;
             if (held && (int64_t)wc < lnt) { got_seq = (int64_t)later; got_tile = (int64_t)wc; }
             else moved_on = true;
-            break;
-          }
+          } while (false);
           if (got_seq >= 0 || leave) break;
           if (moved_on) {
             if (open_count && cur_seq == seq) report();  // leaving request seq
@@ -177,7 +289,9 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
             if (fin_seq >= 0) break;
           }
         } else {
-          if (sys_relaxed(&ctl->stop)) {
+          if ((leader || (idle_rounds & 7) == 7) && sys_relaxed(&ctl->stop)) {
+            __hip_atomic_store(&dev->drain, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (open_count) report();  // (none expected)
             leave = true;
             break;
           }
@@ -189,35 +303,28 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
             break;
           }
           // idle: back off up to ~4 us between polls of host memory
+          ++idle_rounds;
           for (int i = 0; i < backoff; ++i) __builtin_amdgcn_s_sleep(16);
           backoff = backoff < 8 ? 2 * backoff : 8;
         }
       }
-      backoff = 1;
       // -1: exit (after finalizing, if fin_seq is set), -2: nothing claimed but a request to finalize
       claim_info[0] = got_seq >= 0 ? got_seq : (fin_seq >= 0 && !leave ? -2 : -1);
       claim_info[1] = got_tile;
       claim_info[2] = fin_seq;
       if (got_seq >= 0 && (uint64_t)got_seq != cur_seq) {
-        const ServeDesc* d = &ctl->desc[got_seq % slots];
-        cur.knots = sys_relaxed(&d->knots);
-        cur.points = sys_relaxed(&d->points);
-        cur.K = sys_relaxed(&d->K);
-        cur.Np = sys_relaxed(&d->Np);
-        cur.nblk = sys_relaxed(&d->nblk);
-        cur.ntiles = sys_relaxed(&d->ntiles);
-        cur.done_target = sys_relaxed(&d->done_target);
-        cur.d = sys_relaxed(&d->d);
-        cur.J = sys_relaxed(&d->J);
-        cur.minkey = sys_relaxed(&d->minkey);
-        cur.dmin = sys_relaxed(&d->dmin);
-        cur.argmin = sys_relaxed(&d->argmin);
-        cur.Jmin = sys_relaxed(&d->Jmin);
-        cur.want_grad = sys_relaxed(&d->want_grad);
-        cur.seq = (uint64_t)got_seq;
+        if (nxt_seq == (uint64_t)got_seq) cur = nxt;
+        else load_desc(cur, &ctl->desc[got_seq % slots], (uint64_t)got_seq, [](auto* p) { return sys_relaxed(p); });
         cur_seq = (uint64_t)got_seq;
       }
       if (got_seq >= 0) ++open_count;
+      kept.seq = seq;
+      kept.cur_seq = cur_seq;
+      kept.nxt_seq = nxt_seq;
+      kept.pub = pub;
+      kept.nt_seq = nt_seq;
+      kept.ntiles = ntiles;
+      kept.open_count = open_count;
     }
     __syncthreads();
     const int64_t gs = claim_info[0];
@@ -239,35 +346,35 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
         __threadfence();
         __syncthreads();  // every argmin written above is visible to the workgroup
         Job pj{};
-        pj.knots = fin.knots;
-        pj.points = fin.points;
-        pj.K = fin.K;
-        pj.Np = fin.Np;
-        pj.pidx32 = fin.argmin;
-        pj.npairs = fin.K;
-        pj.J = fin.Jmin;
-        for (int64_t q0 = 0; q0 < fin.K; q0 += kTileQ)
+        pj.knots = uniform(fin.knots);
+        pj.points = uniform(fin.points);
+        pj.K = uniform(fin.K);
+        pj.Np = uniform(fin.Np);
+        pj.pidx32 = uniform(fin.argmin);
+        pj.npairs = pj.K;
+        pj.J = uniform(fin.Jmin);
+        for (int64_t q0 = 0; q0 < pj.K; q0 += kTileQ)
           process_tile<W, MODE, true, false, false, SPH>(net, pj, 1, 0, q0, tc);
       }
       __threadfence_system();
       __syncthreads();
       if (tid == 0)
-        __hip_atomic_store(&ctl->complete[fin.seq % slots], fin.seq + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+        __hip_atomic_store(&ctl->complete[fin.seq % kept.slots], fin.seq + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     if (gs == -1) break;
     if (gs < 0) continue;
-    const int64_t t = claim_info[1];
+    const int64_t t = uniform(claim_info[1]), nblk = uniform(cur.nblk);
     Job job{};
-    job.knots = cur.knots;
-    job.points = cur.points;
-    job.K = cur.K;
-    job.Np = cur.Np;
-    job.d = cur.d;
-    job.J = cur.J;
-    job.minkey = cur.minkey;
-    const int64_t kk = t / cur.nblk;
-    process_tile<W, MODE, false, false, false, SPH>(net, job, cur.want_grad, kk, (t - kk * cur.nblk) * kTileQ, tc);
-    if (tid == 0) idle_since = __builtin_amdgcn_s_memrealtime();
+    job.knots = uniform(cur.knots);
+    job.points = uniform(cur.points);
+    job.K = uniform(cur.K);
+    job.Np = uniform(cur.Np);
+    job.d = uniform(cur.d);
+    job.J = uniform(cur.J);
+    job.minkey = uniform(cur.minkey);
+    const int64_t kk = t / nblk;
+    process_tile<W, MODE, false, false, false, SPH>(net, job, cur.want_grad, kk, (t - kk * nblk) * kTileQ, tc);
+    if (tid == 0) kept.idle_since = __builtin_amdgcn_s_memrealtime();
   }
   report_overflow<W, MODE>(net, tc);
 }
