@@ -29,7 +29,7 @@ __device__ __forceinline__ void silu_d12(float z, float& d1, float& d2) {
 }
 
 template <int W>
-__global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(const DevNet net, const T1Job job, int64_t ntiles) {
+__global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) void table1_tiles(const DevNet net, const T1Job job, int64_t ntiles) {
   constexpr int MODE = kFP32;
   using G = Geo<W, MODE>;
   constexpr int MT = G::MT;
@@ -37,25 +37,33 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
   __shared__ __attribute__((aligned(16))) char lds[G::LDS_BYTES];
   __shared__ uint32_t ovf;  // (FP32: never set)
   TileCtx<W, MODE> tc(lds, &ovf, net, threadIdx.x);
-  const Lane<W, MODE>& ln = tc.ln;
-  const Bases<W, MODE>& b = tc.b;
-  float* uin = tc.red;  // [64][9] tangent direction of the tile's samples
+  const View<W, MODE> vw(tc);
+  const Lane<W, MODE>& ln = vw.ln;
+  const Bases<W, MODE>& b = vw.b;
+  __shared__ float uin[kTileQ * 9];  // tangent direction of the tile's samples
   const int tid = threadIdx.x;
   constexpr int NTH = G::THREADS;
   static_assert(NTH == kThreads, "gcdf_train_table1 sizes the scratch for kThreads threads per workgroup");
   const size_t arr = (size_t)NTH * 64;
-  float* scr = job.scratch + (size_t)blockIdx.x * kT1ScratchArrays * arr;
-  float* sZ = scr;             // z_1..z_4
-  float* sZd = scr + 4 * arr;  // zdot_1..zdot_4
-  float* sR = scr + 8 * arr;   // r_1..r_3
+  // this workgroup's scratch through a buffer descriptor: one lane offset reaches every
+  // array, the rest of the address is scalar (64-bit addresses per array and group
+  // took over 100 registers)
+  constexpr int kArr = NTH * 64 * 4;  // bytes of an array
+  const __amdgpu_buffer_rsrc_t rscr = __builtin_amdgcn_make_buffer_rsrc(
+      job.scratch + (size_t)blockIdx.x * kT1ScratchArrays * arr, (short)0, kT1ScratchArrays * kArr, 0x00020000);
+  constexpr int sZ = 0;         // z_1..z_4 (byte offsets)
+  constexpr int sZd = 4 * kArr;  // zdot_1..zdot_4
+  constexpr int sR = 8 * kArr;   // r_1..r_3
+  constexpr int kNone = -1;
   const size_t layer = (size_t)W * job.ldb;
   // float4 idx of this thread in a scratch array (elements 4 (idx % 4) .. +3 of
   // accumulator (i, nt) with idx / 4 = i * 2 + nt)
-  auto sget = [&](const float* base, int idx) {
-    return *reinterpret_cast<const f32x4*>(base + ((size_t)idx * NTH + tid) * 4);
+  auto sget = [&](int base, int idx) {
+    return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rscr, tid * 16, base + idx * NTH * 16, 0));
   };
-  auto sput = [&](float* base, int idx, const f32x4& v) {
-    *reinterpret_cast<f32x4*>(base + ((size_t)idx * NTH + tid) * 4) = v;
+  typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
+  auto sput = [&](int base, int idx, const f32x4& v) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), rscr, tid * 16, base + idx * NTH * 16, 0);
   };
   auto zero = [&](f32x16 (&x)[MT][2]) {
 #pragma unroll
@@ -67,7 +75,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
   };
   // a (accumulators) -> LDS tile, element by element through f(I, NT, j, value, z, zd, r),
   // with z / zd / r read from the scratch arrays when given (group by group)
-  auto emit = [&](f32x16 (&a)[MT][2], const float* bz, const float* bzd, const float* br, auto&& f) {
+  auto emit = [&](f32x16 (&a)[MT][2], int bz, int bzd, int br, auto&& f) {
     static_for<MT>([&](auto I) {
       static_for<2>([&](auto GP) {
         static_for<2>([&](auto NT) {
@@ -75,9 +83,9 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
 #pragma unroll
           for (int hh = 0; hh < 2; ++hh) {
             const int idx = (I * 2 + NT) * 4 + 2 * GP + hh;
-            const f32x4 zz = bz ? sget(bz, idx) : f32x4{0.f, 0.f, 0.f, 0.f};
-            const f32x4 dd = bzd ? sget(bzd, idx) : f32x4{0.f, 0.f, 0.f, 0.f};
-            const f32x4 rr = br ? sget(br, idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+            const f32x4 zz = bz >= 0 ? sget(bz, idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+            const f32x4 dd = bzd >= 0 ? sget(bzd, idx) : f32x4{0.f, 0.f, 0.f, 0.f};
+            const f32x4 rr = br >= 0 ? sget(br, idx) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
               const int j = 8 * GP + 4 * hh + u;
@@ -90,7 +98,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
       });
     });
   };
-  auto put_all = [&](float* base, const f32x16 (&x)[MT][2]) {
+  auto put_all = [&](int base, const f32x16 (&x)[MT][2]) {
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -166,6 +174,8 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
     dumpl(job.H, 0);
 
     f32x16 a[MT][2];
+    APre<W, MODE> ap;  // each product's first weight fragments, requested ahead of it
+    preload_a<W, MODE>(ap, net.fwd[0], b.voff);
     // ---- hidden layers forward: z to the scratch, h to LDS ----
     static_for<3>([&](auto L) {
 #pragma unroll
@@ -178,16 +188,16 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
 #pragma unroll
             for (int r = 0; r < 4; ++r) a[i][nt][4 * g + r] = b4[r];
         }
-      layer_gemm<W, MODE, MODE>(a, stream_rsrc<W, MODE>(net.fwd[L]), b.voff, ln.act_r);
+      layer_gemm<W, MODE, MODE>(a, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], b.voff, ln.act_r, ap);
       __syncthreads();
-      put_all(sZ + (L + 1) * arr, a);
-      emit(a, nullptr, nullptr, nullptr, [&](int, int, int, float acc, float, float, float) { return silu_only(acc); });
+      put_all(sZ + (L + 1) * kArr, a);
+      emit(a, kNone, kNone, kNone, [&](int, int, int, float acc, float, float, float) { return silu_only(acc); });
       __syncthreads();
       dumpl(job.H, L + 1);
       __syncthreads();
     });
     // ---- reverse sweep: g_4 = w_out s'(z_4); r_l = W_{l+1}^T g_{l+1}; g_l = r_l s'(z_l) ----
-    emit(a, sZ + 3 * arr, nullptr, nullptr, [&](int I, int, int j, float, float z, float, float) {
+    emit(a, sZ + 3 * kArr, kNone, kNone, [&](int I, int, int j, float, float z, float, float) {
       float d1, d2;
       silu_d12(z, d1, d2);
       return b.w5[16 * I + j] * d1;
@@ -197,10 +207,10 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
     static_for<3>([&](auto LL) {
       constexpr int L = 2 - LL;  // W_{L+2}^T g_{L+2} = r_{L+1}
       zero(a);
-      layer_gemm<W, MODE, MODE>(a, stream_rsrc<W, MODE>(net.bwd[L]), b.voff, ln.act_r);
+      layer_gemm<W, MODE, MODE>(a, net.bwd[L], L > 0 ? net.bwd[L - 1] : net.fwd[0], b.voff, ln.act_r, ap);
       __syncthreads();
-      put_all(sR + L * arr, a);
-      emit(a, sZ + L * arr, nullptr, nullptr, [&](int, int, int, float acc, float z, float, float) {
+      put_all(sR + L * kArr, a);
+      emit(a, sZ + L * kArr, kNone, kNone, [&](int, int, int, float acc, float z, float, float) {
         float d1, d2;
         silu_d12(z, d1, d2);
         return acc * d1;
@@ -254,10 +264,10 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
     static_for<3>([&](auto L) {
       // zdot_{L+2} = W_{L+2} hdot_{L+1}; hdot_{L+2} = s'(z_{L+2}) zdot_{L+2}
       zero(a);
-      layer_gemm<W, MODE, MODE>(a, stream_rsrc<W, MODE>(net.fwd[L]), b.voff, ln.act_r);
+      layer_gemm<W, MODE, MODE>(a, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], b.voff, ln.act_r, ap);
       __syncthreads();
-      put_all(sZd + (L + 1) * arr, a);
-      emit(a, sZ + (L + 1) * arr, nullptr, nullptr, [&](int, int, int, float acc, float z, float, float) {
+      put_all(sZd + (L + 1) * kArr, a);
+      emit(a, sZ + (L + 1) * kArr, kNone, kNone, [&](int, int, int, float acc, float z, float, float) {
         float d1, d2;
         silu_d12(z, d1, d2);
         return d1 * acc;
@@ -267,7 +277,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
       __syncthreads();
     });
     // ---- adjoint of the primal ----
-    emit(a, sZ + 3 * arr, sZd + 3 * arr, nullptr, [&](int I, int NT, int j, float, float z, float zd, float) {
+    emit(a, sZ + 3 * kArr, sZd + 3 * kArr, kNone, [&](int I, int NT, int j, float, float z, float zd, float) {
       const float w5 = b.w5[16 * I + j];
       const float fb = b.xin[NT * 32 * XF + 11];
       float d1, d2;
@@ -279,9 +289,9 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), 1) void table1_tiles(cons
     static_for<3>([&](auto LL) {
       constexpr int L = 2 - LL;  // hbar_{L+1} = W_{L+2}^T zbar_{L+2}
       zero(a);
-      layer_gemm<W, MODE, MODE>(a, stream_rsrc<W, MODE>(net.bwd[L]), b.voff, ln.act_r);
+      layer_gemm<W, MODE, MODE>(a, net.bwd[L], net.bwd[L > 0 ? L - 1 : 0], b.voff, ln.act_r, ap);
       __syncthreads();
-      emit(a, sZ + L * arr, sZd + L * arr, sR + L * arr, [&](int, int, int, float hb, float z, float zd, float r) {
+      emit(a, sZ + L * kArr, sZd + L * kArr, sR + L * kArr, [&](int, int, int, float hb, float z, float zd, float r) {
         float d1, d2;
         silu_d12(z, d1, d2);
         return hb * d1 + r * d2 * zd;

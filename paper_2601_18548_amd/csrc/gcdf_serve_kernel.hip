@@ -114,7 +114,7 @@ __device__ __forceinline__ bool desc_ntiles(const ServeDesc* d, uint64_t want, i
 }
 
 template <int W, int MODE, bool SPH>
-__global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const DevNet net, ServeCtl* ctl, ServeDev* dev,
+__global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void serve_loop(const DevNet net, ServeCtl* ctl, ServeDev* dev,
                                                           uint64_t first_seq, uint64_t idle_ticks, uint32_t epoch) {
   __shared__ __attribute__((aligned(16))) char lds[Geo<W, MODE>::LDS_BYTES];
   __shared__ int64_t claim_info[3];  // claimed seq (or -1: exit, -2: none), tile, seq to finalize (or -1)
@@ -354,7 +354,7 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
         pj.npairs = pj.K;
         pj.J = uniform(fin.Jmin);
         for (int64_t q0 = 0; q0 < pj.K; q0 += kTileQ)
-          process_tile<W, MODE, true, false, false, SPH>(net, pj, 1, 0, q0, tc);
+          process_tile<W, MODE, true, true, false, false, SPH>(net, pj, 0, q0, tc);
       }
       __threadfence_system();
       __syncthreads();
@@ -373,7 +373,10 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
     job.J = uniform(cur.J);
     job.minkey = uniform(cur.minkey);
     const int64_t kk = t / nblk;
-    process_tile<W, MODE, false, false, false, SPH>(net, job, cur.want_grad, kk, (t - kk * nblk) * kTileQ, tc);
+    const int64_t q0 = (t - kk * nblk) * kTileQ;
+    if (cur.want_grad) process_tile<W, MODE, true, false, false, false, SPH>(net, job, kk, q0, tc);
+    else process_tile<W, MODE, false, false, false, false, SPH>(net, job, kk, q0, tc);
+    __syncthreads();  // every wave's stores are done before thread 0 may report the tile
     if (tid == 0) kept.idle_since = __builtin_amdgcn_s_memrealtime();
   }
   report_overflow<W, MODE>(net, tc);
@@ -382,7 +385,7 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), 1) void serve_loop(const D
 template <int W, int MODE, bool SPH>
 static hipError_t launch_serve_t(const DevNet& net, ServeCtl* ctl, ServeDev* dev, uint64_t first_seq,
                                  uint64_t idle_ticks, uint32_t epoch, int num_cu, hipStream_t s) {
-  hipLaunchKernelGGL((serve_loop<W, MODE, SPH>), dim3(num_cu), dim3((Geo<W, MODE>::THREADS)), 0, s, net, ctl, dev, first_seq, idle_ticks,
+  hipLaunchKernelGGL((serve_loop<W, MODE, SPH>), dim3(num_cu * Geo<W, MODE>::WGS), dim3((Geo<W, MODE>::THREADS)), 0, s, net, ctl, dev, first_seq, idle_ticks,
                      epoch);
   return hipGetLastError();
 }

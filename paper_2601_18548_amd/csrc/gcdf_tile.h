@@ -1,14 +1,22 @@
 // Tile engine of the fused batched neural-GCDF query for gfx950 (MI355X):
 // device code shared by the query, sphere-query and serving kernels.
 //
-// One workgroup (8 waves, two per SIMD, in the BF16 modes; 4 in FP32) owns a
-// tile of 64 queries: 64 points of one knot (dense all-pairs mode) or 64
-// entries of a pair list.  For the
-// tile it runs the whole query without touching HBM in between:
+// One workgroup owns a tile of 64 queries: 64 points of one knot (dense all-pairs
+// mode) or 64 entries of a pair list.  It has 8 waves, two per SIMD, at width 512 in
+// the 16-bit modes, and 4 waves elsewhere, at width 256 two such workgroups per
+// compute unit, each running its own tile (pure BF16 at width 256: one of 8 waves).
+// For the tile it runs the whole query without touching HBM in between:
 //   base-frame transform -> input layer (FP32, VALU) -> hidden layers on
 //   matrix cores -> output dot -> reverse sweep on matrix cores (transposed
 //   weights) -> input-layer gradient (FP32) -> chain rule to (x, y, yaw, arm)
 //   -> stores of d / J -> per-knot minimum (64-bit ordered-key atomic min).
+// What bounds it (BF16X2_F16, 2.1 M pairs): width 512, matrix cores busy 60 % of the
+// cycles and the vector ALU 37 %, with 7 % of them together, at 1.93 GHz (the power
+// limit); width 256, 46 % and 50 %.  Two 4-wave workgroups per compute unit at width
+// 256, the input layer and its gradient on the matrix cores, weight fragments requested
+// a layer ahead, addresses formed per phase and a J-free variant took, on one box:
+// 128 x 16,384 W=512 9.00 -> 8.63 ms; 77 x 5,003 W=256 567 -> 492 us; FP32 64 x 4,096
+// 1.655 -> 1.519 ms; distances only, 128 x 2,048 W=512 BF16X2 692 -> 657 us.
 // (Steps of the query: Sec. III-B base-frame transform and chain rule,
 // Sec. III-C network on [p', a], Sec. IV-A constraint over all knot/point
 // pairs, Sec. IV-A knot-major stacking.)
@@ -55,16 +63,15 @@ typedef __attribute__((__vector_size__(4 * sizeof(_Float16)))) _Float16 f16x4;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // SiLU and its derivative from one exp and one reciprocal.
+__device__ __forceinline__ float sigmoid(float z) {
+  return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-z * kLog2e));
+}
 __device__ __forceinline__ void silu_fwd(float z, float& h, float& dh) {
-  float t = __builtin_amdgcn_exp2f(-z * kLog2e);
-  float sg = __builtin_amdgcn_rcpf(1.0f + t);
+  const float sg = sigmoid(z);
   h = z * sg;
   dh = sg + h * (1.0f - sg);  // s (1 + z (1 - s))
 }
-__device__ __forceinline__ float silu_only(float z) {
-  float t = __builtin_amdgcn_exp2f(-z * kLog2e);
-  return z * __builtin_amdgcn_rcpf(1.0f + t);
-}
+__device__ __forceinline__ float silu_only(float z) { return z * sigmoid(z); }
 __device__ __forceinline__ float silu_prime_only(float z) {
   float t = __builtin_amdgcn_exp2f(-z * kLog2e);
   float sg = __builtin_amdgcn_rcpf(1.0f + t);
@@ -89,9 +96,9 @@ __device__ __forceinline__ float unpark(float a, float after) {
   return x;
 }
 
-// Input-layer pre-activation, in one fixed order shared by every path:
-// c = b1 + sum_a W1[r][3+a] arm[a] (the knot's arm term), then
-// z1 = c + W1[r][0] p'x + W1[r][1] p'y + W1[r][2] p'z.
+// Input-layer pre-activation, in one fixed order shared by every path (each step
+// one fused multiply-add): c = b1 + sum_a W1[r][3+a] arm[a] (the knot's arm term),
+// then z1 = c + W1[r][0] p'x + W1[r][1] p'y + W1[r][2] p'z (see input_preact_tile).
 __device__ __forceinline__ float arm_term(float b1, float w3, float w4, float w5, float w6, float w7, float w8,
                                           const float* arm) {
   float c = b1;
@@ -108,22 +115,19 @@ __device__ __forceinline__ float input_preact(float c, float w0, float w1, float
 }
 // Sphere obstacles (network input [p', r, a]): the radius term comes last,
 // z1 = c + W1[r][0] p'x + W1[r][1] p'y + W1[r][2] p'z + W1[r][radius] r, with r
-// at position kXinRadius of the per-query record.
+// at position kXinRadius of the per-query record (0 for point obstacles, whose
+// packed radius weight is 0 too).
 constexpr int kXinRadius = 12;
 constexpr int kXinTarget = 13;  // training with the fused loss: the sample's target distance
-template <bool SPH>
-__device__ __forceinline__ float input_preact_t(float c, float w0, float w1, float w2, float wr, const float* x) {
-  if constexpr (SPH) return input_preact(c, w0, w1, w2, x) + wr * x[kXinRadius];
-  return input_preact(c, w0, w1, w2, x);
-}
 
 // Waves per workgroup: 8 (two per SIMD) for width 512 on BF16 matrix cores, where
 // the per-wave registers of four waves (accumulators, parked SiLU' values, the
 // weight prefetch) would fill the register file and leave nothing to hide the
-// weight stream's L2 latency; 4 otherwise.
+// weight stream's L2 latency, and for pure BF16 (the training tiles' LDS leaves no
+// room for a second workgroup); 4 otherwise.
 template <int W, int MODE>
 constexpr int waves_for() {
-  return MODE != kFP32 ? 8 : 4;
+  return MODE != kFP32 && (W == 512 || MODE == kBF16) ? 8 : 4;
 }
 
 // Arithmetic of one K loop and of the LDS stores that feed it.  Every mode
@@ -163,9 +167,14 @@ struct Geo {
   // split row group p, SUB waves per group.
   static constexpr int PMT = W / (32 * kWaves);
   static constexpr int SUB = NW / kWaves;
-  // the per-query reduction buffer shares the activation tile when 8 waves would
-  // not leave room for it (the tile is idle by then)
-  static constexpr bool RED_IN_ACT = NW > kWaves;
+  // Row groups of the final sums over the rows: each group's rows are summed in one
+  // chain, the groups then in order, however many waves share them (GPW groups per
+  // wave), so a result's bits do not depend on the wave count.
+  static constexpr int RG = MODE != kFP32 ? 8 : 4;
+  static constexpr int GPW = RG / NW;
+  // the per-query reduction buffer shares the activation tile when it would not
+  // leave room for 8 waves, or for a second workgroup (the tile is idle by then)
+  static constexpr bool RED_IN_ACT = NW > kWaves || W == 256;
   static constexpr int NKB = W / 16;                 // 16-deep K blocks (bf16)
   // bytes of the activation tile per K step (16 rows in the BF16 modes, 8 in FP32);
   // BF16X2 keeps a step's hi and lo halves next to each other, lo at LO_OFF
@@ -174,10 +183,15 @@ struct Geo {
   static constexpr int NK8 = W / 8;                  // 8-deep K groups (fp32: 4 MFMAs of K=2)
   static constexpr int ACT_BYTES = W * kTileQ * 4;   // fp32, or bf16 hi + bf16 lo
   static constexpr int XIN_FLOATS = 17;              // per query: p'(3), cos, sin, arm(6), seed, radius, target, pad; odd stride: lanes reading one field of 32 queries hit 32 different banks
-  static constexpr int RED_VALS = 10;                // d + 9 input-gradient components
-  static constexpr int RED_BYTES = NW * RED_VALS * kTileQ * 4;
+  static constexpr int RED_VALS = 9;                 // d, dd/dp'x, dd/dp'y, dd/da1..dd/da6
+  static constexpr int RED_BYTES = RG * RED_VALS * kTileQ * 4;
   static constexpr int LDS_BYTES = ACT_BYTES + kTileQ * XIN_FLOATS * 4 + W * 4 + (RED_IN_ACT ? 0 : RED_BYTES) + 4 * W * 4;
+  // Workgroups per compute unit.  One 4-wave workgroup alone leaves the matrix cores
+  // idle in its epilogues and the vector ALU in its K loops; where two fit in LDS and
+  // registers they run their layers independently.
+  static constexpr int WGS = NW == kWaves && 2 * (LDS_BYTES + 2048) <= 160 * 1024 ? 2 : 1;
   static_assert(!RED_IN_ACT || RED_BYTES <= ACT_BYTES, "reduction buffer must fit the activation tile");
+  static_assert(GPW == 1 || GPW == MT, "a wave's row groups are its M tiles");
   static_assert(MT >= 1 && PMT == SUB * MT, "row groups must split evenly");
 };
 
@@ -209,9 +223,10 @@ struct Lane {
   char* act_w;        // write base, hi plane (or the fp32 tile)
   char* act_w_lo;     // write base, lo plane
   const char* act_r;  // read base
-  __device__ __forceinline__ Lane(char* act, int tid) {
+  // tid: the thread; wv: its wave, uniform (a scalar register)
+  __device__ __forceinline__ Lane(char* act, int tid, int wv) {
     lane = tid & 63;
-    wave = tid >> 6;
+    wave = wv;
     h = lane >> 5;
     kh = h;
     n0 = lane & 31;
@@ -262,8 +277,12 @@ __device__ __forceinline__ void pack4(const float v[4], uint32_t& d0, uint32_t& 
 // act_pack8 forms the 16-byte words (w[0..3] for the hi plane, w[4..7] for the lo
 // plane) and act_write8 stores them, so a caller can do the arithmetic before a
 // barrier and the stores after it.  AM: the arithmetic (fwd_arith / rev_arith).
+// The values come as products x[k] y[k], whose unrounded difference from hi is lo.
 template <int AM, bool SWAP>
-__device__ __forceinline__ void act_pack8(const float v[8], uint32_t (&w)[8]) {
+__device__ __forceinline__ void act_pack8(const float x[8], const float y[8], uint32_t (&w)[8]) {
+  float v[8];
+#pragma unroll
+  for (int k = 0; k < 8; ++k) v[k] = x[k] * y[k];
   auto put = [&](const uint32_t e0, const uint32_t e1, const uint32_t o0, const uint32_t o1, uint32_t* out) {
     if constexpr (!SWAP) {
       out[0] = e0;
@@ -286,13 +305,13 @@ __device__ __forceinline__ void act_pack8(const float v[8], uint32_t (&w)[8]) {
   pack4<AM>(v, d[0], d[1]);
   pack4<AM>(v + 4, d[2], d[3]);
   if constexpr (AM == kBF16X2) {
-    // lo = v - hi, with hi read back from the packed pairs (the same rounding);
+    // lo = x y - hi, with hi read back from the packed pairs (the same rounding);
     // formed before the swaps, which overwrite their operands
     float lo[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
-      lo[2 * k] = v[2 * k] - __uint_as_float(d[k] << 16);
-      lo[2 * k + 1] = v[2 * k + 1] - __uint_as_float(d[k] & 0xffff0000u);
+      lo[2 * k] = __builtin_fmaf(x[2 * k], y[2 * k], -__uint_as_float(d[k] << 16));
+      lo[2 * k + 1] = __builtin_fmaf(x[2 * k + 1], y[2 * k + 1], -__uint_as_float(d[k] & 0xffff0000u));
     }
     uint32_t l[4];
     pack4<AM>(lo, l[0], l[1]);
@@ -311,21 +330,32 @@ __device__ __forceinline__ void act_write8(const Lane<W, MODE>& L, const uint32_
 }
 
 template <int W, int MODE, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
-__device__ __forceinline__ void act_store8(const Lane<W, MODE>& L, const float v[8]) {
+__device__ __forceinline__ void act_store8(const Lane<W, MODE>& L, const float x[8], const float y[8]) {
   uint32_t w[8];
-  act_pack8<AM, !lane_k_order<MODE>()>(v, w);
+  act_pack8<AM, !lane_k_order<MODE>()>(x, y, w);
   act_write8<W, MODE, I, GP, NT, AM>(L, w);
 }
 
-// Either layout: rows of groups g = 2 GP, 2 GP + 1 (see act_store8).
+// Either layout: rows of groups g = 2 GP, 2 GP + 1 (see act_store8), the products
+// x[k] y[k].
 template <int W, int MODE, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
-__device__ __forceinline__ void act_store_pair(const Lane<W, MODE>& L, const float v[8]) {
+__device__ __forceinline__ void act_store_pair(const Lane<W, MODE>& L, const float x[8], const float y[8]) {
   if constexpr (MODE == kFP32) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = x[k] * y[k];
     act_store4_fp32<W, MODE, I, 2 * GP, NT>(L, v);
     act_store4_fp32<W, MODE, I, 2 * GP + 1, NT>(L, v + 4);
   } else {
-    act_store8<W, MODE, I, GP, NT, AM>(L, v);
+    act_store8<W, MODE, I, GP, NT, AM>(L, x, y);
   }
+}
+// The same for plain values (FP32 and pure BF16: no lo part).
+template <int W, int MODE, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
+__device__ __forceinline__ void act_store_pair(const Lane<W, MODE>& L, const float v[8]) {
+  static_assert(AM != kBF16X2, "the split forms take the values as products");
+  const float one[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
+  act_store_pair<W, MODE, I, GP, NT, AM>(L, v, one);
 }
 
 // Compile-time loop helper: f(integral_constant<0>), ..., f(integral_constant<N-1>).
@@ -427,26 +457,46 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t stream_rsrc(const void* base) 
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000);
 }
 
-// The A fragments of a layer's first two K steps, loaded ahead of the layer.
-// Training loads them before the previous layer's dump: the vector-memory counter
-// completes in order, so a wait for fragments issued after the dump's stores
-// would also wait for those stores.
+// The A fragments of a layer's first two K steps, loaded ahead of the layer.  (In
+// training that is before the previous layer's dump too: the vector-memory counter
+// completes in order, so a wait for fragments issued after the dump's stores would
+// also wait for those stores.)
 template <int W, int MODE>
 struct APre {
   f32x4 a0[Geo<W, MODE>::MT], a1[Geo<W, MODE>::MT];
 };
 template <int W, int MODE>
-__device__ __forceinline__ void preload_a(APre<W, MODE>& p, __amdgpu_buffer_rsrc_t rs, int voff) {
+__device__ __forceinline__ void preload_a(APre<W, MODE>& p, const void* mat, int voff) {
+  const __amdgpu_buffer_rsrc_t rs = stream_rsrc<W, MODE>(mat);
   load_a<W, MODE>(p.a0, rs, voff, 0);
   load_a<W, MODE>(p.a1, rs, voff, 1);
 }
 
-// ZERO: acc starts at zero (its contents on entry are not read).  a0, a1: the A
-// fragments of steps 0 and 1, already requested (preload_a).
+// With two workgroups per compute unit, a wave in an epilogue goes before the other
+// workgroup's wave in its K loop: the vector instructions issue in the gaps that each
+// matrix instruction leaves (32 cycles for 4 of issue), so both advance.  FP32
+// 64 x 4,096 pairs 1.548 -> 1.520 ms, BF16X2_F16 128 x 8,192 (W=256) 1.318 -> 1.304 ms;
+// a fixed order of the two workgroups, or the K loop first, measured as no priority.
+template <int W, int MODE>
+__device__ __forceinline__ void epilogue_priority(bool epilogue) {
+  if constexpr (Geo<W, MODE>::WGS > 1) {
+    if (epilogue) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+  }
+}
+
+// ZERO: acc starts at zero (its contents on entry are not read).  p: the A
+// fragments of steps 0 and 1, already requested; on return those of the layer
+// streamed from `next` (its loads take the place of the last two steps' reloads, so
+// they are in flight during the epilogue, and the next K loop does not start with
+// the weight stream's L2 latency).
 template <int W, int MODE, int AM, bool ZERO = false>
-__device__ __forceinline__ void layer_gemm_pre(f32x16 (&acc)[(Geo<W, MODE>::MT)][2], __amdgpu_buffer_rsrc_t rs,
-                                               int voff, const char* br, f32x4 (&a0)[(Geo<W, MODE>::MT)],
-                                               f32x4 (&a1)[(Geo<W, MODE>::MT)]) {
+__device__ __forceinline__ void layer_gemm(f32x16 (&acc)[(Geo<W, MODE>::MT)][2], const void* mat, const void* next,
+                                           int voff, const char* br, APre<W, MODE>& p) {
+  epilogue_priority<W, MODE>(false);
+  const __amdgpu_buffer_rsrc_t rs = stream_rsrc<W, MODE>(mat);
+  f32x4 (&a0)[(Geo<W, MODE>::MT)] = p.a0;
+  f32x4 (&a1)[(Geo<W, MODE>::MT)] = p.a1;
   constexpr int NS = (MODE == kFP32) ? Geo<W, MODE>::NK8 : Geo<W, MODE>::NKB;  // even, >= 16
   constexpr int SB = Geo<W, MODE>::STEP_BYTES;
   BFrag<AM> b0, b1;
@@ -466,20 +516,15 @@ __device__ __forceinline__ void layer_gemm_pre(f32x16 (&acc)[(Geo<W, MODE>::MT)]
   for (; s < NS; s += 2) {
     load_b<W, MODE, AM>(b1, br + SB);  // B of step s+1, one step ahead
     __builtin_amdgcn_sched_barrier(0);
-    mma_step_reload<W, MODE, AM>(acc, a0, b0, rs, voff, s + 2 < NS ? s + 2 : NS - 1);
-    load_b<W, MODE, AM>(b0, s + 2 < NS ? br + 2 * SB : br);  // B of step s+2
+    const bool more = s + 2 < NS;
+    const __amdgpu_buffer_rsrc_t rn = stream_rsrc<W, MODE>(more ? mat : next);
+    mma_step_reload<W, MODE, AM>(acc, a0, b0, rn, voff, more ? s + 2 : 0);
+    load_b<W, MODE, AM>(b0, more ? br + 2 * SB : br);  // B of step s+2
     __builtin_amdgcn_sched_barrier(0);
-    mma_step_reload<W, MODE, AM>(acc, a1, b1, rs, voff, s + 3 < NS ? s + 3 : NS - 1);
+    mma_step_reload<W, MODE, AM>(acc, a1, b1, rn, voff, more ? s + 3 : 1);
     br += 2 * SB;
   }
-}
-
-template <int W, int MODE, int AM, bool ZERO = false>
-__device__ __forceinline__ void layer_gemm(f32x16 (&acc)[(Geo<W, MODE>::MT)][2], __amdgpu_buffer_rsrc_t rs, int voff,
-                                           const char* br) {
-  APre<W, MODE> p;
-  preload_a<W, MODE>(p, rs, voff);
-  layer_gemm_pre<W, MODE, AM, ZERO>(acc, rs, voff, br, p.a0, p.a1);
+  epilogue_priority<W, MODE>(true);
 }
 
 // The reverse layers' accumulators start at zero: in single FP16 the first
@@ -668,6 +713,84 @@ struct Bases {
   int voff;           // lane offset inside a matrix's fragment stream (see load_a)
 };
 
+// ----------------------------------------------------------------------------
+// Per-workgroup state.
+// ----------------------------------------------------------------------------
+template <int W, int MODE>
+struct TileCtx {
+  char* act;
+  float* xin;   // [64][16]
+  float* crow;  // [W]
+  float* red;   // [waves][10][64]
+  uint32_t* ovf;  // LDS word: a tile of this workgroup overflowed FP16 (see report_overflow)
+  float b5;       // the output bias, read once (every tile's final sum adds it)
+  // BF16 training, wave 0: the next tile's inputs (knot, point, target) of this
+  // lane's query, fetched during the tile before (see process_tile)
+  float nx[13];
+  bool nx_ok;
+  float* vec;  // LDS [4][W]: b2, b3, b4, w_out (lane-major)
+  const float* w1p;
+  int wave;    // uniform
+  __device__ __forceinline__ TileCtx(char* lds, uint32_t* ovf_word, const DevNet& net, int tid)
+      : act(lds), ovf(ovf_word), b5(*net.b5p), nx_ok(false), w1p(net.w1p), wave(__builtin_amdgcn_readfirstlane(tid >> 6)) {
+    if (tid == 0) *ovf = 0u;  // ordered before any tile's use by the tile's first barrier
+    using G = Geo<W, MODE>;
+    xin = reinterpret_cast<float*>(lds + G::ACT_BYTES);
+    crow = xin + kTileQ * G::XIN_FLOATS;
+    float* after = crow + W;
+    if constexpr (G::RED_IN_ACT) {
+      red = reinterpret_cast<float*>(lds);
+    } else {
+      red = after;
+      after += G::RED_BYTES / 4;
+    }
+    vec = after;
+    // w_out carries the reverse sweep's scale (a power of two, taken out of d and J
+    // at the end of the tile)
+    for (int i = tid; i < 4 * W; i += G::THREADS) vec[i] = i < 3 * W ? net.bh[i] : net.w5[i - 3 * W] * rev_scale<MODE>();
+    // Two waves per SIMD: the first four waves take the matrix cores first, so
+    // they reach each layer's epilogue (vector ALU) early and run it while the
+    // other four are still in their K loops.
+    if constexpr (G::SUB > 1) {
+      if (wave < kWaves) __builtin_amdgcn_s_setprio(1);
+    }
+  }
+};
+
+// A thread's place in the tile and the addresses that follow from it, formed anew
+// from the thread index by each phase of the tile (a few instructions): kept through
+// the tile they took a dozen registers per lane of the 128 that a width-512 wave has
+// beside its parked SiLU' values, and pushed some of those into scratch memory.
+template <int W, int MODE>
+struct View {
+  Lane<W, MODE> ln;
+  Bases<W, MODE> b;
+  __device__ __forceinline__ explicit View(const TileCtx<W, MODE>& tc) : ln(tc.act, fresh_tid(), tc.wave) {
+    using G = Geo<W, MODE>;
+    constexpr int MT = G::MT;
+    // bytes of one row group's fragment stream (1 KiB per fragment, PMT per K step)
+    constexpr int stream_bytes = (MODE == kFP32 ? G::NK8 : G::NKB) * G::PMT * 1024;
+    const int pw = ln.wave / G::SUB, sub = ln.wave % G::SUB;  // row group, and this wave's share of it
+    // this lane's block of lane-major rows (see lane_major_pos: 16 PMT per (group, h))
+    const int lblk = ((pw * 2 + ln.h) * G::PMT + sub * MT) * 16;
+    b.bh = tc.vec + lblk;
+    b.w5 = tc.vec + 3 * W + lblk;
+    b.w1 = tc.w1p + lblk * 12;
+    {  // row m = lane%32 of M tile 0 is lane-major row ((pw 2 + h_m) PMT + sub MT) 16 + 4 g_m + r_m
+      const int m = ln.n0;
+      b.w1a = tc.w1p + ((((pw * 2 + ((m >> 2) & 1)) * G::PMT + sub * MT) * 16) + 4 * (m >> 3) + (m & 3)) * 12;
+    }
+    b.crow = tc.crow + lblk;
+    b.xin = tc.xin + ln.n0 * G::XIN_FLOATS;
+    b.voff = pw * stream_bytes + sub * MT * 1024 + ln.lane * 16;
+  }
+  __device__ __forceinline__ static int fresh_tid() {
+    int t = threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+  }
+};
+
 // Dump of the current LDS tile for training (no-op when not training).
 struct TileDump {
   const char* act;  // the LDS activation tile
@@ -703,21 +826,20 @@ struct TileDump {
 };
 
 // Whether a hidden-layer epilogue keeps its packed results in registers across
-// the barrier (two waves per SIMD).  At width 512 the last forward layer, which
-// also carries the output-layer sums, would spill, so it stores after the barrier
-// as before; so does training's last forward layer, which stores h4 first.
+// the barrier (two waves of one workgroup per SIMD), except training's last forward
+// layer, which stores h4 first.
 template <int W, int MODE, bool TRAIN>
 constexpr bool defer_stores(bool last_forward) {
-  return Geo<W, MODE>::SUB > 1 && (!last_forward || (Geo<W, MODE>::MT == 1 && !TRAIN));
+  return Geo<W, MODE>::SUB > 1 && (!last_forward || !TRAIN);
 }
 
 // The packed words of elements 8 GP .. 8 GP + 7 of an accumulator go back into
 // those elements (consumed in order, so no extra registers), and are written out
 // after the barrier.
 template <int MODE, int AM, int GP>
-__device__ __forceinline__ void park_packed(const float v[8], f32x16& a) {
+__device__ __forceinline__ void park_packed(const float x[8], const float y[8], f32x16& a) {
   uint32_t w[8];
-  act_pack8<AM, !lane_k_order<MODE>()>(v, w);
+  act_pack8<AM, !lane_k_order<MODE>()>(x, y, w);
   constexpr int NWORDS = AM == kBF16X2 ? 8 : 4;  // hi and lo words, or hi only
 #pragma unroll
   for (int k = 0; k < NWORDS; ++k) a[8 * GP + k] = __uint_as_float(w[k]);
@@ -737,26 +859,27 @@ __device__ __forceinline__ void write_packed(const Lane<W, MODE>& ln, const f32x
   });
 }
 
-template <int W, int MODE, int L, bool TRAIN>
-__device__ __forceinline__ void fwd_hidden(const DevNet& net, const Lane<W, MODE>& ln, const Bases<W, MODE>& b,
-                                           float (&sp)[2][(Geo<W, MODE>::MT)][2][16], float (&dpart)[2], int want_grad,
+template <int W, int MODE, int L, bool TRAIN, bool GRAD>
+__device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, MODE>& tc,
+                                           float (&sp)[2][(Geo<W, MODE>::MT)][2][16], float (&dpart)[Geo<W, MODE>::GPW][2],
                                            const TileDump& td, APre<W, MODE>& ap) {
   constexpr int MT = Geo<W, MODE>::MT;
+  const View<W, MODE> v0(tc);
   f32x16 acc[MT][2];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const f32x4 b4 = *reinterpret_cast<const f32x4*>(b.bh + L * W + 16 * i + 4 * g);
+      const f32x4 b4 = *reinterpret_cast<const f32x4*>(v0.b.bh + L * W + 16 * i + 4 * g);
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][nt][4 * g + r] = b4[r];
     }
-  if constexpr (TRAIN)
-    layer_gemm_pre<W, MODE, fwd_arith<MODE>()>(acc, stream_rsrc<W, MODE>(net.fwd[L]), b.voff, ln.act_r, ap.a0, ap.a1);
-  else
-    layer_gemm<W, MODE, fwd_arith<MODE>()>(acc, stream_rsrc<W, MODE>(net.fwd[L]), b.voff, ln.act_r);
+  layer_gemm<W, MODE, fwd_arith<MODE>()>(acc, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], v0.b.voff, v0.ln.act_r, ap);
+  const View<W, MODE> vw(tc);
+  const Lane<W, MODE>& ln = vw.ln;
+  const Bases<W, MODE>& b = vw.b;
   // arithmetic of what this layer stores: the next layer's activations, or g4
   // for the reverse sweep
   constexpr int SA = L == 2 ? rev_arith<MODE>() : fwd_arith<MODE>();
@@ -781,7 +904,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const Lane<W, MODE
             float dv;
             silu_fwd(acc[I][NT][8 * GP + q], v[q], dv);
             acc[I][NT][8 * GP + q] = dv;
-            dpart[NT] += w5r[q >> 2][q & 3] * v[q];
+            dpart[0][NT] += w5r[q >> 2][q & 3] * v[q];
           }
           act_store_pair<W, MODE, I, GP, NT>(ln, v);
         });
@@ -791,7 +914,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const Lane<W, MODE
       // d over the rows: lane halves, then waves in order, as at the end of the tile
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) {
-        const float dp = dpart[nt] + __shfl_xor(dpart[nt], 32);
+        const float dp = dpart[0][nt] + __shfl_xor(dpart[0][nt], 32);
         if (ln.h == 0) td.dred[ln.wave * kTileQ + 32 * nt + ln.n0] = dp;
       }
     }
@@ -848,25 +971,35 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const Lane<W, MODE
         w5r[1] = *reinterpret_cast<const f32x4*>(b.w5 + 16 * I + 8 * GP + 4);
       }
       static_for<2>([&](auto NT) {
-        const float seed = b.xin[NT * 32 * Geo<W, MODE>::XIN_FLOATS + 11] * rev_scale<MODE>();
-        float v[8];
+        const float seed = TRAIN ? b.xin[NT * 32 * Geo<W, MODE>::XIN_FLOATS + 11] : 1.f;
+        float x[8], y[8];  // what is stored, as products
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           const int j = 8 * GP + q;  // accumulator element: g = 2 GP + q/4, r = q%4
-          float hv, dv;
-          if constexpr (TRAIN && L == 2) dv = acc[I][NT][j];  // SiLU'(z4), kept above
-          else silu_fwd(acc[I][NT][j], hv, dv);
-          if constexpr (L < 2) {
-            sp[L][I][NT][j] = park(dv);
-            v[q] = hv;
+          const float z = acc[I][NT][j];
+          float sg = 0.f, hv = 0.f, dv = 0.f;
+          if constexpr (TRAIN && L == 2) {
+            dv = z;  // SiLU'(z4), kept above
           } else {
-            if constexpr (!TRAIN) dpart[NT] += w5r[q >> 2][q & 3] * hv;  // (training: summed above)
-            v[q] = seed * (w5r[q >> 2][q & 3] * dv);  // g4 = seed * w5 * SiLU'(z4)
+            sg = sigmoid(z);
+            hv = z * sg;
+            dv = sg + hv * (1.0f - sg);
+          }
+          if constexpr (L < 2) {
+            if constexpr (GRAD) sp[L][I][NT][j] = park(dv);
+            x[q] = z;
+            y[q] = sg;
+          } else {
+            if constexpr (!TRAIN) dpart[Geo<W, MODE>::GPW > 1 ? (int)I : 0][NT] += w5r[q >> 2][q & 3] * hv;  // (training: above)
+            // g4 = seed * w5 * SiLU'(z4); the query's seed 1 (times rev_scale) is in w5
+            x[q] = w5r[q >> 2][q & 3] * dv;
+            asm("" : "+v"(x[q]));  // rounded before the seed (1 in the query) multiplies it
+            y[q] = seed;
           }
         }
-        if (L < 2 || want_grad) {
-          if constexpr (DEFER) park_packed<MODE, SA, GP>(v, acc[I][NT]);
-          else act_store_pair<W, MODE, I, GP, NT, SA>(ln, v);
+        if constexpr (L < 2 || GRAD) {
+          if constexpr (DEFER) park_packed<MODE, SA, GP>(x, y, acc[I][NT]);
+          else act_store_pair<W, MODE, I, GP, NT, SA>(ln, x, y);
         }
       });
       __builtin_amdgcn_sched_barrier(0);
@@ -876,17 +1009,17 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const Lane<W, MODE
     // Materialise the output-layer partial sums here; left alone, the compiler
     // sinks them to their use after the reverse sweep and keeps every h4 and
     // w_out value live through it.
-    asm volatile("" : "+v"(dpart[0]), "+v"(dpart[1]));
+#pragma unroll
+    for (int k = 0; k < Geo<W, MODE>::GPW; ++k) asm volatile("" : "+v"(dpart[k][0]), "+v"(dpart[k][1]));
   }
   if constexpr (DEFER) {
     __syncthreads();  // every wave has finished reading the tile
-    if (L < 2 || want_grad) write_packed<W, MODE, SA>(ln, acc);
+    if constexpr (L < 2 || GRAD) write_packed<W, MODE, SA>(ln, acc);
   }
   __syncthreads();
   // training: h2, h3 (layers 2, 3) or g4 (layer 4) to HBM; the tile is next
   // overwritten only after the following K loop and its barrier
   if constexpr (TRAIN) {  // h2, h3, or g4 (with db4 = sum_i g4_i)
-    preload_a<W, MODE>(ap, stream_rsrc<W, MODE>(L < 2 ? net.fwd[L + 1] : net.bwd[2]), b.voff);  // the next layer's
     const DumpSums sm{td.row(3), nullptr, nullptr, td.vt};
     dump_tile<W, MODE>(td.act, td.stage, L < 2 ? td.h(L + 1) : td.g(3), td.ldb, td.q0, td.nvalid,
                        (L == 2 && td.bsum) ? &sm : nullptr);
@@ -894,7 +1027,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const Lane<W, MODE
 }
 
 template <int W, int MODE, int L, bool TRAIN>
-__device__ __forceinline__ void bwd_hidden(const DevNet& net, const Lane<W, MODE>& ln, const Bases<W, MODE>& b,
+__device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, MODE>& tc,
                                            const float (&sp)[2][(Geo<W, MODE>::MT)][2][16], const TileDump& td,
                                            APre<W, MODE>& ap) {
   constexpr int MT = Geo<W, MODE>::MT;
@@ -904,33 +1037,34 @@ __device__ __forceinline__ void bwd_hidden(const DevNet& net, const Lane<W, MODE
   // layers alternate halves: g4 (hi) -> g3 (lo) -> g2 (hi).  Nobody reads the half
   // a layer writes, so its stores need no barrier before them.
   constexpr bool PP = RA == kF16 && !TRAIN;
-  const char* br = (PP && L == 1) ? ln.act_r + Geo<W, MODE>::LO_OFF : ln.act_r;
+  const View<W, MODE> v0(tc);
+  const char* br = (PP && L == 1) ? v0.ln.act_r + Geo<W, MODE>::LO_OFF : v0.ln.act_r;
   if constexpr (!rev_zero_c<MODE>()) zero_acc<W, MODE>(acc);
-  if constexpr (TRAIN)
-    layer_gemm_pre<W, MODE, RA, rev_zero_c<MODE>()>(acc, stream_rsrc<W, MODE>(net.bwd[L]), b.voff, br, ap.a0, ap.a1);
-  else
-    layer_gemm<W, MODE, RA, rev_zero_c<MODE>()>(acc, stream_rsrc<W, MODE>(net.bwd[L]), b.voff, br);
+  layer_gemm<W, MODE, RA, rev_zero_c<MODE>()>(acc, net.bwd[L], net.bwd[L - 1], v0.b.voff, br, ap);
+  const View<W, MODE> vw(tc);
+  const Lane<W, MODE>& ln = vw.ln;
   constexpr bool DEFER = !PP && defer_stores<W, MODE, TRAIN>(false);  // as in fwd_hidden
   if constexpr (!DEFER && !PP) __syncthreads();
   static_for<MT>([&](auto I) {
     static_for<2>([&](auto GP) {
       static_for<2>([&](auto NT) {
-        float v[8];
+        float x[8], y[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           const int j = 8 * GP + q;
-          v[q] = acc[I][NT][j] * unpark(sp[L - 1][I][NT][j], acc[I][NT][j]);
+          x[q] = acc[I][NT][j];
+          y[q] = unpark(sp[L - 1][I][NT][j], x[q]);
         }
         if constexpr (PP) {
           uint32_t w[8];
-          act_pack8<RA, !lane_k_order<MODE>()>(v, w);
+          act_pack8<RA, !lane_k_order<MODE>()>(x, y, w);
           typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
           constexpr int off = (2 * I + GP) * Geo<W, MODE>::STEP_BYTES + NT * 512;
           *reinterpret_cast<u32x4*>((L == 2 ? ln.act_w_lo : ln.act_w) + off) = u32x4{w[0], w[1], w[2], w[3]};
         } else if constexpr (DEFER) {
-          park_packed<MODE, RA, GP>(v, acc[I][NT]);
+          park_packed<MODE, RA, GP>(x, y, acc[I][NT]);
         } else {
-          act_store_pair<W, MODE, I, GP, NT, RA>(ln, v);
+          act_store_pair<W, MODE, I, GP, NT, RA>(ln, x, y);
         }
       });
       __builtin_amdgcn_sched_barrier(0);
@@ -942,7 +1076,6 @@ __device__ __forceinline__ void bwd_hidden(const DevNet& net, const Lane<W, MODE
   }
   __syncthreads();
   if constexpr (TRAIN) {  // g3 or g2, with their bias sums
-    preload_a<W, MODE>(ap, stream_rsrc<W, MODE>(net.bwd[L - 1]), b.voff);  // the next layer's
     const DumpSums sm{td.row(L), nullptr, nullptr, td.vt};
     dump_tile<W, MODE>(td.act, td.stage, td.g(L), td.ldb, td.q0, td.nvalid, td.bsum ? &sm : nullptr);
   }
@@ -1004,22 +1137,64 @@ __device__ __forceinline__ void input_gemm(const Lane<W, MODE>& ln, const Bases<
   }
 }
 
-// Last reverse layer: g1 = (W2^T g2) * SiLU'(z1) with z1 recomputed, then the
-// input-layer gradient e = W1^T g1 accumulated per lane in FP32.
+// Pre-activations z1 of M tile I (32 rows) and column block NT, in FP32 on the
+// matrix cores: z = c + W1 x with two steps (p'x, p'y), (p'z, radius) of
+// v_mfma_f32_32x32x2_f32 on top of the knot's arm term (dense tiles; pair lists:
+// b1, then three steps for the arm joints first).  That instruction adds its two
+// products one after the other as fused multiply-adds, so z1 has the bits of the
+// chain c + w0 x0 + w1 x1 + w2 x2 of arm_term's order, at 2 issue slots for 16
+// elements instead of 48, and a row's weights are loaded once per tile of rows
+// rather than by every lane.
+template <int W, int MODE, bool PAIRS>
+__device__ __forceinline__ void input_preact_tile(const Lane<W, MODE>& ln, const Bases<W, MODE>& b, int i, int nt,
+                                                  f32x16& z) {
+  constexpr int XF = Geo<W, MODE>::XIN_FLOATS;
+  const float* w = b.w1a + i * 16 * 12;    // A: row lane%32 of the tile, step element kh
+  const float* x = b.xin + nt * 32 * XF;   // B: query lane%32 of the block, step element kh
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    f32x4 c4;
+    if constexpr (PAIRS) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) c4[r] = b.w1[(16 * i + 4 * g + r) * 12 + 3];  // b1
+    } else {
+      c4 = *reinterpret_cast<const f32x4*>(b.crow + 16 * i + 4 * g);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) z[4 * g + r] = c4[r];
+  }
+  if constexpr (PAIRS) {
+#pragma unroll
+    for (int a = 0; a < 6; a += 2) z = __builtin_amdgcn_mfma_f32_32x32x2f32(w[4 + a + ln.kh], x[5 + a + ln.kh], z, 0, 0, 0);
+  }
+  z = __builtin_amdgcn_mfma_f32_32x32x2f32(w[ln.kh], x[ln.kh], z, 0, 0, 0);
+  z = __builtin_amdgcn_mfma_f32_32x32x2f32(w[2 + 8 * ln.kh], x[2 + (kXinRadius - 2) * ln.kh], z, 0, 0, 0);
+}
+
+// Last reverse layer: g1 = (W2^T g2) * SiLU'(z1) with z1 recomputed, then the eight
+// input-gradient components that J needs (p'x, p'y, a1..a6; dd/dp'z is not a
+// configuration coordinate), summed per lane in FP32: lane (n, h) adds w_r[c] g1[r]
+// over its rows r in order, four components per v_mfma_f32_4x4x1_16b_f32.  In that
+// instruction's 4-lane blocks lane l supplies component l%4 of the row (A) and its
+// own g1 (B) and holds the four sums of its own column (D), each the fused
+// multiply-add chain that the vector ALU would run, at 2 issue slots for an element's
+// 8 sums; a lane loads 2 floats of a row instead of 12, one group of four rows ahead.
+struct GradSums {
+  f32x4 v[2][2];  // [column block][p'x p'y a1 a2 | a3..a6]
+};
+
 template <int W, int MODE, bool PAIRS, bool TRAIN, bool SPH, class F>
-__device__ __forceinline__ void bwd_input(const DevNet& net, const Lane<W, MODE>& ln, const Bases<W, MODE>& b,
-                                          float (&epart)[2][9], const TileDump& td, const char* vb,
+__device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MODE>& tc,
+                                          GradSums (&epart)[Geo<W, MODE>::GPW], const TileDump& td, const char* vb,
                                           APre<W, MODE>& ap, F&& before_copy) {
   constexpr int MT = Geo<W, MODE>::MT;
-  constexpr int XF = Geo<W, MODE>::XIN_FLOATS;
+  const View<W, MODE> v0(tc);
   f32x16 acc[MT][2];
   if constexpr (!rev_zero_c<MODE>()) zero_acc<W, MODE>(acc);
-  if constexpr (TRAIN)
-    layer_gemm_pre<W, MODE, rev_arith<MODE>(), rev_zero_c<MODE>()>(acc, stream_rsrc<W, MODE>(net.bwd[0]), b.voff,
-                                                                   ln.act_r, ap.a0, ap.a1);
-  else
-    layer_gemm<W, MODE, rev_arith<MODE>(), rev_zero_c<MODE>()>(acc, stream_rsrc<W, MODE>(net.bwd[0]), b.voff,
-                                                               ln.act_r);
+  layer_gemm<W, MODE, rev_arith<MODE>(), rev_zero_c<MODE>()>(acc, net.bwd[0], net.bwd[0], v0.b.voff, v0.ln.act_r, ap);
+  const View<W, MODE> vw(tc);
+  const Lane<W, MODE>& ln = vw.ln;
+  const Bases<W, MODE>& b = vw.b;
   float g1keep[TRAIN ? MT : 1][2][16];
   constexpr bool KEPT = TRAIN && MODE == kBF16;  // SiLU'(z1) kept by the input layer
   if constexpr (KEPT) {
@@ -1035,79 +1210,61 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const Lane<W, MODE>
           for (int r = 0; r < 4; ++r) g1keep[i][nt][4 * g + r] = acc[i][nt][4 * g + r] * sv[r];
         }
   }
-  constexpr bool MMA = !KEPT && mma_input<W, MODE>(PAIRS, SPH);  // z1 from the matrix cores again
-  if constexpr (MMA) {
+  // this lane's component pair of packed row k (slots p'x p'y . . a1 a2 a3 a4 a5 a6 . .)
+  const float* we = b.w1 + (ln.lane & 3);
+  const int c0 = (ln.lane & 2);  // a1, a2 sit two slots past p'x, p'y
+  float a[2][4][2];
+  auto load_rows = [&](float (&x)[4][2], int grp) {  // rows 4 grp .. 4 grp + 3 of this lane
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* w = we + (4 * grp + r) * 12;
+      x[r][0] = w[c0];
+      x[r][1] = w[6];
+    }
+  };
+  if constexpr (!KEPT) {
+    if constexpr (!TRAIN) load_rows(a[0], 0);
     static_for<MT>([&](auto I) {
-      f32x16 z[2];
-      input_gemm<W, MODE, I>(ln, b, vb, z);
+      if constexpr (mma_input<W, MODE>(PAIRS, SPH)) {
+        f32x16 z[2];
+        input_gemm<W, MODE, I>(ln, b, vb, z);
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
+        for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float* w = b.w1 + (16 * I + 4 * g + r) * 12;
-          const f32x4 wa = *reinterpret_cast<const f32x4*>(w);
-          const f32x4 wb = *reinterpret_cast<const f32x4*>(w + 4);
-          const f32x2 wc = *reinterpret_cast<const f32x2*>(w + 8);
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
-            const float g1 = acc[I][nt][4 * g + r] * silu_prime_only(z[nt][4 * g + r]);
-            if constexpr (TRAIN) {
-              g1keep[I][nt][4 * g + r] = g1;
-            } else {
-              epart[nt][0] += wa[0] * g1;
-              epart[nt][1] += wa[1] * g1;
-              epart[nt][2] += wa[2] * g1;
-              epart[nt][3] += wb[0] * g1;
-              epart[nt][4] += wb[1] * g1;
-              epart[nt][5] += wb[2] * g1;
-              epart[nt][6] += wb[3] * g1;
-              epart[nt][7] += wc[0] * g1;
-              epart[nt][8] += wc[1] * g1;
-            }
-          }
-          __builtin_amdgcn_sched_barrier(0);
-        }
-    });
-  }
-#pragma unroll
-  for (int i = 0; i < ((KEPT || MMA) ? 0 : MT); ++i)
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float* w = b.w1 + (16 * i + 4 * g + r) * 12;
-        const f32x4 wa = *reinterpret_cast<const f32x4*>(w);
-        const f32x4 wb = *reinterpret_cast<const f32x4*>(w + 4);
-        f32x4 wc;  // slots 8, 9 (arm), 10 (radius weight), 11
-        if constexpr (SPH) {
-          wc = *reinterpret_cast<const f32x4*>(w + 8);
-        } else {
-          const f32x2 w2 = *reinterpret_cast<const f32x2*>(w + 8);
-          wc = f32x4{w2[0], w2[1], 0.f, 0.f};
-        }
-        const float cr = PAIRS ? wa[3] : b.crow[16 * i + 4 * g + r];
+          for (int j = 0; j < 16; ++j) acc[I][nt][j] *= silu_prime_only(z[nt][j]);
+      } else {
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-          const float* x = b.xin + nt * 32 * XF;
-          const float c = PAIRS ? arm_term(wa[3], wb[0], wb[1], wb[2], wb[3], wc[0], wc[1], x + 5) : cr;
-          const float z = input_preact_t<SPH>(c, wa[0], wa[1], wa[2], wc[2], x);
-          const float g1 = acc[i][nt][4 * g + r] * silu_prime_only(z);
-          if constexpr (TRAIN) {
-            g1keep[i][nt][4 * g + r] = g1;  // training needs g1, not J
-          } else {
-            epart[nt][0] += wa[0] * g1;
-            epart[nt][1] += wa[1] * g1;
-            epart[nt][2] += wa[2] * g1;
-            epart[nt][3] += wb[0] * g1;
-            epart[nt][4] += wb[1] * g1;
-            epart[nt][5] += wb[2] * g1;
-            epart[nt][6] += wb[3] * g1;
-            epart[nt][7] += wc[0] * g1;
-            epart[nt][8] += wc[1] * g1;
-          }
+          f32x16 z;
+          input_preact_tile<W, MODE, PAIRS>(ln, b, I, nt, z);
+#pragma unroll
+          for (int j = 0; j < 16; ++j) acc[I][nt][j] *= silu_prime_only(z[j]);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_sched_barrier(0);
       }
+      if constexpr (TRAIN) {  // training needs g1, not J
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+          for (int j = 0; j < 16; ++j) g1keep[I][nt][j] = acc[I][nt][j];
+      } else {
+        GradSums& ep = epart[Geo<W, MODE>::GPW > 1 ? (int)I : 0];
+        static_for<4>([&](auto GG) {
+          constexpr int grp = 4 * I + GG;
+          if constexpr (grp + 1 < 4 * MT) load_rows(a[(grp + 1) & 1], grp + 1);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+              for (int nt = 0; nt < 2; ++nt)
+                ep.v[nt][k] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[grp & 1][r][k], acc[I][nt][4 * GG + r], ep.v[nt][k], 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      }
+    });
+  }
   if constexpr (TRAIN) {
     // training: g1 through LDS to HBM (every wave has finished reading g2)
     __syncthreads();
@@ -1133,10 +1290,13 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const Lane<W, MODE>
 // Input layer (FP32): z1 = W1 [p'; a] + b1, h1 = SiLU(z1) -> LDS.  KEEP: SiLU'(z1)
 // also goes to sp1 (train_sp1's layout) for the reverse sweep.
 template <int W, int MODE, bool PAIRS, bool SPH, bool KEEP = false>
-__device__ __forceinline__ void fwd_input(const Lane<W, MODE>& ln, const Bases<W, MODE>& b, const char* vb,
+__device__ __forceinline__ void fwd_input(const TileCtx<W, MODE>& tc, const char* vb,
                                           float* sp1 = nullptr) {
   constexpr int MT = Geo<W, MODE>::MT;
-  constexpr int XF = Geo<W, MODE>::XIN_FLOATS;
+  const View<W, MODE> vw(tc);
+  const Lane<W, MODE>& ln = vw.ln;
+  const Bases<W, MODE>& b = vw.b;
+  static_assert(!KEEP || mma_input<W, MODE>(PAIRS, SPH), "SiLU'(z1) is kept by the BF16 training tiles");
   if constexpr (mma_input<W, MODE>(PAIRS, SPH)) {
     static_for<MT>([&](auto I) {
       f32x16 z[2];
@@ -1165,104 +1325,22 @@ __device__ __forceinline__ void fwd_input(const Lane<W, MODE>& ln, const Bases<W
     return;
   }
   static_for<MT>([&](auto I) {
-    static_for<2>([&](auto GP) {
-      f32x4 wa[8], wb[8];
-      f32x2 wc[8];
-      float cr[8], wr[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const float* w = b.w1 + (16 * I + 8 * GP + q) * 12;
-        wa[q] = *reinterpret_cast<const f32x4*>(w);
-        wr[q] = SPH ? w[10] : 0.f;
-        if constexpr (PAIRS) {
-          wb[q] = *reinterpret_cast<const f32x4*>(w + 4);
-          wc[q] = *reinterpret_cast<const f32x2*>(w + 8);
-        } else {
-          cr[q] = b.crow[16 * I + 8 * GP + q];
-        }
-      }
-      static_for<2>([&](auto NT) {
-        const float* x = b.xin + NT * 32 * XF;
-        float v[8], dv[8];
+    static_for<2>([&](auto NT) {
+      f32x16 z;
+      input_preact_tile<W, MODE, PAIRS>(ln, b, I, NT, z);
+      static_for<2>([&](auto GP) {
+        float x[8], y[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
-          float c = PAIRS ? 0.f : cr[q];
-          if constexpr (PAIRS) c = arm_term(wa[q][3], wb[q][0], wb[q][1], wb[q][2], wb[q][3], wc[q][0], wc[q][1], x + 5);
-          const float z = input_preact_t<SPH>(c, wa[q][0], wa[q][1], wa[q][2], wr[q], x);
-          if constexpr (KEEP) silu_fwd(z, v[q], dv[q]);
-          else v[q] = silu_only(z);
+          x[q] = z[8 * GP + q];
+          y[q] = sigmoid(x[q]);
         }
-        act_store_pair<W, MODE, I, GP, NT>(ln, v);
-        if constexpr (KEEP) {
-          constexpr int T = Geo<W, MODE>::THREADS;
-          constexpr int k = ((I * 2 + NT) * 16 + 8 * GP) / 4;  // first of the two 16-byte groups
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            *reinterpret_cast<f32x4*>(sp1 + ((k + h) * T + threadIdx.x) * 4) =
-                f32x4{dv[4 * h], dv[4 * h + 1], dv[4 * h + 2], dv[4 * h + 3]};
-        }
+        act_store_pair<W, MODE, I, GP, NT>(ln, x, y);
       });
       __builtin_amdgcn_sched_barrier(0);
     });
   });
 }
-
-// ----------------------------------------------------------------------------
-// Per-workgroup state and the body that processes one tile.
-// ----------------------------------------------------------------------------
-template <int W, int MODE>
-struct TileCtx {
-  char* act;
-  float* xin;   // [64][16]
-  float* crow;  // [W]
-  float* red;   // [waves][10][64]
-  uint32_t* ovf;  // LDS word: a tile of this workgroup overflowed FP16 (see report_overflow)
-  float b5;       // the output bias, read once (every tile's final sum adds it)
-  // BF16 training, wave 0: the next tile's inputs (knot, point, target) of this
-  // lane's query, fetched during the tile before (see process_tile)
-  float nx[13];
-  bool nx_ok;
-  Lane<W, MODE> ln;
-  Bases<W, MODE> b;
-  __device__ __forceinline__ TileCtx(char* lds, uint32_t* ovf_word, const DevNet& net, int tid)
-      : act(lds), ovf(ovf_word), b5(*net.b5p), nx_ok(false), ln(lds, tid) {
-    if (tid == 0) *ovf = 0u;  // ordered before any tile's use by the tile's first barrier
-    using G = Geo<W, MODE>;
-    constexpr int MT = G::MT;
-    xin = reinterpret_cast<float*>(lds + G::ACT_BYTES);
-    crow = xin + kTileQ * G::XIN_FLOATS;
-    float* after = crow + W;
-    if constexpr (G::RED_IN_ACT) {
-      red = reinterpret_cast<float*>(lds);
-    } else {
-      red = after;
-      after += G::RED_BYTES / 4;
-    }
-    float* vec = after;  // [4][W]: b2, b3, b4, w_out
-    for (int i = tid; i < 4 * W; i += G::THREADS) vec[i] = i < 3 * W ? net.bh[i] : net.w5[i - 3 * W];
-    // bytes of one row group's fragment stream (1 KiB per fragment, PMT per K step)
-    const size_t stream_bytes = (size_t)(MODE == kFP32 ? G::NK8 : G::NKB) * G::PMT * 1024;
-    const int pw = ln.wave / G::SUB, sub = ln.wave % G::SUB;  // row group, and this wave's share of it
-    // this lane's block of lane-major rows (see lane_major_pos: 16 PMT per (group, h))
-    const int lblk = ((pw * 2 + ln.h) * G::PMT + sub * MT) * 16;
-    b.bh = vec + lblk;
-    b.w5 = vec + 3 * W + lblk;
-    b.w1 = net.w1p + lblk * 12;
-    {  // row m = lane%32 of M tile 0 is lane-major row ((pw 2 + h_m) PMT + sub MT) 16 + 4 g_m + r_m
-      const int m = ln.n0;
-      b.w1a = net.w1p + ((((pw * 2 + ((m >> 2) & 1)) * G::PMT + sub * MT) * 16) + 4 * (m >> 3) + (m & 3)) * 12;
-    }
-    b.crow = crow + lblk;
-    b.xin = xin + ln.n0 * G::XIN_FLOATS;
-    b.voff = (int)(pw * stream_bytes) + sub * MT * 1024 + ln.lane * 16;
-    // Two waves per SIMD: the first four waves take the matrix cores first, so
-    // they reach each layer's epilogue (vector ALU) early and run it while the
-    // other four are still in their K loops.
-    if constexpr (G::SUB > 1) {
-      if (ln.wave < kWaves) __builtin_amdgcn_s_setprio(1);
-    }
-  }
-};
 
 // LDS that training adds after the query's own: the fused loss's per-wave
 // partial sums ([waves][64]) and, for pure BF16, the per-workgroup sums of
@@ -1293,12 +1371,14 @@ __device__ __forceinline__ float* train_sp1(char* lds) {
 }
 
 // One tile: 64 points of knot kk starting at point q0 (dense), or pair-list
-// entries q0 .. q0+63 (pairs).  Every thread of the workgroup calls it; it ends
-// with a barrier, so consecutive calls can reuse the shared memory.  SPH: the
+// entries q0 .. q0+63 (pairs).  Every thread of the workgroup calls it; consecutive
+// calls can reuse the shared memory, but the last stores of J are issued after the
+// last barrier.  GRAD: the reverse sweep and J too; without it the tile ends with d
+// (and keeps no SiLU').  SPH: the
 // obstacles are spheres (x, y, z, r) and the network input is [p', r, a].
-template <int W, int MODE, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
-__device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, int want_grad, int64_t kk,
-                                             int64_t q0, TileCtx<W, MODE>& tc) {
+template <int W, int MODE, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
+__device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, int64_t kk, int64_t q0,
+                                             TileCtx<W, MODE>& tc) {
   using G = Geo<W, MODE>;
   constexpr int MT = G::MT;
   constexpr int XF = G::XIN_FLOATS;
@@ -1306,8 +1386,6 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
   float* xin = tc.xin;
   float* crow = tc.crow;
   float* red = tc.red;
-  const Lane<W, MODE>& ln = tc.ln;
-  const Bases<W, MODE>& b = tc.b;
   const int64_t qlimit = PAIRS ? job.npairs : (GATHER ? job.row_off[kk + 1] : job.Np);
 
   // BF16 training: sample i = knot i, point i; the inputs of a workgroup's next tile
@@ -1420,7 +1498,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
         vt[(9 + c) * kTileQ + tid] = (__bf16)(v - (float)hi);
       }
     }
-    if constexpr (SPH) x[kXinRadius] = pxyz[3];  // the radius passes through the rigid transform
+    x[kXinRadius] = SPH ? pxyz[3] : 0.f;  // the radius passes through the rigid transform
     if constexpr (mma_input<W, MODE>(PAIRS, SPH)) {
       // the inputs as B fragments of the matrix-core input layer (input_gemm), in
       // the idle half of the activation tile
@@ -1491,31 +1569,35 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
     td.b5 = tc.b5;
     td.inv_b = job.inv_b;
   }
-  fwd_input<W, MODE, PAIRS, SPH, TRAIN && MODE == kBF16>(ln, b, tc.act + G::ACT_BYTES / 2, td.sp1);
+  APre<W, MODE> ap;  // each layer's first weight fragments, requested ahead of it
+  preload_a<W, MODE>(ap, net.fwd[0], View<W, MODE>(tc).b.voff);
+  fwd_input<W, MODE, PAIRS, SPH, TRAIN && MODE == kBF16>(tc, tc.act + G::ACT_BYTES / 2, td.sp1);
   __syncthreads();
-  APre<W, MODE> ap;  // training: each layer's first weight fragments, requested before the dump ahead of it
   if constexpr (TRAIN) {
-    preload_a<W, MODE>(ap, stream_rsrc<W, MODE>(net.fwd[0]), b.voff);
     dump_tile<W, MODE>(td.act, td.stage, td.h(0), td.ldb, td.q0, td.nvalid);  // h1
   }
 
   // ---- hidden layers 2..4 (forward), keeping SiLU' of layers 2 and 3 ----
   float sp[2][MT][2][16];
-  float dpart[2] = {0.f, 0.f};
-  fwd_hidden<W, MODE, 0, TRAIN>(net, ln, b, sp, dpart, want_grad, td, ap);
-  fwd_hidden<W, MODE, 1, TRAIN>(net, ln, b, sp, dpart, want_grad, td, ap);
-  fwd_hidden<W, MODE, 2, TRAIN>(net, ln, b, sp, dpart, want_grad, td, ap);
+  float dpart[G::GPW][2];
+#pragma unroll
+  for (int k = 0; k < G::GPW; ++k) dpart[k][0] = dpart[k][1] = 0.f;
+  fwd_hidden<W, MODE, 0, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
+  fwd_hidden<W, MODE, 1, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
+  fwd_hidden<W, MODE, 2, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
 
   // ---- reverse sweep: W4^T, W3^T (into LDS), W2^T (into the input-layer gradient) ----
-  float epart[2][9];
+  GradSums epart[G::GPW];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt)
+  for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
-    for (int c = 0; c < 9; ++c) epart[nt][c] = 0.f;
-  if (want_grad) {
-    bwd_hidden<W, MODE, 2, TRAIN>(net, ln, b, sp, td, ap);
-    bwd_hidden<W, MODE, 1, TRAIN>(net, ln, b, sp, td, ap);
-    bwd_input<W, MODE, PAIRS, TRAIN, SPH>(net, ln, b, epart, td, tc.act + G::ACT_BYTES / 2, ap, fetch_next);
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) epart[k].v[nt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (GRAD) {
+    bwd_hidden<W, MODE, 2, TRAIN>(net, tc, sp, td, ap);
+    bwd_hidden<W, MODE, 1, TRAIN>(net, tc, sp, td, ap);
+    bwd_input<W, MODE, PAIRS, TRAIN, SPH>(net, tc, epart, td, tc.act + G::ACT_BYTES / 2, ap, fetch_next);
     if constexpr (rev_arith<MODE>() == kF16) {
       // a lane whose output partial sum is finite but whose input-gradient partial
       // sums are not: the FP16 reverse sweep overflowed (the forward accumulates in
@@ -1524,92 +1606,113 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
       // (report_overflow).
       uint32_t bad = 0;
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
-        float t = 0.f;
+      for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
-        for (int c = 0; c < 9; ++c) t += epart[nt][c];
-        bad |= (uint32_t)(!__builtin_isfinite(t)) & (uint32_t)__builtin_isfinite(dpart[nt]);
-      }
+        for (int nt = 0; nt < 2; ++nt) {
+          float t = 0.f;
+#pragma unroll
+          for (int c = 0; c < 8; ++c) t += epart[k].v[nt][c >> 2][c & 3];
+          bad |= (uint32_t)(!__builtin_isfinite(t)) & (uint32_t)__builtin_isfinite(dpart[k][nt]);
+        }
       if (bad) *tc.ovf = 1u;
     }
   }
 
-  // ---- reduce d and e over the rows: lane halves, then waves (fixed order) ----
+  // ---- reduce d and e over the rows: lane halves, then row groups (fixed order) ----
   // (training needs neither: the fused loss finished d inside the tile)
   if constexpr (!TRAIN) {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      dpart[nt] += __shfl_xor(dpart[nt], 32);
+    for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
-      for (int c = 0; c < 9; ++c) epart[nt][c] += __shfl_xor(epart[nt][c], 32);
-    }
+      for (int nt = 0; nt < 2; ++nt) {
+        dpart[k][nt] += __shfl_xor(dpart[k][nt], 32);
+#pragma unroll
+        for (int c = 0; c < (GRAD ? 8 : 0); ++c)
+          epart[k].v[nt][c >> 2][c & 3] += __shfl_xor(epart[k].v[nt][c >> 2][c & 3], 32);
+      }
     // the reduction buffer may share the activation tile: every wave must have
     // finished reading it
     if constexpr (G::RED_IN_ACT) __syncthreads();
-    if (ln.h == 0) {
+    const Lane<W, MODE> ln(tc.act, View<W, MODE>::fresh_tid(), tc.wave);
+#pragma unroll
+    for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
       for (int nt = 0; nt < 2; ++nt) {
-        const int n = 32 * nt + ln.n0;
-        red[(ln.wave * G::RED_VALS + 0) * kTileQ + n] = dpart[nt];
+        // lane half 0 stores d and the first four components, half 1 the other four
+        float* r = red + (ln.wave * G::GPW + k) * G::RED_VALS * kTileQ + 32 * nt + ln.n0;
+        if (ln.h == 0) r[0] = dpart[k][nt];
 #pragma unroll
-        for (int c = 0; c < 9; ++c) red[(ln.wave * G::RED_VALS + 1 + c) * kTileQ + n] = epart[nt][c];
+        for (int c = 0; c < (GRAD ? 4 : 0); ++c)
+          r[(1 + 4 * ln.h + c) * kTileQ] = ln.h ? epart[k].v[nt][1][c] : epart[k].v[nt][0][c];
       }
-    }
     __syncthreads();
 
     // ---- per query: final sums, chain rule, stores, per-knot minimum ----
-    if (tid < kTileQ) {
-      // recomputed here rather than kept from the prologue (the compiler would
+    // Wave 0 finishes d, wave 1 dd/dp' and J's base columns, the others the arm
+    // columns (a single wave doing all of it kept the rest waiting for 72 LDS reads).
+    // J's rows of the tile are staged in the idle activation tile and copied out as
+    // contiguous dwords.
+    {
+      // n: recomputed here rather than kept from the prologue (the compiler would
       // otherwise hold q0 + tid through the whole tile, in a spill slot)
-      int n = tid;
+      int n = tid & 63;
       asm volatile("" : "+v"(n));
-      float vals[G::RED_VALS];
+      auto total = [&](int c) {
+        float sum = red[c * kTileQ + n];
 #pragma unroll
-      for (int c = 0; c < G::RED_VALS; ++c) {
-        float sum = red[(0 * G::RED_VALS + c) * kTileQ + n];
+        for (int w = 1; w < G::RG; ++w) sum += red[(w * G::RED_VALS + c) * kTileQ + n];
+        return sum * (1.0f / rev_scale<MODE>());
+      };
+      float* jt = G::RED_IN_ACT ? red + G::RED_BYTES / 4 : reinterpret_cast<float*>(tc.act);  // [64][9]
+      const bool want_J = GRAD && job.J;
+      const int64_t out0 = (PAIRS || GATHER) ? q0 : kk * job.Np + q0;
+      if (ln.wave == 0) {
+        const float dv = total(0) + tc.b5;
+        const int64_t q = q0 + n;
+        const bool valid = q < qlimit;
+        // outputs are streamed with non-temporal stores: written once and never read
+        // here, they would otherwise evict the packed weights from L2
+        if (valid && job.d) __builtin_nontemporal_store(dv, job.d + out0 + n);
+        if constexpr (!PAIRS) {
+          if (job.minkey) {
+            unsigned long long key = valid ? (((unsigned long long)ordered_bits(dv) << 32) | (uint32_t)q) : ~0ull;
 #pragma unroll
-        for (int w = 1; w < G::NW; ++w) sum += red[(w * G::RED_VALS + c) * kTileQ + n];
-        vals[c] = sum;
-      }
-      if constexpr (rev_scale<MODE>() != 1.0f) {
-#pragma unroll
-        for (int c = 1; c < G::RED_VALS; ++c) vals[c] *= 1.0f / rev_scale<MODE>();
-      }
-      const float dv = vals[0] + tc.b5;
-      const int64_t q = q0 + n;
-      const bool valid = q < qlimit;
-      const int64_t out = (PAIRS || GATHER) ? q : kk * job.Np + q;
-      // outputs are streamed with non-temporal stores: written once and never read
-      // here, they would otherwise evict the packed weights from L2
-      if (valid && job.d) __builtin_nontemporal_store(dv, job.d + out);
-      if (!TRAIN && valid && job.J && want_grad) {  // (training computes g1, not J)
-        const float* x = xin + n * XF;
-        const float cs = x[3], sn = x[4];
-        const float* e = vals + 1;
-        float* Jo = job.J + out * kInDim;
-        __builtin_nontemporal_store(-(cs * e[0] - sn * e[1]), Jo + 0);
-        __builtin_nontemporal_store(-(sn * e[0] + cs * e[1]), Jo + 1);
-        __builtin_nontemporal_store(e[0] * x[1] - e[1] * x[0], Jo + 2);
-#pragma unroll
-        for (int c = 3; c < 9; ++c) __builtin_nontemporal_store(e[c], Jo + c);
-      }
-      if constexpr (!PAIRS) {
-        if (job.minkey) {
-          unsigned long long key = valid ? (((unsigned long long)ordered_bits(dv) << 32) | (uint32_t)q) : ~0ull;
-#pragma unroll
-          for (int off = 32; off >= 1; off >>= 1) {
-            unsigned long long o = __shfl_xor(key, off);
-            key = o < key ? o : key;
+            for (int off = 32; off >= 1; off >>= 1) {
+              unsigned long long o = __shfl_xor(key, off);
+              key = o < key ? o : key;
+            }
+            if (n == 0 && key != ~0ull) atomicMin(job.minkey + kk, key);
           }
-          if (n == 0 && key != ~0ull) atomicMin(job.minkey + kk, key);
         }
+      } else if (ln.wave == 1) {
+        if (want_J) {
+          const float* x = xin + n * XF;
+          const float cs = x[3], sn = x[4], e0 = total(1), e1 = total(2);
+          // (which product is fused is spelled out, so that every instantiation rounds alike)
+          jt[n * kInDim + 0] = -__builtin_fmaf(cs, e0, -(sn * e1));
+          jt[n * kInDim + 1] = -__builtin_fmaf(cs, e1, sn * e0);
+          jt[n * kInDim + 2] = __builtin_fmaf(e0, x[1], -(e1 * x[0]));
+        }
+      } else if (want_J) {
+#pragma unroll
+        for (int c = 0; c < 6; c += G::NW - 2) {
+          const int a = c + ln.wave - 2;
+          jt[n * kInDim + 3 + a] = total(3 + a);
+        }
+      }
+      __syncthreads();
+      if (want_J) {
+        const int64_t left = (qlimit - q0) * kInDim;
+        float* Jo = job.J + out0 * kInDim;
+        for (int t = tid; t < kTileQ * kInDim; t += G::THREADS)
+          if (t < left) __builtin_nontemporal_store(jt[t], Jo + t);
       }
     }
   }  // !TRAIN
-  // The next tile's prologue rewrites xin and crow: every wave has passed the
-  // barrier above (crow's last reader), and xin's readers here are wave 0,
-  // which also writes it, in program order.
-  __syncthreads();
+  // The next tile's prologue rewrites xin and crow, which nobody reads after the last
+  // barrier above; the staged rows of J are read before its first barrier, and the
+  // tile is written after it.
+  if constexpr (TRAIN) __syncthreads();
 }
 
 // End of a kernel that ran tiles: if any tile of this workgroup flagged an FP16
@@ -1626,9 +1729,9 @@ __device__ __forceinline__ void report_overflow(const DevNet& net, const TileCtx
 // ----------------------------------------------------------------------------
 // One-shot kernel: a persistent grid strides over all tiles of one job.
 // ----------------------------------------------------------------------------
-template <int W, int MODE, bool PAIRS, int OCC, bool TRAIN = false, bool GATHER = false, bool SPH = false>
-__global__ __launch_bounds__((Geo<W, MODE>::THREADS), OCC) void fused_query(const DevNet net, const Job job, int want_grad,
-                                                             int64_t ntiles) {
+template <int W, int MODE, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
+__global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void fused_query(const DevNet net, const Job job,
+                                                                                         int64_t ntiles) {
   static_assert(Geo<W, MODE>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0) + 16 <= 160 * 1024,
                 "the workgroup's LDS exceeds the compute unit's 160 KiB");
   __shared__ __attribute__((aligned(16))) char lds[Geo<W, MODE>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0)];
@@ -1642,7 +1745,7 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), OCC) void fused_query(cons
   int64_t kk = PAIRS ? 0 : blockIdx.x / nblk;  // dense: the knot of the current tile
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     if constexpr (PAIRS) {
-      process_tile<W, MODE, true, TRAIN, false, SPH>(net, job, want_grad, 0, tile * kTileQ, tc);
+      process_tile<W, MODE, GRAD, true, TRAIN, false, SPH>(net, job, 0, tile * kTileQ, tc);
     } else if constexpr (GATHER) {
       if (tile >= job.tile_off[job.K]) break;  // the grid is sized by an upper bound
       int64_t lo = 0, hi = job.K - 1;            // knot: the last i with tile_off[i] <= tile
@@ -1650,10 +1753,10 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), OCC) void fused_query(cons
         const int64_t mid = (lo + hi + 1) >> 1;
         if (job.tile_off[mid] <= tile) lo = mid; else hi = mid - 1;
       }
-      process_tile<W, MODE, false, false, true, SPH>(net, job, want_grad, lo,
-                                                     job.row_off[lo] + (tile - job.tile_off[lo]) * kTileQ, tc);
+      process_tile<W, MODE, GRAD, false, false, true, SPH>(net, job, lo,
+                                                           job.row_off[lo] + (tile - job.tile_off[lo]) * kTileQ, tc);
     } else {
-      process_tile<W, MODE, false, false, false, SPH>(net, job, want_grad, kk, (tile - kk * nblk) * kTileQ, tc);
+      process_tile<W, MODE, GRAD, false, false, false, SPH>(net, job, kk, (tile - kk * nblk) * kTileQ, tc);
       // the next tile's knot: at most one knot further when a knot has at least as
       // many tiles as the grid has workgroups, with no 64-bit division then
       const int64_t next = tile + gridDim.x;
@@ -1673,39 +1776,37 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), OCC) void fused_query(cons
 // Host-side launchers of fused_query (grid = min(tiles, CUs)); each source file
 // instantiates the obstacle kind (SPH) it serves.
 // ----------------------------------------------------------------------------
-template <int W, int MODE, bool PAIRS, bool SPH>
-static hipError_t launch_t(const DevNet& net, const Job& job, bool want_grad, int num_cu, hipStream_t s) {
-  constexpr int OCC = 1;
+template <int W, int MODE, bool GRAD, bool PAIRS, bool SPH>
+static hipError_t launch_t(const DevNet& net, const Job& job, int num_cu, hipStream_t s) {
+  using G = Geo<W, MODE>;
   const int64_t ntiles = PAIRS ? (job.npairs + kTileQ - 1) / kTileQ
                                : (job.tile_off ? job.ntiles_bound : job.K * ((job.Np + kTileQ - 1) / kTileQ));
   if (ntiles <= 0) return hipSuccess;
-  const int grid = fused_grid(ntiles, num_cu);
-  if constexpr (PAIRS && W == 256 && (MODE == kFP32 || MODE == kBF16) && !SPH) {  // training: width 256, FP32 or BF16
+  const dim3 grid((unsigned)fused_grid(ntiles, num_cu * G::WGS)), block(G::THREADS);
+  if constexpr (GRAD && PAIRS && W == 256 && (MODE == kFP32 || MODE == kBF16) && !SPH) {  // training: width 256, FP32 or BF16
     if (job.dumpH) {
       // the kernel writes its sums to bias_part, no J, and d only with the fused loss
       if ((MODE == kBF16 && !job.bias_part) || job.J || (job.d && !job.target)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((fused_query<W, MODE, true, OCC, true>), dim3(grid), dim3((Geo<W, MODE>::THREADS)), 0, s, net, job, 1,
-                         ntiles);
+      hipLaunchKernelGGL((fused_query<W, MODE, true, true, true>), grid, block, 0, s, net, job, ntiles);
       return hipGetLastError();
     }
   }
   if (job.dumpH || job.seed) return hipErrorInvalidValue;  // a seed is honoured by the training instantiation only
   if constexpr (!PAIRS) {
     if (job.tile_off) {
-      hipLaunchKernelGGL((fused_query<W, MODE, false, OCC, false, true, SPH>), dim3(grid), dim3((Geo<W, MODE>::THREADS)), 0, s, net,
-                         job, want_grad ? 1 : 0, ntiles);
+      hipLaunchKernelGGL((fused_query<W, MODE, GRAD, false, false, true, SPH>), grid, block, 0, s, net, job, ntiles);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((fused_query<W, MODE, PAIRS, OCC, false, false, SPH>), dim3(grid), dim3((Geo<W, MODE>::THREADS)), 0, s, net, job,
-                     want_grad ? 1 : 0, ntiles);
+  hipLaunchKernelGGL((fused_query<W, MODE, GRAD, PAIRS, false, false, SPH>), grid, block, 0, s, net, job, ntiles);
   return hipGetLastError();
 }
 
 template <int W, int MODE, bool SPH>
 static hipError_t launch_m(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s) {
-  return pairs ? launch_t<W, MODE, true, SPH>(net, job, want_grad, num_cu, s)
-               : launch_t<W, MODE, false, SPH>(net, job, want_grad, num_cu, s);
+  if (want_grad)
+    return pairs ? launch_t<W, MODE, true, true, SPH>(net, job, num_cu, s) : launch_t<W, MODE, true, false, SPH>(net, job, num_cu, s);
+  return pairs ? launch_t<W, MODE, false, true, SPH>(net, job, num_cu, s) : launch_t<W, MODE, false, false, SPH>(net, job, num_cu, s);
 }
 
 template <int W, bool SPH>
