@@ -419,7 +419,9 @@ gcdf_status gcdf_eval_grad_csr(gcdf_ctx* ctx, const float* knots, int64_t N, con
   hipStream_t s = static_cast<hipStream_t>(stream);
   // each knot's rows run as gathered dense tiles (one knot per tile): the arm term
   // of the input layer is computed once per tile, as in the dense query
-  hipError_t e = gcdf::launch_csr_tile_offsets(offsets, N, ctx->tile_off, s);
+  const int64_t tiles32 = (total + gcdf::kTileQ / 2 - 1) / (gcdf::kTileQ / 2) + N;  // (an upper bound)
+  const int tile_q = gcdf::narrow_tiles(tiles32, ctx->num_cu) ? gcdf::kTileQ / 2 : gcdf::kTileQ;
+  hipError_t e = gcdf::launch_csr_tile_offsets(offsets, N, tile_q, ctx->tile_off, s);
   gcdf::Job job{};
   job.knots = knots;
   job.points = points;
@@ -428,7 +430,8 @@ gcdf_status gcdf_eval_grad_csr(gcdf_ctx* ctx, const float* knots, int64_t N, con
   job.tile_off = ctx->tile_off;
   job.row_off = offsets;
   job.pgather = idx;
-  job.ntiles_bound = (total + gcdf::kTileQ - 1) / gcdf::kTileQ + N;
+  job.tile_q = tile_q;
+  job.ntiles_bound = (total + tile_q - 1) / tile_q + N;
   job.d = c;
   job.J = J;
   if (e == hipSuccess) e = gcdf::launch_fused(ctx->net, job, false, J != nullptr, ctx->num_cu, s);

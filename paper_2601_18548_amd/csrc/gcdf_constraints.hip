@@ -152,14 +152,14 @@ __global__ __launch_bounds__(kPartThreads) void partition_fill_kernel(const floa
   }
 }
 
-// One workgroup: tile_off[0] = 0, tile_off[i+1] = tile_off[i] + ceil(m_i / 64) with
+// One workgroup: tile_off[0] = 0, tile_off[i+1] = tile_off[i] + ceil(m_i / tile_q) with
 // m_i = offsets[i+1] - offsets[i] (the gathered tiles of the CSR query).  Thread t
 // takes the contiguous knots [t L, (t + 1) L), L = ceil(N / 1024): it sums their
 // tile counts, the workgroup scans the 1024 sums, and the thread writes its
 // knots' offsets from its base (two passes over the offsets, two barriers per
 // scan step, however large N is).
 constexpr int kScanThreads = 1024;
-__global__ __launch_bounds__(kScanThreads) void csr_tile_offsets_kernel(const int64_t* __restrict__ offsets, int64_t N,
+__global__ __launch_bounds__(kScanThreads) void csr_tile_offsets_kernel(const int64_t* __restrict__ offsets, int64_t N, int tile_q,
                                                                         int64_t* __restrict__ tile_off) {
   __shared__ int64_t buf[kScanThreads];
   const int t = threadIdx.x;
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(kScanThreads) void csr_tile_offsets_kernel(const in
   const int64_t i1 = i0 + L < N ? i0 + L : N;
   auto tiles = [&](int64_t i) {
     const int64_t m = offsets[i + 1] - offsets[i];
-    return m > 0 ? (m + kTileQ - 1) / kTileQ : (int64_t)0;
+    return m > 0 ? (m + tile_q - 1) / tile_q : (int64_t)0;
   };
   int64_t sum = 0;
 #pragma unroll 8
@@ -313,8 +313,8 @@ hipError_t launch_partition_fill(const float* ref, int64_t N, int64_t ref_stride
   return hipGetLastError();
 }
 
-hipError_t launch_csr_tile_offsets(const int64_t* offsets, int64_t N, int64_t* tile_off, hipStream_t s) {
-  hipLaunchKernelGGL(csr_tile_offsets_kernel, dim3(1), dim3(kScanThreads), 0, s, offsets, N, tile_off);
+hipError_t launch_csr_tile_offsets(const int64_t* offsets, int64_t N, int tile_q, int64_t* tile_off, hipStream_t s) {
+  hipLaunchKernelGGL(csr_tile_offsets_kernel, dim3(1), dim3(kScanThreads), 0, s, offsets, N, tile_q, tile_off);
   return hipGetLastError();
 }
 

@@ -92,7 +92,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
               v[4 * hh + u] = f(I, NT, j, a[I][NT][j], zz[u], dd[u], rr[u]);
             }
           }
-          act_store_pair<W, MODE, I, GP, NT>(ln, v);
+          act_store_pair<W, MODE, 2, I, GP, NT>(ln, v);
         });
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -165,7 +165,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
           const int idx = (I * 2 + NT) * 4 + 2 * GP;
           sput(sZ, idx, f32x4{zv[0], zv[1], zv[2], zv[3]});
           sput(sZ, idx + 1, f32x4{zv[4], zv[5], zv[6], zv[7]});
-          act_store_pair<W, MODE, I, GP, NT>(ln, hv);
+          act_store_pair<W, MODE, 2, I, GP, NT>(ln, hv);
         });
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -175,7 +175,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
 
     f32x16 a[MT][2];
     APre<W, MODE> ap;  // each product's first weight fragments, requested ahead of it
-    preload_a<W, MODE>(ap, net.fwd[0], b.voff);
+    preload_a<W, MODE, 2>(ap, net.fwd[0], b.voff);
     // ---- hidden layers forward: z to the scratch, h to LDS ----
     static_for<3>([&](auto L) {
 #pragma unroll
@@ -188,7 +188,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
 #pragma unroll
             for (int r = 0; r < 4; ++r) a[i][nt][4 * g + r] = b4[r];
         }
-      layer_gemm<W, MODE, MODE>(a, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], b.voff, ln.act_r, ap);
+      layer_gemm<W, MODE, 2, MODE>(a, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], b.voff, ln.act_r, ap);
       __syncthreads();
       put_all(sZ + (L + 1) * kArr, a);
       emit(a, kNone, kNone, kNone, [&](int, int, int, float acc, float, float, float) { return silu_only(acc); });
@@ -207,7 +207,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
     static_for<3>([&](auto LL) {
       constexpr int L = 2 - LL;  // W_{L+2}^T g_{L+2} = r_{L+1}
       zero(a);
-      layer_gemm<W, MODE, MODE>(a, net.bwd[L], L > 0 ? net.bwd[L - 1] : net.fwd[0], b.voff, ln.act_r, ap);
+      layer_gemm<W, MODE, 2, MODE>(a, net.bwd[L], L > 0 ? net.bwd[L - 1] : net.fwd[0], b.voff, ln.act_r, ap);
       __syncthreads();
       put_all(sR + L * kArr, a);
       emit(a, sZ + L * kArr, kNone, kNone, [&](int, int, int, float acc, float z, float, float) {
@@ -254,7 +254,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
           }
           sput(sZd, idx, f32x4{zd[0], zd[1], zd[2], zd[3]});
           sput(sZd, idx + 1, f32x4{zd[4], zd[5], zd[6], zd[7]});
-          act_store_pair<W, MODE, I, GP, NT>(ln, hd);
+          act_store_pair<W, MODE, 2, I, GP, NT>(ln, hd);
         });
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -264,7 +264,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
     static_for<3>([&](auto L) {
       // zdot_{L+2} = W_{L+2} hdot_{L+1}; hdot_{L+2} = s'(z_{L+2}) zdot_{L+2}
       zero(a);
-      layer_gemm<W, MODE, MODE>(a, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], b.voff, ln.act_r, ap);
+      layer_gemm<W, MODE, 2, MODE>(a, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], b.voff, ln.act_r, ap);
       __syncthreads();
       put_all(sZd + (L + 1) * kArr, a);
       emit(a, sZ + (L + 1) * kArr, kNone, kNone, [&](int, int, int, float acc, float z, float, float) {
@@ -289,7 +289,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
     static_for<3>([&](auto LL) {
       constexpr int L = 2 - LL;  // hbar_{L+1} = W_{L+2}^T zbar_{L+2}
       zero(a);
-      layer_gemm<W, MODE, MODE>(a, net.bwd[L], net.bwd[L > 0 ? L - 1 : 0], b.voff, ln.act_r, ap);
+      layer_gemm<W, MODE, 2, MODE>(a, net.bwd[L], net.bwd[L > 0 ? L - 1 : 0], b.voff, ln.act_r, ap);
       __syncthreads();
       emit(a, sZ + L * kArr, sZd + L * kArr, sR + L * kArr, [&](int, int, int, float hb, float z, float zd, float r) {
         float d1, d2;
@@ -716,8 +716,9 @@ hipError_t launch_minkey_decode(const unsigned long long* minkey, int64_t K, flo
 // ----------------------------------------------------------------------------
 hipError_t launch_fused(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s) {
   if (net.in_dim == kInDimSphere) return launch_fused_sphere(net, job, pairs, want_grad, num_cu, s);
-  if (net.width == 256) return launch_w<256, false>(net, job, pairs, want_grad, num_cu, s);
-  return launch_w<512, false>(net, job, pairs, want_grad, num_cu, s);
+  if (narrow_tiles(job, pairs, num_cu)) return launch_fused_narrow(net, job, pairs, want_grad, num_cu, s);
+  if (net.width == 256) return launch_w<256, 2, false>(net, job, pairs, want_grad, num_cu, s);
+  return launch_w<512, 2, false>(net, job, pairs, want_grad, num_cu, s);
 }
 
 // ----------------------------------------------------------------------------

@@ -53,12 +53,13 @@ struct Job {
   const int32_t* csr_idx;
   // Gathered knot tiles (dense mode, when tile_off is set): knot i owns rows
   // row_off[i] .. row_off[i+1]-1, row r pairing it with point pgather[r]; its rows
-  // form tile_off[i+1] - tile_off[i] tiles of up to 64 (tile_off[0] = 0), so no tile
+  // form tile_off[i+1] - tile_off[i] tiles of up to tile_q (tile_off[0] = 0), so no tile
   // mixes knots; d and J are indexed by row; ntiles_bound >= tile_off[K] sizes the grid.
   const int64_t* tile_off;
   const int64_t* row_off;
   const int32_t* pgather;
   int64_t ntiles_bound;
+  int tile_q;                // rows per gathered tile: kTileQ or kTileQ / 2
   float* d;                  // dense: [K][Np]; pairs: [npairs]      (nullable)
   float* J;                  // dense: [K][Np][9]; pairs: [npairs][9] (nullable)
   unsigned long long* minkey;// dense only: [K] ordered (distance, index) keys (nullable)
@@ -128,8 +129,8 @@ hipError_t launch_partition_count(const float* ref, int64_t N, int64_t ref_strid
 hipError_t launch_partition_fill(const float* ref, int64_t N, int64_t ref_stride, const float* points, int64_t M,
                                  bool spheres, float radius, const int64_t* offsets, int32_t* idx, int64_t capacity,
                                  hipStream_t s);
-// tile_off[0] = 0, tile_off[i+1] = tile_off[i] + ceil((offsets[i+1] - offsets[i]) / 64).
-hipError_t launch_csr_tile_offsets(const int64_t* offsets, int64_t N, int64_t* tile_off, hipStream_t s);
+// tile_off[0] = 0, tile_off[i+1] = tile_off[i] + ceil((offsets[i+1] - offsets[i]) / tile_q).
+hipError_t launch_csr_tile_offsets(const int64_t* offsets, int64_t N, int tile_q, int64_t* tile_off, hipStream_t s);
 // Sparsity pattern of the stacked constraint Jacobian: row_ptr[r] = n_conf * r (r <= total),
 // cols[n_conf * r + c] = col0 + state_dim * knot(r) + c.
 hipError_t launch_jacobian_pattern(const int64_t* offsets, int64_t N, int64_t total, int32_t state_dim, int64_t col0,
@@ -145,11 +146,35 @@ struct Minv9 {
 hipError_t launch_project(const float* knots, int64_t N, int64_t Np, const int64_t* offsets, int64_t rows,
                           const float* f, const float* J, const Minv9& minv, float* qz, float* eik, hipStream_t s);
 
+// Tiles of tq queries that a job runs (an upper bound for gathered tiles, whose
+// offsets are made for one tile size).
+inline int64_t query_tiles(const Job& job, bool pairs, int tq) {
+  if (pairs) return (job.npairs + tq - 1) / tq;
+  return job.tile_off ? job.ntiles_bound : job.K * ((job.Np + tq - 1) / tq);
+}
+// Whether a query job runs in 32-query tiles (gathered tiles: as its offsets were
+// made): when every such tile has a compute unit to itself.  A tile's time is then the
+// call's, and 32 queries take little more than half of what 64 take (us a call, 64 /
+// 32 queries: W=256 BF16X2_F16 16 x 64 26.3 / 14.8, 100 x 64 26.4 / 15.7; FP32 16 x 64
+// 104 / 58; W=512 128 x 64 57 / 46).  Past that, two of them follow each other on a
+// compute unit, and 64-query tiles are as fast or faster (200 x 64: W=256 27.5 / 28.6,
+// W=512 63 / 79), since each weight fragment then serves twice the queries.
+inline bool narrow_tiles(int64_t tiles32, int num_cu) { return tiles32 <= num_cu; }
+inline bool narrow_tiles(const Job& job, bool pairs, int num_cu) {
+  if (job.dumpH) return false;  // training dumps 64-sample tiles
+  if (!pairs && job.tile_off) return job.tile_q == kTileQ / 2;
+  return narrow_tiles(query_tiles(job, pairs, kTileQ / 2), num_cu);
+}
+
 // Launch the fused query kernel (dense all-pairs if !pairs, else the pair list).
 hipError_t launch_fused(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s);
 // The same for a sphere network (net.in_dim == 10; points hold (x, y, z, r)); no training.
 hipError_t launch_fused_sphere(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu,
                                hipStream_t s);
+// Their 32-query tiles (narrow_tiles).
+hipError_t launch_fused_narrow(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s);
+hipError_t launch_fused_sphere_narrow(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu,
+                                      hipStream_t s);
 
 // minkey[i] = all ones, for i < K (fill kernel; graph-capture safe).
 hipError_t launch_minkey_init(unsigned long long* minkey, int64_t K, hipStream_t s);

@@ -354,7 +354,7 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
         pj.npairs = pj.K;
         pj.J = uniform(fin.Jmin);
         for (int64_t q0 = 0; q0 < pj.K; q0 += kTileQ)
-          process_tile<W, MODE, true, true, false, false, SPH>(net, pj, 0, q0, tc);
+          process_tile<W, MODE, 2, true, true, false, false, SPH>(net, pj, 0, q0, tc);
       }
       __threadfence_system();
       __syncthreads();
@@ -374,12 +374,12 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
     job.minkey = uniform(cur.minkey);
     const int64_t kk = t / nblk;
     const int64_t q0 = (t - kk * nblk) * kTileQ;
-    if (cur.want_grad) process_tile<W, MODE, true, false, false, false, SPH>(net, job, kk, q0, tc);
-    else process_tile<W, MODE, false, false, false, false, SPH>(net, job, kk, q0, tc);
+    if (cur.want_grad) process_tile<W, MODE, 2, true, false, false, false, SPH>(net, job, kk, q0, tc);
+    else process_tile<W, MODE, 2, false, false, false, false, SPH>(net, job, kk, q0, tc);
     __syncthreads();  // every wave's stores are done before thread 0 may report the tile
     if (tid == 0) kept.idle_since = __builtin_amdgcn_s_memrealtime();
   }
-  report_overflow<W, MODE>(net, tc);
+  report_overflow<W, MODE, 2>(net, tc);
 }
 
 template <int W, int MODE, bool SPH>

@@ -157,9 +157,18 @@ constexpr bool lane_k_order() {
   return MODE == kBF16X2 || MODE == kBF16X2F16;
 }
 
-template <int W, int MODE>
+// CB: 32-wide column blocks of a tile.  Tiles of one block (32 queries) serve launches
+// too small to give every compute unit a 64-query tile (see narrow_tiles): half the
+// work per tile, and with it little more than half the time of a call.  Their waves
+// have room for longer rings of weight and activation fragments (AR, BR), which their
+// shorter K steps need against the same latencies.  A query's arithmetic and the order
+// of its sums do not depend on CB.
+template <int W, int MODE, int CB = 2>
 struct Geo {
-  static constexpr int NW = waves_for<W, MODE>();    // waves per workgroup
+  static constexpr int TQ = 32 * CB;                 // queries per tile
+  static constexpr int NW = CB == 1 && MODE != kFP32 ? 8 : waves_for<W, MODE>();  // waves per workgroup
+  static constexpr int AR = CB == 1 && MODE != kFP32 ? (W == 256 ? 8 : 4) : 2;    // K steps of A in flight
+  static constexpr int BR = CB == 1 && MODE != kFP32 && W == 256 ? 4 : 2;         // K steps of B, the current one included
   static constexpr int THREADS = 64 * NW;
   static constexpr int MT = W / (32 * NW);           // 32-row M tiles per wave
   // The packed matrices and row vectors are laid out for 4 row groups of PMT M
@@ -178,25 +187,27 @@ struct Geo {
   static constexpr int NKB = W / 16;                 // 16-deep K blocks (bf16)
   // bytes of the activation tile per K step (16 rows in the BF16 modes, 8 in FP32);
   // BF16X2 keeps a step's hi and lo halves next to each other, lo at LO_OFF
-  static constexpr int STEP_BYTES = fwd_arith<MODE>() == kBF16X2 ? 4096 : 2048;
-  static constexpr int LO_OFF = 2048;
+  static constexpr int STEP_BYTES = (fwd_arith<MODE>() == kBF16X2 ? 64 : 32) * TQ;
+  static constexpr int LO_OFF = 32 * TQ;
   static constexpr int NK8 = W / 8;                  // 8-deep K groups (fp32: 4 MFMAs of K=2)
-  static constexpr int ACT_BYTES = W * kTileQ * 4;   // fp32, or bf16 hi + bf16 lo
+  static constexpr int ACT_BYTES = W * TQ * 4;   // fp32, or bf16 hi + bf16 lo
   static constexpr int XIN_FLOATS = 17;              // per query: p'(3), cos, sin, arm(6), seed, radius, target, pad; odd stride: lanes reading one field of 32 queries hit 32 different banks
   static constexpr int RED_VALS = 9;                 // d, dd/dp'x, dd/dp'y, dd/da1..dd/da6
-  static constexpr int RED_BYTES = RG * RED_VALS * kTileQ * 4;
-  static constexpr int LDS_BYTES = ACT_BYTES + kTileQ * XIN_FLOATS * 4 + W * 4 + (RED_IN_ACT ? 0 : RED_BYTES) + 4 * W * 4;
+  static constexpr int RED_BYTES = RG * RED_VALS * TQ * 4;
+  static constexpr int LDS_BYTES = ACT_BYTES + TQ * XIN_FLOATS * 4 + W * 4 + (RED_IN_ACT ? 0 : RED_BYTES) + 4 * W * 4;
   // Workgroups per compute unit.  One 4-wave workgroup alone leaves the matrix cores
   // idle in its epilogues and the vector ALU in its K loops; where two fit in LDS and
   // registers they run their layers independently.
-  static constexpr int WGS = NW == kWaves && 2 * (LDS_BYTES + 2048) <= 160 * 1024 ? 2 : 1;
+  static constexpr int WGS = NW == kWaves && W == 256 ? 2 : 1;
+  static constexpr int WPE = WGS * NW / 4;  // waves per SIMD that the registers have to leave room for
+  static_assert(WGS * (LDS_BYTES + 2304 + 16) <= 160 * 1024, "the workgroups exceed the compute unit's LDS");
   static_assert(!RED_IN_ACT || RED_BYTES <= ACT_BYTES, "reduction buffer must fit the activation tile");
   static_assert(GPW == 1 || GPW == MT, "a wave's row groups are its M tiles");
   static_assert(MT >= 1 && PMT == SUB * MT, "row groups must split evenly");
 };
 
 // ----------------------------------------------------------------------------
-// Activation tile in LDS (64 query columns).
+// Activation tile in LDS (64 query columns; byte counts for 32 are half).
 //  bf16 modes: K step s (rows 16s .. 16s+15) occupies STEP_BYTES at s*STEP_BYTES:
 //    its hi half, then (BF16X2) its lo half at +LO_OFF, so one base register with
 //    small immediate offsets reaches both.  A half holds 16-byte groups (kh, n) at
@@ -216,9 +227,9 @@ struct Geo {
 // constant, so the constants fold into the instructions' offset fields instead
 // of occupying registers.
 // ----------------------------------------------------------------------------
-template <int W, int MODE>
+template <int W, int MODE, int CB = 2>
 struct Lane {
-  static constexpr int MT = Geo<W, MODE>::MT;
+  static constexpr int MT = Geo<W, MODE, CB>::MT;
   int lane, wave, h, n0, kh, rbase;
   char* act_w;        // write base, hi plane (or the fp32 tile)
   char* act_w_lo;     // write base, lo plane
@@ -232,20 +243,20 @@ struct Lane {
     n0 = lane & 31;
     rbase = 32 * MT * wave;
     if constexpr (MODE == kFP32) {
-      act_w = act + 4 * (((rbase >> 3) * kTileQ + n0) * 8 + 2 * h);
+      act_w = act + 4 * (((rbase >> 3) * Geo<W, MODE, CB>::TQ + n0) * 8 + 2 * h);
       act_r = act + n0 * 32 + kh * 16;
     } else {
-      act_w = act + (rbase >> 4) * Geo<W, MODE>::STEP_BYTES + h * 1024 + n0 * 16;
-      act_r = act + kh * 1024 + n0 * 16;
+      act_w = act + (rbase >> 4) * Geo<W, MODE, CB>::STEP_BYTES + h * 16 * Geo<W, MODE, CB>::TQ + n0 * 16;
+      act_r = act + kh * 16 * Geo<W, MODE, CB>::TQ + n0 * 16;
     }
-    act_w_lo = act_w + Geo<W, MODE>::LO_OFF;
+    act_w_lo = act_w + Geo<W, MODE, CB>::LO_OFF;
   }
 };
 
 // Write rows R0..R0+3 (R0 = rbase + 32 i + 8 g + 4 h) of column n = 32 nt + n0 (fp32).
-template <int W, int MODE, int I, int G, int NT>
-__device__ __forceinline__ void act_store4_fp32(const Lane<W, MODE>& L, const float v[4]) {
-  constexpr int off = (4 * I + G) * 2048 + NT * 1024;
+template <int W, int MODE, int CB, int I, int G, int NT>
+__device__ __forceinline__ void act_store4_fp32(const Lane<W, MODE, CB>& L, const float v[4]) {
+  constexpr int off = (4 * I + G) * Geo<W, MODE, CB>::STEP_BYTES + NT * 1024;
   *reinterpret_cast<f32x2*>(L.act_w + off) = f32x2{v[0], v[2]};       // rows R0, R0+2 (k%2 = 0)
   *reinterpret_cast<f32x2*>(L.act_w + off + 16) = f32x2{v[1], v[3]};  // rows R0+1, R0+3 (k%2 = 1)
 }
@@ -321,41 +332,41 @@ __device__ __forceinline__ void act_pack8(const float x[8], const float y[8], ui
   put(d[0], d[1], d[2], d[3], w);
 }
 
-template <int W, int MODE, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
-__device__ __forceinline__ void act_write8(const Lane<W, MODE>& L, const uint32_t (&w)[8]) {
-  constexpr int off = (2 * I + GP) * Geo<W, MODE>::STEP_BYTES + NT * 512;
+template <int W, int MODE, int CB, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
+__device__ __forceinline__ void act_write8(const Lane<W, MODE, CB>& L, const uint32_t (&w)[8]) {
+  constexpr int off = (2 * I + GP) * Geo<W, MODE, CB>::STEP_BYTES + NT * 512;
   typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
   *reinterpret_cast<u32x4*>(L.act_w + off) = u32x4{w[0], w[1], w[2], w[3]};
   if constexpr (AM == kBF16X2) *reinterpret_cast<u32x4*>(L.act_w_lo + off) = u32x4{w[4], w[5], w[6], w[7]};
 }
 
-template <int W, int MODE, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
-__device__ __forceinline__ void act_store8(const Lane<W, MODE>& L, const float x[8], const float y[8]) {
+template <int W, int MODE, int CB, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
+__device__ __forceinline__ void act_store8(const Lane<W, MODE, CB>& L, const float x[8], const float y[8]) {
   uint32_t w[8];
   act_pack8<AM, !lane_k_order<MODE>()>(x, y, w);
-  act_write8<W, MODE, I, GP, NT, AM>(L, w);
+  act_write8<W, MODE, CB, I, GP, NT, AM>(L, w);
 }
 
 // Either layout: rows of groups g = 2 GP, 2 GP + 1 (see act_store8), the products
 // x[k] y[k].
-template <int W, int MODE, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
-__device__ __forceinline__ void act_store_pair(const Lane<W, MODE>& L, const float x[8], const float y[8]) {
+template <int W, int MODE, int CB, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
+__device__ __forceinline__ void act_store_pair(const Lane<W, MODE, CB>& L, const float x[8], const float y[8]) {
   if constexpr (MODE == kFP32) {
     float v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = x[k] * y[k];
-    act_store4_fp32<W, MODE, I, 2 * GP, NT>(L, v);
-    act_store4_fp32<W, MODE, I, 2 * GP + 1, NT>(L, v + 4);
+    act_store4_fp32<W, MODE, CB, I, 2 * GP, NT>(L, v);
+    act_store4_fp32<W, MODE, CB, I, 2 * GP + 1, NT>(L, v + 4);
   } else {
-    act_store8<W, MODE, I, GP, NT, AM>(L, x, y);
+    act_store8<W, MODE, CB, I, GP, NT, AM>(L, x, y);
   }
 }
 // The same for plain values (FP32 and pure BF16: no lo part).
-template <int W, int MODE, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
-__device__ __forceinline__ void act_store_pair(const Lane<W, MODE>& L, const float v[8]) {
+template <int W, int MODE, int CB, int I, int GP, int NT, int AM = fwd_arith<MODE>()>
+__device__ __forceinline__ void act_store_pair(const Lane<W, MODE, CB>& L, const float v[8]) {
   static_assert(AM != kBF16X2, "the split forms take the values as products");
   const float one[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
-  act_store_pair<W, MODE, I, GP, NT, AM>(L, v, one);
+  act_store_pair<W, MODE, CB, I, GP, NT, AM>(L, v, one);
 }
 
 // Compile-time loop helper: f(integral_constant<0>), ..., f(integral_constant<N-1>).
@@ -378,31 +389,31 @@ __device__ __forceinline__ void static_for(F&& f) {
 // Software pipeline: A is loaded two K steps ahead, B (LDS) one step ahead.
 // AM is the K loop's arithmetic (fwd_arith / rev_arith of the tile's mode).
 // ----------------------------------------------------------------------------
-template <int AM>
+template <int AM, int CB>
 struct BFrag {
-  bf16x8 h[2], l[2];
-  f32x4 f[2];
+  bf16x8 h[CB], l[CB];
+  f32x4 f[CB];
 };
 
-template <int W, int MODE, int AM>
-__device__ __forceinline__ void load_b(BFrag<AM>& b, const char* br) {
+template <int W, int MODE, int CB, int AM>
+__device__ __forceinline__ void load_b(BFrag<AM, CB>& b, const char* br) {
   if constexpr (AM == kFP32) {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) b.f[nt] = *reinterpret_cast<const f32x4*>(br + nt * 1024);
+    for (int nt = 0; nt < CB; ++nt) b.f[nt] = *reinterpret_cast<const f32x4*>(br + nt * 1024);
   } else {
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
+    for (int nt = 0; nt < CB; ++nt) {
       b.h[nt] = *reinterpret_cast<const bf16x8*>(br + nt * 512);
-      if constexpr (AM == kBF16X2) b.l[nt] = *reinterpret_cast<const bf16x8*>(br + Geo<W, MODE>::LO_OFF + nt * 512);
+      if constexpr (AM == kBF16X2) b.l[nt] = *reinterpret_cast<const bf16x8*>(br + Geo<W, MODE, CB>::LO_OFF + nt * 512);
     }
   }
 }
 
-template <int W, int MODE>
-__device__ __forceinline__ void load_a(f32x4 (&af)[(Geo<W, MODE>::MT)], __amdgpu_buffer_rsrc_t rs, int voff, int step) {
-  const int soff = step * Geo<W, MODE>::PMT * 1024;
+template <int W, int MODE, int CB>
+__device__ __forceinline__ void load_a(f32x4 (&af)[(Geo<W, MODE, CB>::MT)], __amdgpu_buffer_rsrc_t rs, int voff, int step) {
+  const int soff = step * Geo<W, MODE, CB>::PMT * 1024;
 #pragma unroll
-  for (int i = 0; i < Geo<W, MODE>::MT; ++i)
+  for (int i = 0; i < Geo<W, MODE, CB>::MT; ++i)
     af[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff + i * 1024, soff, 0));
 }
 
@@ -413,12 +424,12 @@ __device__ __forceinline__ void load_a(f32x4 (&af)[(Geo<W, MODE>::MT)], __amdgpu
 // the compiler from sinking the loads to the end of the loop body.  ZC: the
 // accumulators start at zero, so the first product of each tile reads a zero C
 // operand instead of registers cleared beforehand.
-template <int W, int MODE, int AM, bool ZC = false>
-__device__ __forceinline__ void mma_step_reload(f32x16 (&acc)[(Geo<W, MODE>::MT)][2], f32x4 (&af)[(Geo<W, MODE>::MT)],
-                                                const BFrag<AM>& b, __amdgpu_buffer_rsrc_t rs, int voff,
+template <int W, int MODE, int CB, int AM, bool ZC = false>
+__device__ __forceinline__ void mma_step_reload(f32x16 (&acc)[(Geo<W, MODE, CB>::MT)][CB], f32x4 (&af)[(Geo<W, MODE, CB>::MT)],
+                                                const BFrag<AM, CB>& b, __amdgpu_buffer_rsrc_t rs, int voff,
                                                 int next) {
-  constexpr int MT = Geo<W, MODE>::MT;
-  const int soff = next * Geo<W, MODE>::PMT * 1024;
+  constexpr int MT = Geo<W, MODE, CB>::MT;
+  const int soff = next * Geo<W, MODE, CB>::PMT * 1024;
   const f32x16 zero = {};
 #pragma unroll
   for (int i = 0; i < MT; ++i) {
@@ -426,23 +437,23 @@ __device__ __forceinline__ void mma_step_reload(f32x16 (&acc)[(Geo<W, MODE>::MT)
 #pragma unroll
       for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < CB; ++nt)
           acc[i][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][q], b.f[nt][q], (ZC && q == 0) ? zero : acc[i][nt],
                                                             0, 0, 0);
     } else if constexpr (AM == kF16) {
       const f16x8 a8 = __builtin_bit_cast(f16x8, af[i]);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < CB; ++nt)
         acc[i][nt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a8, __builtin_bit_cast(f16x8, b.h[nt]),
                                                             ZC ? zero : acc[i][nt], 0, 0, 0);
     } else {
       const bf16x8 a8 = __builtin_bit_cast(bf16x8, af[i]);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < CB; ++nt)
         acc[i][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8, b.h[nt], ZC ? zero : acc[i][nt], 0, 0, 0);
       if constexpr (AM == kBF16X2) {
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < CB; ++nt)
           acc[i][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a8, b.l[nt], acc[i][nt], 0, 0, 0);
       }
     }
@@ -451,25 +462,25 @@ __device__ __forceinline__ void mma_step_reload(f32x16 (&acc)[(Geo<W, MODE>::MT)
   }
 }
 
-template <int W, int MODE>
+template <int W, int MODE, int CB>
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t stream_rsrc(const void* base) {
   constexpr int bytes = W * W * (MODE == kFP32 ? 4 : 2);
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, bytes, 0x00020000);
 }
 
-// The A fragments of a layer's first two K steps, loaded ahead of the layer.  (In
+// The A fragments of a layer's first AR K steps, loaded ahead of the layer.  (In
 // training that is before the previous layer's dump too: the vector-memory counter
 // completes in order, so a wait for fragments issued after the dump's stores would
 // also wait for those stores.)
-template <int W, int MODE>
+template <int W, int MODE, int CB = 2>
 struct APre {
-  f32x4 a0[Geo<W, MODE>::MT], a1[Geo<W, MODE>::MT];
+  f32x4 a[Geo<W, MODE, CB>::AR][Geo<W, MODE, CB>::MT];
 };
-template <int W, int MODE>
-__device__ __forceinline__ void preload_a(APre<W, MODE>& p, const void* mat, int voff) {
-  const __amdgpu_buffer_rsrc_t rs = stream_rsrc<W, MODE>(mat);
-  load_a<W, MODE>(p.a0, rs, voff, 0);
-  load_a<W, MODE>(p.a1, rs, voff, 1);
+template <int W, int MODE, int CB>
+__device__ __forceinline__ void preload_a(APre<W, MODE, CB>& p, const void* mat, int voff) {
+  const __amdgpu_buffer_rsrc_t rs = stream_rsrc<W, MODE, CB>(mat);
+#pragma unroll
+  for (int u = 0; u < Geo<W, MODE, CB>::AR; ++u) load_a<W, MODE, CB>(p.a[u], rs, voff, u);
 }
 
 // With two workgroups per compute unit, a wave in an epilogue goes before the other
@@ -477,54 +488,52 @@ __device__ __forceinline__ void preload_a(APre<W, MODE>& p, const void* mat, int
 // matrix instruction leaves (32 cycles for 4 of issue), so both advance.  FP32
 // 64 x 4,096 pairs 1.548 -> 1.520 ms, BF16X2_F16 128 x 8,192 (W=256) 1.318 -> 1.304 ms;
 // a fixed order of the two workgroups, or the K loop first, measured as no priority.
-template <int W, int MODE>
+template <int W, int MODE, int CB>
 __device__ __forceinline__ void epilogue_priority(bool epilogue) {
-  if constexpr (Geo<W, MODE>::WGS > 1) {
+  if constexpr (Geo<W, MODE, CB>::WGS > 1) {
     if (epilogue) __builtin_amdgcn_s_setprio(1);
     else __builtin_amdgcn_s_setprio(0);
   }
 }
 
 // ZERO: acc starts at zero (its contents on entry are not read).  p: the A
-// fragments of steps 0 and 1, already requested; on return those of the layer
-// streamed from `next` (its loads take the place of the last two steps' reloads, so
-// they are in flight during the epilogue, and the next K loop does not start with
-// the weight stream's L2 latency).
-template <int W, int MODE, int AM, bool ZERO = false>
-__device__ __forceinline__ void layer_gemm(f32x16 (&acc)[(Geo<W, MODE>::MT)][2], const void* mat, const void* next,
-                                           int voff, const char* br, APre<W, MODE>& p) {
-  epilogue_priority<W, MODE>(false);
-  const __amdgpu_buffer_rsrc_t rs = stream_rsrc<W, MODE>(mat);
-  f32x4 (&a0)[(Geo<W, MODE>::MT)] = p.a0;
-  f32x4 (&a1)[(Geo<W, MODE>::MT)] = p.a1;
-  constexpr int NS = (MODE == kFP32) ? Geo<W, MODE>::NK8 : Geo<W, MODE>::NKB;  // even, >= 16
-  constexpr int SB = Geo<W, MODE>::STEP_BYTES;
-  BFrag<AM> b0, b1;
-  load_b<W, MODE, AM>(b0, br);
+// fragments of the first AR steps, already requested; on return those of the layer
+// streamed from `next` (its loads take the place of the last steps' reloads, so they
+// are in flight during the epilogue, and the next K loop does not start with the
+// weight stream's L2 latency).
+template <int W, int MODE, int CB, int AM, bool ZERO = false>
+__device__ __forceinline__ void layer_gemm(f32x16 (&acc)[(Geo<W, MODE, CB>::MT)][CB], const void* mat, const void* next,
+                                           int voff, const char* br, APre<W, MODE, CB>& p) {
+  using G = Geo<W, MODE, CB>;
+  constexpr int NS = (MODE == kFP32) ? G::NK8 : G::NKB;
+  constexpr int SB = G::STEP_BYTES, U = G::AR, R = G::BR;  // U steps per round of the loop
+  static_assert(NS % U == 0 && NS > U && U % R == 0, "whole rounds, and whole turns of both rings");
+  epilogue_priority<W, MODE, CB>(false);
+  BFrag<AM, CB> b[R];
+#pragma unroll
+  for (int u = 0; u < R - 1; ++u) load_b<W, MODE, CB, AM>(b[u], br + u * SB);
+  // one round: steps s .. s + U - 1; the B fragments of R - 1 steps further, and the A
+  // fragments of U steps further, which in the last round are the next layer's first
+  auto round = [&](int s, auto zc) {
+    const bool more = s + U < NS;
+    const __amdgpu_buffer_rsrc_t rn = stream_rsrc<W, MODE, CB>(more ? mat : next);
+    const int sn = more ? s + U : 0;
+    const char* bw = more ? br : br - U * SB;  // (nothing reads past the tile's last step)
+    static_for<U>([&](auto u) {
+      load_b<W, MODE, CB, AM>(b[(u + R - 1) % R], (u + R - 1 < U ? br : bw) + (u + R - 1) * SB);
+      __builtin_amdgcn_sched_barrier(0);
+      mma_step_reload<W, MODE, CB, AM, (decltype(zc)::value && u == 0)>(acc, p.a[u], b[u % R], rn, voff, sn + u);
+    });
+    br += U * SB;
+  };
   int s = 0;
-  if constexpr (ZERO) {  // steps 0 and 1, the first writing acc from a zero C operand
-    load_b<W, MODE, AM>(b1, br + SB);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_step_reload<W, MODE, AM, true>(acc, a0, b0, rs, voff, 2);
-    load_b<W, MODE, AM>(b0, br + 2 * SB);
-    __builtin_amdgcn_sched_barrier(0);
-    mma_step_reload<W, MODE, AM>(acc, a1, b1, rs, voff, 3);
-    br += 2 * SB;
-    s = 2;
+  if constexpr (ZERO) {  // the first round, its first step writing acc from a zero C operand
+    round(0, std::true_type{});
+    s = U;
   }
 #pragma unroll 1
-  for (; s < NS; s += 2) {
-    load_b<W, MODE, AM>(b1, br + SB);  // B of step s+1, one step ahead
-    __builtin_amdgcn_sched_barrier(0);
-    const bool more = s + 2 < NS;
-    const __amdgpu_buffer_rsrc_t rn = stream_rsrc<W, MODE>(more ? mat : next);
-    mma_step_reload<W, MODE, AM>(acc, a0, b0, rn, voff, more ? s + 2 : 0);
-    load_b<W, MODE, AM>(b0, more ? br + 2 * SB : br);  // B of step s+2
-    __builtin_amdgcn_sched_barrier(0);
-    mma_step_reload<W, MODE, AM>(acc, a1, b1, rn, voff, more ? s + 3 : 1);
-    br += 2 * SB;
-  }
-  epilogue_priority<W, MODE>(true);
+  for (; s < NS; s += U) round(s, std::false_type{});
+  epilogue_priority<W, MODE, CB>(true);
 }
 
 // The reverse layers' accumulators start at zero: in single FP16 the first
@@ -534,12 +543,12 @@ template <int MODE>
 constexpr bool rev_zero_c() {
   return rev_arith<MODE>() == kF16;
 }
-template <int W, int MODE>
-__device__ __forceinline__ void zero_acc(f32x16 (&acc)[(Geo<W, MODE>::MT)][2]) {
+template <int W, int MODE, int CB>
+__device__ __forceinline__ void zero_acc(f32x16 (&acc)[(Geo<W, MODE, CB>::MT)][CB]) {
 #pragma unroll
-  for (int i = 0; i < Geo<W, MODE>::MT; ++i)
+  for (int i = 0; i < Geo<W, MODE, CB>::MT; ++i)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < CB; ++nt)
 #pragma unroll
       for (int j = 0; j < 16; ++j) acc[i][nt][j] = 0.f;
 }
@@ -702,7 +711,7 @@ __device__ __forceinline__ void dump_tile(const char* act, char* stage, void* ds
 // ((p*2 + h)*PMT + s*MT + i)*16 + 4 g + r for a wave that is share s of row
 // group p (with 4 waves, p = wave, s = 0, PMT = MT), so each lane addresses them
 // from one base with small constant offsets.
-template <int W, int MODE>
+template <int W, int MODE, int CB = 2>
 struct Bases {
   const float* bh;    // LDS copy of b2, b3, b4 (lane-major), at this lane's block
   const float* w5;    // LDS copy of w_out (lane-major), at this lane's block
@@ -716,7 +725,7 @@ struct Bases {
 // ----------------------------------------------------------------------------
 // Per-workgroup state.
 // ----------------------------------------------------------------------------
-template <int W, int MODE>
+template <int W, int MODE, int CB = 2>
 struct TileCtx {
   char* act;
   float* xin;   // [64][16]
@@ -734,9 +743,9 @@ struct TileCtx {
   __device__ __forceinline__ TileCtx(char* lds, uint32_t* ovf_word, const DevNet& net, int tid)
       : act(lds), ovf(ovf_word), b5(*net.b5p), nx_ok(false), w1p(net.w1p), wave(__builtin_amdgcn_readfirstlane(tid >> 6)) {
     if (tid == 0) *ovf = 0u;  // ordered before any tile's use by the tile's first barrier
-    using G = Geo<W, MODE>;
+    using G = Geo<W, MODE, CB>;
     xin = reinterpret_cast<float*>(lds + G::ACT_BYTES);
-    crow = xin + kTileQ * G::XIN_FLOATS;
+    crow = xin + G::TQ * G::XIN_FLOATS;
     float* after = crow + W;
     if constexpr (G::RED_IN_ACT) {
       red = reinterpret_cast<float*>(lds);
@@ -761,12 +770,12 @@ struct TileCtx {
 // from the thread index by each phase of the tile (a few instructions): kept through
 // the tile they took a dozen registers per lane of the 128 that a width-512 wave has
 // beside its parked SiLU' values, and pushed some of those into scratch memory.
-template <int W, int MODE>
+template <int W, int MODE, int CB = 2>
 struct View {
-  Lane<W, MODE> ln;
-  Bases<W, MODE> b;
-  __device__ __forceinline__ explicit View(const TileCtx<W, MODE>& tc) : ln(tc.act, fresh_tid(), tc.wave) {
-    using G = Geo<W, MODE>;
+  Lane<W, MODE, CB> ln;
+  Bases<W, MODE, CB> b;
+  __device__ __forceinline__ explicit View(const TileCtx<W, MODE, CB>& tc) : ln(tc.act, fresh_tid(), tc.wave) {
+    using G = Geo<W, MODE, CB>;
     constexpr int MT = G::MT;
     // bytes of one row group's fragment stream (1 KiB per fragment, PMT per K step)
     constexpr int stream_bytes = (MODE == kFP32 ? G::NK8 : G::NKB) * G::PMT * 1024;
@@ -828,9 +837,9 @@ struct TileDump {
 // Whether a hidden-layer epilogue keeps its packed results in registers across
 // the barrier (two waves of one workgroup per SIMD), except training's last forward
 // layer, which stores h4 first.
-template <int W, int MODE, bool TRAIN>
+template <int W, int MODE, int CB, bool TRAIN>
 constexpr bool defer_stores(bool last_forward) {
-  return Geo<W, MODE>::SUB > 1 && (!last_forward || !TRAIN);
+  return Geo<W, MODE, CB>::SUB > 1 && (!last_forward || !TRAIN);
 }
 
 // The packed words of elements 8 GP .. 8 GP + 7 of an accumulator go back into
@@ -845,48 +854,48 @@ __device__ __forceinline__ void park_packed(const float x[8], const float y[8], 
   for (int k = 0; k < NWORDS; ++k) a[8 * GP + k] = __uint_as_float(w[k]);
 }
 
-template <int W, int MODE, int AM>
-__device__ __forceinline__ void write_packed(const Lane<W, MODE>& ln, const f32x16 (&acc)[(Geo<W, MODE>::MT)][2]) {
-  static_for<Geo<W, MODE>::MT>([&](auto I) {
+template <int W, int MODE, int CB, int AM>
+__device__ __forceinline__ void write_packed(const Lane<W, MODE, CB>& ln, const f32x16 (&acc)[(Geo<W, MODE, CB>::MT)][CB]) {
+  static_for<Geo<W, MODE, CB>::MT>([&](auto I) {
     static_for<2>([&](auto GP) {
-      static_for<2>([&](auto NT) {
+      static_for<CB>([&](auto NT) {
         uint32_t w[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) w[k] = __float_as_uint(acc[I][NT][8 * GP + k]);
-        act_write8<W, MODE, I, GP, NT, AM>(ln, w);
+        act_write8<W, MODE, CB, I, GP, NT, AM>(ln, w);
       });
     });
   });
 }
 
-template <int W, int MODE, int L, bool TRAIN, bool GRAD>
-__device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, MODE>& tc,
-                                           float (&sp)[2][(Geo<W, MODE>::MT)][2][16], float (&dpart)[Geo<W, MODE>::GPW][2],
-                                           const TileDump& td, APre<W, MODE>& ap) {
-  constexpr int MT = Geo<W, MODE>::MT;
-  const View<W, MODE> v0(tc);
-  f32x16 acc[MT][2];
+template <int W, int MODE, int CB, int L, bool TRAIN, bool GRAD>
+__device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, MODE, CB>& tc,
+                                           float (&sp)[2][(Geo<W, MODE, CB>::MT)][CB][16], float (&dpart)[Geo<W, MODE, CB>::GPW][CB],
+                                           const TileDump& td, APre<W, MODE, CB>& ap) {
+  constexpr int MT = Geo<W, MODE, CB>::MT;
+  const View<W, MODE, CB> v0(tc);
+  f32x16 acc[MT][CB];
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const f32x4 b4 = *reinterpret_cast<const f32x4*>(v0.b.bh + L * W + 16 * i + 4 * g);
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < CB; ++nt)
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][nt][4 * g + r] = b4[r];
     }
-  layer_gemm<W, MODE, fwd_arith<MODE>()>(acc, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], v0.b.voff, v0.ln.act_r, ap);
-  const View<W, MODE> vw(tc);
-  const Lane<W, MODE>& ln = vw.ln;
-  const Bases<W, MODE>& b = vw.b;
+  layer_gemm<W, MODE, CB, fwd_arith<MODE>()>(acc, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], v0.b.voff, v0.ln.act_r, ap);
+  const View<W, MODE, CB> vw(tc);
+  const Lane<W, MODE, CB>& ln = vw.ln;
+  const Bases<W, MODE, CB>& b = vw.b;
   // arithmetic of what this layer stores: the next layer's activations, or g4
   // for the reverse sweep
   constexpr int SA = L == 2 ? rev_arith<MODE>() : fwd_arith<MODE>();
   // With two waves per SIMD the epilogue arithmetic runs before the barrier (the
   // results wait in registers), overlapping the K loops of waves still running;
   // only the stores into the tile they read wait for it.
-  constexpr bool DEFER = defer_stores<W, MODE, TRAIN>(L == 2);
+  constexpr bool DEFER = defer_stores<W, MODE, CB, TRAIN>(L == 2);
   if constexpr (!DEFER) __syncthreads();
   if constexpr (TRAIN && L == 2) {
     // training: the layer-4 activations h4 go through LDS first (for dL/dw_out),
@@ -896,7 +905,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
       static_for<2>([&](auto GP) {
         const f32x4 w5r[2] = {*reinterpret_cast<const f32x4*>(b.w5 + 16 * I + 8 * GP),
                               *reinterpret_cast<const f32x4*>(b.w5 + 16 * I + 8 * GP + 4)};
-        static_for<2>([&](auto NT) {
+        static_for<CB>([&](auto NT) {
           float v[8];
 #pragma unroll
           for (int q = 0; q < 8; ++q) {
@@ -906,14 +915,14 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
             acc[I][NT][8 * GP + q] = dv;
             dpart[0][NT] += w5r[q >> 2][q & 3] * v[q];
           }
-          act_store_pair<W, MODE, I, GP, NT>(ln, v);
+          act_store_pair<W, MODE, CB, I, GP, NT>(ln, v);
         });
       });
     });
     if (td.target) {
       // d over the rows: lane halves, then waves in order, as at the end of the tile
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < CB; ++nt) {
         const float dp = dpart[0][nt] + __shfl_xor(dpart[0][nt], 32);
         if (ln.h == 0) td.dred[ln.wave * kTileQ + 32 * nt + ln.n0] = dp;
       }
@@ -921,16 +930,16 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
     __syncthreads();
     if (threadIdx.x < kTileQ && (td.target || td.bsum)) {  // wave 0, one lane per query
       const int n = threadIdx.x;
-      float* seedp = td.xin + n * Geo<W, MODE>::XIN_FLOATS + 11;
+      float* seedp = td.xin + n * Geo<W, MODE, CB>::XIN_FLOATS + 11;
       float sq = 0.f;
       if (td.target) {
         float sum = td.dred[n];
 #pragma unroll
-        for (int w = 1; w < Geo<W, MODE>::NW; ++w) sum += td.dred[w * kTileQ + n];
+        for (int w = 1; w < Geo<W, MODE, CB>::NW; ++w) sum += td.dred[w * kTileQ + n];
         const float dv = sum + td.b5;
         const bool valid = n < td.nvalid;
         const int64_t q = td.q0 + n;
-        const float r = valid ? dv - td.xin[n * Geo<W, MODE>::XIN_FLOATS + kXinTarget] : 0.f;
+        const float r = valid ? dv - td.xin[n * Geo<W, MODE, CB>::XIN_FLOATS + kXinTarget] : 0.f;
         const float seed = td.mse_scale * r;  // dL/dd for L = mean (d - target)^2
         sq = td.inv_b * (r * r);
         *seedp = seed;
@@ -970,8 +979,8 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
         w5r[0] = *reinterpret_cast<const f32x4*>(b.w5 + 16 * I + 8 * GP);
         w5r[1] = *reinterpret_cast<const f32x4*>(b.w5 + 16 * I + 8 * GP + 4);
       }
-      static_for<2>([&](auto NT) {
-        const float seed = TRAIN ? b.xin[NT * 32 * Geo<W, MODE>::XIN_FLOATS + 11] : 1.f;
+      static_for<CB>([&](auto NT) {
+        const float seed = TRAIN ? b.xin[NT * 32 * Geo<W, MODE, CB>::XIN_FLOATS + 11] : 1.f;
         float x[8], y[8];  // what is stored, as products
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -990,7 +999,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
             x[q] = z;
             y[q] = sg;
           } else {
-            if constexpr (!TRAIN) dpart[Geo<W, MODE>::GPW > 1 ? (int)I : 0][NT] += w5r[q >> 2][q & 3] * hv;  // (training: above)
+            if constexpr (!TRAIN) dpart[Geo<W, MODE, CB>::GPW > 1 ? (int)I : 0][NT] += w5r[q >> 2][q & 3] * hv;  // (training: above)
             // g4 = seed * w5 * SiLU'(z4); the query's seed 1 (times rev_scale) is in w5
             x[q] = w5r[q >> 2][q & 3] * dv;
             asm("" : "+v"(x[q]));  // rounded before the seed (1 in the query) multiplies it
@@ -999,7 +1008,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
         }
         if constexpr (L < 2 || GRAD) {
           if constexpr (DEFER) park_packed<MODE, SA, GP>(x, y, acc[I][NT]);
-          else act_store_pair<W, MODE, I, GP, NT, SA>(ln, x, y);
+          else act_store_pair<W, MODE, CB, I, GP, NT, SA>(ln, x, y);
         }
       });
       __builtin_amdgcn_sched_barrier(0);
@@ -1010,11 +1019,13 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
     // sinks them to their use after the reverse sweep and keeps every h4 and
     // w_out value live through it.
 #pragma unroll
-    for (int k = 0; k < Geo<W, MODE>::GPW; ++k) asm volatile("" : "+v"(dpart[k][0]), "+v"(dpart[k][1]));
+    for (int k = 0; k < Geo<W, MODE, CB>::GPW; ++k)
+#pragma unroll
+      for (int nt = 0; nt < CB; ++nt) asm volatile("" : "+v"(dpart[k][nt]));
   }
   if constexpr (DEFER) {
     __syncthreads();  // every wave has finished reading the tile
-    if constexpr (L < 2 || GRAD) write_packed<W, MODE, SA>(ln, acc);
+    if constexpr (L < 2 || GRAD) write_packed<W, MODE, CB, SA>(ln, acc);
   }
   __syncthreads();
   // training: h2, h3 (layers 2, 3) or g4 (layer 4) to HBM; the tile is next
@@ -1026,28 +1037,28 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
   }
 }
 
-template <int W, int MODE, int L, bool TRAIN>
-__device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, MODE>& tc,
-                                           const float (&sp)[2][(Geo<W, MODE>::MT)][2][16], const TileDump& td,
-                                           APre<W, MODE>& ap) {
-  constexpr int MT = Geo<W, MODE>::MT;
-  f32x16 acc[MT][2];
+template <int W, int MODE, int CB, int L, bool TRAIN>
+__device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, MODE, CB>& tc,
+                                           const float (&sp)[2][(Geo<W, MODE, CB>::MT)][CB][16], const TileDump& td,
+                                           APre<W, MODE, CB>& ap) {
+  constexpr int MT = Geo<W, MODE, CB>::MT;
+  f32x16 acc[MT][CB];
   constexpr int RA = rev_arith<MODE>();
   // Single FP16 products use only the hi halves of the tile, so the two reverse
   // layers alternate halves: g4 (hi) -> g3 (lo) -> g2 (hi).  Nobody reads the half
   // a layer writes, so its stores need no barrier before them.
   constexpr bool PP = RA == kF16 && !TRAIN;
-  const View<W, MODE> v0(tc);
-  const char* br = (PP && L == 1) ? v0.ln.act_r + Geo<W, MODE>::LO_OFF : v0.ln.act_r;
-  if constexpr (!rev_zero_c<MODE>()) zero_acc<W, MODE>(acc);
-  layer_gemm<W, MODE, RA, rev_zero_c<MODE>()>(acc, net.bwd[L], net.bwd[L - 1], v0.b.voff, br, ap);
-  const View<W, MODE> vw(tc);
-  const Lane<W, MODE>& ln = vw.ln;
-  constexpr bool DEFER = !PP && defer_stores<W, MODE, TRAIN>(false);  // as in fwd_hidden
+  const View<W, MODE, CB> v0(tc);
+  const char* br = (PP && L == 1) ? v0.ln.act_r + Geo<W, MODE, CB>::LO_OFF : v0.ln.act_r;
+  if constexpr (!rev_zero_c<MODE>()) zero_acc<W, MODE, CB>(acc);
+  layer_gemm<W, MODE, CB, RA, rev_zero_c<MODE>()>(acc, net.bwd[L], net.bwd[L - 1], v0.b.voff, br, ap);
+  const View<W, MODE, CB> vw(tc);
+  const Lane<W, MODE, CB>& ln = vw.ln;
+  constexpr bool DEFER = !PP && defer_stores<W, MODE, CB, TRAIN>(false);  // as in fwd_hidden
   if constexpr (!DEFER && !PP) __syncthreads();
   static_for<MT>([&](auto I) {
     static_for<2>([&](auto GP) {
-      static_for<2>([&](auto NT) {
+      static_for<CB>([&](auto NT) {
         float x[8], y[8];
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
@@ -1059,12 +1070,12 @@ __device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, M
           uint32_t w[8];
           act_pack8<RA, !lane_k_order<MODE>()>(x, y, w);
           typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-          constexpr int off = (2 * I + GP) * Geo<W, MODE>::STEP_BYTES + NT * 512;
+          constexpr int off = (2 * I + GP) * Geo<W, MODE, CB>::STEP_BYTES + NT * 512;
           *reinterpret_cast<u32x4*>((L == 2 ? ln.act_w_lo : ln.act_w) + off) = u32x4{w[0], w[1], w[2], w[3]};
         } else if constexpr (DEFER) {
           park_packed<MODE, RA, GP>(x, y, acc[I][NT]);
         } else {
-          act_store_pair<W, MODE, I, GP, NT, RA>(ln, x, y);
+          act_store_pair<W, MODE, CB, I, GP, NT, RA>(ln, x, y);
         }
       });
       __builtin_amdgcn_sched_barrier(0);
@@ -1072,7 +1083,7 @@ __device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, M
   });
   if constexpr (DEFER) {
     __syncthreads();  // every wave has finished reading the tile
-    write_packed<W, MODE, RA>(ln, acc);
+    write_packed<W, MODE, CB, RA>(ln, acc);
   }
   __syncthreads();
   if constexpr (TRAIN) {  // g3 or g2, with their bias sums
@@ -1096,12 +1107,12 @@ constexpr bool mma_input(bool pairs, bool sph) {
 }
 constexpr int kVbBytes = 64;  // per query: B fragments of the inputs, hi then lo
 
-template <int W, int MODE, int I>
-__device__ __forceinline__ void input_gemm(const Lane<W, MODE>& ln, const Bases<W, MODE>& b, const char* vb,
-                                           f32x16 (&z)[2]) {
-  bf16x8 bh[2], bl[2];
+template <int W, int MODE, int CB, int I>
+__device__ __forceinline__ void input_gemm(const Lane<W, MODE, CB>& ln, const Bases<W, MODE, CB>& b, const char* vb,
+                                           f32x16 (&z)[CB]) {
+  bf16x8 bh[CB], bl[CB];
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
+  for (int nt = 0; nt < CB; ++nt) {
     const char* p = vb + (32 * nt + ln.n0) * kVbBytes + ln.kh * 16;
     bh[nt] = *reinterpret_cast<const bf16x8*>(p);
     bl[nt] = *reinterpret_cast<const bf16x8*>(p + 32);
@@ -1126,11 +1137,11 @@ __device__ __forceinline__ void input_gemm(const Lane<W, MODE>& ln, const Bases<
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float bias = b.w1[(16 * I + 4 * g + r) * 12 + 3];
-      z[0][4 * g + r] = bias;
-      z[1][4 * g + r] = bias;
+#pragma unroll
+      for (int nt = 0; nt < CB; ++nt) z[nt][4 * g + r] = bias;
     }
 #pragma unroll
-  for (int nt = 0; nt < 2; ++nt) {
+  for (int nt = 0; nt < CB; ++nt) {
     z[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh[nt], z[nt], 0, 0, 0);
     z[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl[nt], z[nt], 0, 0, 0);
     z[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh[nt], z[nt], 0, 0, 0);
@@ -1145,10 +1156,10 @@ __device__ __forceinline__ void input_gemm(const Lane<W, MODE>& ln, const Bases<
 // chain c + w0 x0 + w1 x1 + w2 x2 of arm_term's order, at 2 issue slots for 16
 // elements instead of 48, and a row's weights are loaded once per tile of rows
 // rather than by every lane.
-template <int W, int MODE, bool PAIRS>
-__device__ __forceinline__ void input_preact_tile(const Lane<W, MODE>& ln, const Bases<W, MODE>& b, int i, int nt,
+template <int W, int MODE, int CB, bool PAIRS>
+__device__ __forceinline__ void input_preact_tile(const Lane<W, MODE, CB>& ln, const Bases<W, MODE, CB>& b, int i, int nt,
                                                   f32x16& z) {
-  constexpr int XF = Geo<W, MODE>::XIN_FLOATS;
+  constexpr int XF = Geo<W, MODE, CB>::XIN_FLOATS;
   const float* w = b.w1a + i * 16 * 12;    // A: row lane%32 of the tile, step element kh
   const float* x = b.xin + nt * 32 * XF;   // B: query lane%32 of the block, step element kh
 #pragma unroll
@@ -1179,30 +1190,31 @@ __device__ __forceinline__ void input_preact_tile(const Lane<W, MODE>& ln, const
 // own g1 (B) and holds the four sums of its own column (D), each the fused
 // multiply-add chain that the vector ALU would run, at 2 issue slots for an element's
 // 8 sums; a lane loads 2 floats of a row instead of 12, one group of four rows ahead.
+template <int CB>
 struct GradSums {
-  f32x4 v[2][2];  // [column block][p'x p'y a1 a2 | a3..a6]
+  f32x4 v[CB][2];  // [column block][p'x p'y a1 a2 | a3..a6]
 };
 
-template <int W, int MODE, bool PAIRS, bool TRAIN, bool SPH, class F>
-__device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MODE>& tc,
-                                          GradSums (&epart)[Geo<W, MODE>::GPW], const TileDump& td, const char* vb,
-                                          APre<W, MODE>& ap, F&& before_copy) {
-  constexpr int MT = Geo<W, MODE>::MT;
-  const View<W, MODE> v0(tc);
-  f32x16 acc[MT][2];
-  if constexpr (!rev_zero_c<MODE>()) zero_acc<W, MODE>(acc);
-  layer_gemm<W, MODE, rev_arith<MODE>(), rev_zero_c<MODE>()>(acc, net.bwd[0], net.bwd[0], v0.b.voff, v0.ln.act_r, ap);
-  const View<W, MODE> vw(tc);
-  const Lane<W, MODE>& ln = vw.ln;
-  const Bases<W, MODE>& b = vw.b;
-  float g1keep[TRAIN ? MT : 1][2][16];
+template <int W, int MODE, int CB, bool PAIRS, bool TRAIN, bool SPH, class F>
+__device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MODE, CB>& tc,
+                                          GradSums<CB> (&epart)[Geo<W, MODE, CB>::GPW], const TileDump& td, const char* vb,
+                                          APre<W, MODE, CB>& ap, F&& before_copy) {
+  constexpr int MT = Geo<W, MODE, CB>::MT;
+  const View<W, MODE, CB> v0(tc);
+  f32x16 acc[MT][CB];
+  if constexpr (!rev_zero_c<MODE>()) zero_acc<W, MODE, CB>(acc);
+  layer_gemm<W, MODE, CB, rev_arith<MODE>(), rev_zero_c<MODE>()>(acc, net.bwd[0], net.bwd[0], v0.b.voff, v0.ln.act_r, ap);
+  const View<W, MODE, CB> vw(tc);
+  const Lane<W, MODE, CB>& ln = vw.ln;
+  const Bases<W, MODE, CB>& b = vw.b;
+  float g1keep[TRAIN ? MT : 1][CB][16];
   constexpr bool KEPT = TRAIN && MODE == kBF16;  // SiLU'(z1) kept by the input layer
   if constexpr (KEPT) {
-    constexpr int T = Geo<W, MODE>::THREADS;
+    constexpr int T = Geo<W, MODE, CB>::THREADS;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
+      for (int nt = 0; nt < CB; ++nt)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 sv = *reinterpret_cast<const f32x4*>(td.sp1 + (((i * 2 + nt) * 4 + g) * T + threadIdx.x) * 4);
@@ -1226,17 +1238,17 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
     if constexpr (!TRAIN) load_rows(a[0], 0);
     static_for<MT>([&](auto I) {
       if constexpr (mma_input<W, MODE>(PAIRS, SPH)) {
-        f32x16 z[2];
-        input_gemm<W, MODE, I>(ln, b, vb, z);
+        f32x16 z[CB];
+        input_gemm<W, MODE, CB, I>(ln, b, vb, z);
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < CB; ++nt)
 #pragma unroll
           for (int j = 0; j < 16; ++j) acc[I][nt][j] *= silu_prime_only(z[nt][j]);
       } else {
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int nt = 0; nt < CB; ++nt) {
           f32x16 z;
-          input_preact_tile<W, MODE, PAIRS>(ln, b, I, nt, z);
+          input_preact_tile<W, MODE, CB, PAIRS>(ln, b, I, nt, z);
 #pragma unroll
           for (int j = 0; j < 16; ++j) acc[I][nt][j] *= silu_prime_only(z[j]);
           __builtin_amdgcn_sched_barrier(0);
@@ -1244,11 +1256,11 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
       }
       if constexpr (TRAIN) {  // training needs g1, not J
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
+        for (int nt = 0; nt < CB; ++nt)
 #pragma unroll
           for (int j = 0; j < 16; ++j) g1keep[I][nt][j] = acc[I][nt][j];
       } else {
-        GradSums& ep = epart[Geo<W, MODE>::GPW > 1 ? (int)I : 0];
+        GradSums<CB>& ep = epart[Geo<W, MODE, CB>::GPW > 1 ? (int)I : 0];
         static_for<4>([&](auto GG) {
           constexpr int grp = 4 * I + GG;
           if constexpr (grp + 1 < 4 * MT) load_rows(a[(grp + 1) & 1], grp + 1);
@@ -1258,7 +1270,7 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
 #pragma unroll
             for (int k = 0; k < 2; ++k)
 #pragma unroll
-              for (int nt = 0; nt < 2; ++nt)
+              for (int nt = 0; nt < CB; ++nt)
                 ep.v[nt][k] = __builtin_amdgcn_mfma_f32_4x4x1f32(a[grp & 1][r][k], acc[I][nt][4 * GG + r], ep.v[nt][k], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
         });
@@ -1270,11 +1282,11 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
     __syncthreads();
     static_for<MT>([&](auto I) {
       static_for<2>([&](auto GP) {
-        static_for<2>([&](auto NT) {
+        static_for<CB>([&](auto NT) {
           float v[8];
 #pragma unroll
           for (int q = 0; q < 8; ++q) v[q] = g1keep[I][NT][8 * GP + q];
-          act_store_pair<W, MODE, I, GP, NT>(ln, v);
+          act_store_pair<W, MODE, CB, I, GP, NT>(ln, v);
         });
       });
     });
@@ -1289,29 +1301,29 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
 
 // Input layer (FP32): z1 = W1 [p'; a] + b1, h1 = SiLU(z1) -> LDS.  KEEP: SiLU'(z1)
 // also goes to sp1 (train_sp1's layout) for the reverse sweep.
-template <int W, int MODE, bool PAIRS, bool SPH, bool KEEP = false>
-__device__ __forceinline__ void fwd_input(const TileCtx<W, MODE>& tc, const char* vb,
+template <int W, int MODE, int CB, bool PAIRS, bool SPH, bool KEEP = false>
+__device__ __forceinline__ void fwd_input(const TileCtx<W, MODE, CB>& tc, const char* vb,
                                           float* sp1 = nullptr) {
-  constexpr int MT = Geo<W, MODE>::MT;
-  const View<W, MODE> vw(tc);
-  const Lane<W, MODE>& ln = vw.ln;
-  const Bases<W, MODE>& b = vw.b;
+  constexpr int MT = Geo<W, MODE, CB>::MT;
+  const View<W, MODE, CB> vw(tc);
+  const Lane<W, MODE, CB>& ln = vw.ln;
+  const Bases<W, MODE, CB>& b = vw.b;
   static_assert(!KEEP || mma_input<W, MODE>(PAIRS, SPH), "SiLU'(z1) is kept by the BF16 training tiles");
   if constexpr (mma_input<W, MODE>(PAIRS, SPH)) {
     static_for<MT>([&](auto I) {
-      f32x16 z[2];
-      input_gemm<W, MODE, I>(ln, b, vb, z);
+      f32x16 z[CB];
+      input_gemm<W, MODE, CB, I>(ln, b, vb, z);
       static_for<2>([&](auto GP) {
-        static_for<2>([&](auto NT) {
+        static_for<CB>([&](auto NT) {
           float v[8], dv[8];
 #pragma unroll
           for (int q = 0; q < 8; ++q) {
             if constexpr (KEEP) silu_fwd(z[NT][8 * GP + q], v[q], dv[q]);
             else v[q] = silu_only(z[NT][8 * GP + q]);
           }
-          act_store_pair<W, MODE, I, GP, NT>(ln, v);
+          act_store_pair<W, MODE, CB, I, GP, NT>(ln, v);
           if constexpr (KEEP) {
-            constexpr int T = Geo<W, MODE>::THREADS;
+            constexpr int T = Geo<W, MODE, CB>::THREADS;
             constexpr int k = ((I * 2 + NT) * 16 + 8 * GP) / 4;  // first of the two 16-byte groups
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -1325,9 +1337,9 @@ __device__ __forceinline__ void fwd_input(const TileCtx<W, MODE>& tc, const char
     return;
   }
   static_for<MT>([&](auto I) {
-    static_for<2>([&](auto NT) {
+    static_for<CB>([&](auto NT) {
       f32x16 z;
-      input_preact_tile<W, MODE, PAIRS>(ln, b, I, NT, z);
+      input_preact_tile<W, MODE, CB, PAIRS>(ln, b, I, NT, z);
       static_for<2>([&](auto GP) {
         float x[8], y[8];
 #pragma unroll
@@ -1335,7 +1347,7 @@ __device__ __forceinline__ void fwd_input(const TileCtx<W, MODE>& tc, const char
           x[q] = z[8 * GP + q];
           y[q] = sigmoid(x[q]);
         }
-        act_store_pair<W, MODE, I, GP, NT>(ln, x, y);
+        act_store_pair<W, MODE, CB, I, GP, NT>(ln, x, y);
       });
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -1376,12 +1388,14 @@ __device__ __forceinline__ float* train_sp1(char* lds) {
 // last barrier.  GRAD: the reverse sweep and J too; without it the tile ends with d
 // (and keeps no SiLU').  SPH: the
 // obstacles are spheres (x, y, z, r) and the network input is [p', r, a].
-template <int W, int MODE, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
+template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
 __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, int64_t kk, int64_t q0,
-                                             TileCtx<W, MODE>& tc) {
-  using G = Geo<W, MODE>;
+                                             TileCtx<W, MODE, CB>& tc) {
+  using G = Geo<W, MODE, CB>;
   constexpr int MT = G::MT;
   constexpr int XF = G::XIN_FLOATS;
+  constexpr int TQ = G::TQ;
+  static_assert(!TRAIN || CB == 2, "training runs 64-sample tiles");
   const int tid = threadIdx.x;
   float* xin = tc.xin;
   float* crow = tc.crow;
@@ -1395,9 +1409,9 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
   const bool fetched = PREFETCH && tc.nx_ok;
   auto fetch_next = [&]() {
     if constexpr (PREFETCH) {
-      const int64_t qn = q0 + (int64_t)gridDim.x * kTileQ;
+      const int64_t qn = q0 + (int64_t)gridDim.x * TQ;
       tc.nx_ok = qn < qlimit && !job.csr_off && !job.kidx && !job.pidx && !job.pidx32;
-      if (tid < kTileQ && tc.nx_ok) {
+      if (tid < TQ && tc.nx_ok) {
         const int64_t q = qn + tid;
         const int64_t qc = q < qlimit ? q : qlimit - 1;
         const float* kn = job.knots + qc * kInDim;
@@ -1412,7 +1426,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
   };
 
   // ---- prologue: base-frame points (+ per-knot arm term of the input layer) ----
-  if (tid < kTileQ) {
+  if (tid < TQ) {
     const int64_t q = q0 + tid;
     const int64_t qc = q < qlimit ? q : qlimit - 1;   // clamp the ragged tail (never stored)
     int64_t ki = 0, pi = 0;
@@ -1494,8 +1508,8 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
       for (int c = 0; c < 9; ++c) {
         const float v = x[c < 3 ? c : c + 2];
         const __bf16 hi = (__bf16)v;
-        vt[c * kTileQ + tid] = hi;
-        vt[(9 + c) * kTileQ + tid] = (__bf16)(v - (float)hi);
+        vt[c * TQ + tid] = hi;
+        vt[(9 + c) * TQ + tid] = (__bf16)(v - (float)hi);
       }
     }
     x[kXinRadius] = SPH ? pxyz[3] : 0.f;  // the radius passes through the rigid transform
@@ -1549,7 +1563,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
     td.G = job.dumpG;
     td.ldb = job.ldb;
     td.q0 = q0;
-    td.nvalid = (int)(qlimit - q0 < kTileQ ? qlimit - q0 : kTileQ);
+    td.nvalid = (int)(qlimit - q0 < TQ ? qlimit - q0 : TQ);
     td.layer_elems = (size_t)W * job.ldb;
     td.elem_bytes = MODE == kFP32 ? 4 : 2;
     // LDS beyond the query's own: the fused loss's partial sums ([waves][64]); the
@@ -1569,35 +1583,37 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
     td.b5 = tc.b5;
     td.inv_b = job.inv_b;
   }
-  APre<W, MODE> ap;  // each layer's first weight fragments, requested ahead of it
-  preload_a<W, MODE>(ap, net.fwd[0], View<W, MODE>(tc).b.voff);
-  fwd_input<W, MODE, PAIRS, SPH, TRAIN && MODE == kBF16>(tc, tc.act + G::ACT_BYTES / 2, td.sp1);
+  APre<W, MODE, CB> ap;  // each layer's first weight fragments, requested ahead of it
+  preload_a<W, MODE, CB>(ap, net.fwd[0], View<W, MODE, CB>(tc).b.voff);
+  fwd_input<W, MODE, CB, PAIRS, SPH, TRAIN && MODE == kBF16>(tc, tc.act + G::ACT_BYTES / 2, td.sp1);
   __syncthreads();
   if constexpr (TRAIN) {
     dump_tile<W, MODE>(td.act, td.stage, td.h(0), td.ldb, td.q0, td.nvalid);  // h1
   }
 
   // ---- hidden layers 2..4 (forward), keeping SiLU' of layers 2 and 3 ----
-  float sp[2][MT][2][16];
-  float dpart[G::GPW][2];
-#pragma unroll
-  for (int k = 0; k < G::GPW; ++k) dpart[k][0] = dpart[k][1] = 0.f;
-  fwd_hidden<W, MODE, 0, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
-  fwd_hidden<W, MODE, 1, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
-  fwd_hidden<W, MODE, 2, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
-
-  // ---- reverse sweep: W4^T, W3^T (into LDS), W2^T (into the input-layer gradient) ----
-  GradSums epart[G::GPW];
+  float sp[2][MT][CB][16];
+  float dpart[G::GPW][CB];
 #pragma unroll
   for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int nt = 0; nt < CB; ++nt) dpart[k][nt] = 0.f;
+  fwd_hidden<W, MODE, CB, 0, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
+  fwd_hidden<W, MODE, CB, 1, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
+  fwd_hidden<W, MODE, CB, 2, TRAIN, GRAD>(net, tc, sp, dpart, td, ap);
+
+  // ---- reverse sweep: W4^T, W3^T (into LDS), W2^T (into the input-layer gradient) ----
+  GradSums<CB> epart[G::GPW];
+#pragma unroll
+  for (int k = 0; k < G::GPW; ++k)
+#pragma unroll
+    for (int nt = 0; nt < CB; ++nt)
 #pragma unroll
       for (int t = 0; t < 2; ++t) epart[k].v[nt][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   if constexpr (GRAD) {
-    bwd_hidden<W, MODE, 2, TRAIN>(net, tc, sp, td, ap);
-    bwd_hidden<W, MODE, 1, TRAIN>(net, tc, sp, td, ap);
-    bwd_input<W, MODE, PAIRS, TRAIN, SPH>(net, tc, epart, td, tc.act + G::ACT_BYTES / 2, ap, fetch_next);
+    bwd_hidden<W, MODE, CB, 2, TRAIN>(net, tc, sp, td, ap);
+    bwd_hidden<W, MODE, CB, 1, TRAIN>(net, tc, sp, td, ap);
+    bwd_input<W, MODE, CB, PAIRS, TRAIN, SPH>(net, tc, epart, td, tc.act + G::ACT_BYTES / 2, ap, fetch_next);
     if constexpr (rev_arith<MODE>() == kF16) {
       // a lane whose output partial sum is finite but whose input-gradient partial
       // sums are not: the FP16 reverse sweep overflowed (the forward accumulates in
@@ -1608,7 +1624,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
 #pragma unroll
       for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
+        for (int nt = 0; nt < CB; ++nt) {
           float t = 0.f;
 #pragma unroll
           for (int c = 0; c < 8; ++c) t += epart[k].v[nt][c >> 2][c & 3];
@@ -1624,7 +1640,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
 #pragma unroll
     for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < CB; ++nt) {
         dpart[k][nt] += __shfl_xor(dpart[k][nt], 32);
 #pragma unroll
         for (int c = 0; c < (GRAD ? 8 : 0); ++c)
@@ -1633,17 +1649,17 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
     // the reduction buffer may share the activation tile: every wave must have
     // finished reading it
     if constexpr (G::RED_IN_ACT) __syncthreads();
-    const Lane<W, MODE> ln(tc.act, View<W, MODE>::fresh_tid(), tc.wave);
+    const Lane<W, MODE, CB> ln(tc.act, View<W, MODE, CB>::fresh_tid(), tc.wave);
 #pragma unroll
     for (int k = 0; k < G::GPW; ++k)
 #pragma unroll
-      for (int nt = 0; nt < 2; ++nt) {
+      for (int nt = 0; nt < CB; ++nt) {
         // lane half 0 stores d and the first four components, half 1 the other four
-        float* r = red + (ln.wave * G::GPW + k) * G::RED_VALS * kTileQ + 32 * nt + ln.n0;
+        float* r = red + (ln.wave * G::GPW + k) * G::RED_VALS * TQ + 32 * nt + ln.n0;
         if (ln.h == 0) r[0] = dpart[k][nt];
 #pragma unroll
         for (int c = 0; c < (GRAD ? 4 : 0); ++c)
-          r[(1 + 4 * ln.h + c) * kTileQ] = ln.h ? epart[k].v[nt][1][c] : epart[k].v[nt][0][c];
+          r[(1 + 4 * ln.h + c) * TQ] = ln.h ? epart[k].v[nt][1][c] : epart[k].v[nt][0][c];
       }
     __syncthreads();
 
@@ -1658,18 +1674,18 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
       int n = tid & 63;
       asm volatile("" : "+v"(n));
       auto total = [&](int c) {
-        float sum = red[c * kTileQ + n];
+        float sum = red[c * TQ + n % TQ];
 #pragma unroll
-        for (int w = 1; w < G::RG; ++w) sum += red[(w * G::RED_VALS + c) * kTileQ + n];
+        for (int w = 1; w < G::RG; ++w) sum += red[(w * G::RED_VALS + c) * TQ + n % TQ];
         return sum * (1.0f / rev_scale<MODE>());
       };
-      float* jt = G::RED_IN_ACT ? red + G::RED_BYTES / 4 : reinterpret_cast<float*>(tc.act);  // [64][9]
+      float* jt = G::RED_IN_ACT ? red + G::RED_BYTES / 4 : reinterpret_cast<float*>(tc.act);  // [TQ][9]
       const bool want_J = GRAD && job.J;
       const int64_t out0 = (PAIRS || GATHER) ? q0 : kk * job.Np + q0;
       if (ln.wave == 0) {
         const float dv = total(0) + tc.b5;
         const int64_t q = q0 + n;
-        const bool valid = q < qlimit;
+        const bool valid = n < TQ && q < qlimit;
         // outputs are streamed with non-temporal stores: written once and never read
         // here, they would otherwise evict the packed weights from L2
         if (valid && job.d) __builtin_nontemporal_store(dv, job.d + out0 + n);
@@ -1685,7 +1701,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
           }
         }
       } else if (ln.wave == 1) {
-        if (want_J) {
+        if (want_J && n < TQ) {
           const float* x = xin + n * XF;
           const float cs = x[3], sn = x[4], e0 = total(1), e1 = total(2);
           // (which product is fused is spelled out, so that every instantiation rounds alike)
@@ -1693,7 +1709,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
           jt[n * kInDim + 1] = -__builtin_fmaf(cs, e1, sn * e0);
           jt[n * kInDim + 2] = __builtin_fmaf(e0, x[1], -(e1 * x[0]));
         }
-      } else if (want_J) {
+      } else if (want_J && n < TQ) {
 #pragma unroll
         for (int c = 0; c < 6; c += G::NW - 2) {
           const int a = c + ln.wave - 2;
@@ -1704,7 +1720,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
       if (want_J) {
         const int64_t left = (qlimit - q0) * kInDim;
         float* Jo = job.J + out0 * kInDim;
-        for (int t = tid; t < kTileQ * kInDim; t += G::THREADS)
+        for (int t = tid; t < TQ * kInDim; t += G::THREADS)
           if (t < left) __builtin_nontemporal_store(jt[t], Jo + t);
       }
     }
@@ -1717,8 +1733,8 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
 
 // End of a kernel that ran tiles: if any tile of this workgroup flagged an FP16
 // overflow, write the context's host-visible flag (all threads call it).
-template <int W, int MODE>
-__device__ __forceinline__ void report_overflow(const DevNet& net, const TileCtx<W, MODE>& tc) {
+template <int W, int MODE, int CB>
+__device__ __forceinline__ void report_overflow(const DevNet& net, const TileCtx<W, MODE, CB>& tc) {
   if constexpr (rev_arith<MODE>() == kF16) {
     __syncthreads();
     if (threadIdx.x == 0 && *tc.ovf && net.overflow)
@@ -1729,23 +1745,23 @@ __device__ __forceinline__ void report_overflow(const DevNet& net, const TileCtx
 // ----------------------------------------------------------------------------
 // One-shot kernel: a persistent grid strides over all tiles of one job.
 // ----------------------------------------------------------------------------
-template <int W, int MODE, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
-__global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void fused_query(const DevNet net, const Job job,
+template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
+__global__ __launch_bounds__((Geo<W, MODE, CB>::THREADS), (Geo<W, MODE, CB>::WPE)) void fused_query(const DevNet net, const Job job,
                                                                                          int64_t ntiles) {
-  static_assert(Geo<W, MODE>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0) + 16 <= 160 * 1024,
+  static_assert(Geo<W, MODE, CB>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0) + 16 <= 160 * 1024,
                 "the workgroup's LDS exceeds the compute unit's 160 KiB");
-  __shared__ __attribute__((aligned(16))) char lds[Geo<W, MODE>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0)];
+  __shared__ __attribute__((aligned(16))) char lds[Geo<W, MODE, CB>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0)];
   __shared__ uint32_t ovf;
-  TileCtx<W, MODE> tc(lds, &ovf, net, threadIdx.x);
+  TileCtx<W, MODE, CB> tc(lds, &ovf, net, threadIdx.x);
   float* bsum = TRAIN ? train_bsum<W, MODE>(lds) : nullptr;
   if (bsum) {  // ordered before the first tile's sums by its barriers
-    for (int j = threadIdx.x; j < kTrainSumRows * W; j += Geo<W, MODE>::THREADS) bsum[j] = 0.f;
+    for (int j = threadIdx.x; j < kTrainSumRows * W; j += Geo<W, MODE, CB>::THREADS) bsum[j] = 0.f;
   }
-  const int64_t nblk = PAIRS ? 0 : (job.Np + kTileQ - 1) / kTileQ;
+  const int64_t nblk = PAIRS ? 0 : (job.Np + (Geo<W, MODE, CB>::TQ) - 1) / (Geo<W, MODE, CB>::TQ);
   int64_t kk = PAIRS ? 0 : blockIdx.x / nblk;  // dense: the knot of the current tile
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     if constexpr (PAIRS) {
-      process_tile<W, MODE, GRAD, true, TRAIN, false, SPH>(net, job, 0, tile * kTileQ, tc);
+      process_tile<W, MODE, CB, GRAD, true, TRAIN, false, SPH>(net, job, 0, tile * (Geo<W, MODE, CB>::TQ), tc);
     } else if constexpr (GATHER) {
       if (tile >= job.tile_off[job.K]) break;  // the grid is sized by an upper bound
       int64_t lo = 0, hi = job.K - 1;            // knot: the last i with tile_off[i] <= tile
@@ -1753,10 +1769,10 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
         const int64_t mid = (lo + hi + 1) >> 1;
         if (job.tile_off[mid] <= tile) lo = mid; else hi = mid - 1;
       }
-      process_tile<W, MODE, GRAD, false, false, true, SPH>(net, job, lo,
-                                                           job.row_off[lo] + (tile - job.tile_off[lo]) * kTileQ, tc);
+      process_tile<W, MODE, CB, GRAD, false, false, true, SPH>(net, job, lo,
+                                                           job.row_off[lo] + (tile - job.tile_off[lo]) * (Geo<W, MODE, CB>::TQ), tc);
     } else {
-      process_tile<W, MODE, GRAD, false, false, false, SPH>(net, job, kk, (tile - kk * nblk) * kTileQ, tc);
+      process_tile<W, MODE, CB, GRAD, false, false, false, SPH>(net, job, kk, (tile - kk * nblk) * (Geo<W, MODE, CB>::TQ), tc);
       // the next tile's knot: at most one knot further when a knot has at least as
       // many tiles as the grid has workgroups, with no 64-bit division then
       const int64_t next = tile + gridDim.x;
@@ -1766,56 +1782,55 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
   }
   if (bsum) {  // this workgroup's sums; summed over workgroups in order afterwards
     __syncthreads();
-    for (int j = threadIdx.x; j < kTrainSumRows * W; j += Geo<W, MODE>::THREADS)
+    for (int j = threadIdx.x; j < kTrainSumRows * W; j += Geo<W, MODE, CB>::THREADS)
       job.bias_part[(int64_t)j * gridDim.x + blockIdx.x] = bsum[j];
   }
-  report_overflow<W, MODE>(net, tc);
+  report_overflow<W, MODE, CB>(net, tc);
 }
 
 // ----------------------------------------------------------------------------
 // Host-side launchers of fused_query (grid = min(tiles, CUs)); each source file
 // instantiates the obstacle kind (SPH) it serves.
 // ----------------------------------------------------------------------------
-template <int W, int MODE, bool GRAD, bool PAIRS, bool SPH>
+template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool SPH>
 static hipError_t launch_t(const DevNet& net, const Job& job, int num_cu, hipStream_t s) {
-  using G = Geo<W, MODE>;
-  const int64_t ntiles = PAIRS ? (job.npairs + kTileQ - 1) / kTileQ
-                               : (job.tile_off ? job.ntiles_bound : job.K * ((job.Np + kTileQ - 1) / kTileQ));
+  using G = Geo<W, MODE, CB>;
+  const int64_t ntiles = query_tiles(job, PAIRS, G::TQ);
   if (ntiles <= 0) return hipSuccess;
   const dim3 grid((unsigned)fused_grid(ntiles, num_cu * G::WGS)), block(G::THREADS);
-  if constexpr (GRAD && PAIRS && W == 256 && (MODE == kFP32 || MODE == kBF16) && !SPH) {  // training: width 256, FP32 or BF16
+  if constexpr (CB == 2 && GRAD && PAIRS && W == 256 && (MODE == kFP32 || MODE == kBF16) && !SPH) {  // training: width 256, FP32 or BF16
     if (job.dumpH) {
       // the kernel writes its sums to bias_part, no J, and d only with the fused loss
       if ((MODE == kBF16 && !job.bias_part) || job.J || (job.d && !job.target)) return hipErrorInvalidValue;
-      hipLaunchKernelGGL((fused_query<W, MODE, true, true, true>), grid, block, 0, s, net, job, ntiles);
+      hipLaunchKernelGGL((fused_query<W, MODE, CB, true, true, true>), grid, block, 0, s, net, job, ntiles);
       return hipGetLastError();
     }
   }
   if (job.dumpH || job.seed) return hipErrorInvalidValue;  // a seed is honoured by the training instantiation only
   if constexpr (!PAIRS) {
     if (job.tile_off) {
-      hipLaunchKernelGGL((fused_query<W, MODE, GRAD, false, false, true, SPH>), grid, block, 0, s, net, job, ntiles);
+      hipLaunchKernelGGL((fused_query<W, MODE, CB, GRAD, false, false, true, SPH>), grid, block, 0, s, net, job, ntiles);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((fused_query<W, MODE, GRAD, PAIRS, false, false, SPH>), grid, block, 0, s, net, job, ntiles);
+  hipLaunchKernelGGL((fused_query<W, MODE, CB, GRAD, PAIRS, false, false, SPH>), grid, block, 0, s, net, job, ntiles);
   return hipGetLastError();
 }
 
-template <int W, int MODE, bool SPH>
+template <int W, int MODE, int CB, bool SPH>
 static hipError_t launch_m(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s) {
   if (want_grad)
-    return pairs ? launch_t<W, MODE, true, true, SPH>(net, job, num_cu, s) : launch_t<W, MODE, true, false, SPH>(net, job, num_cu, s);
-  return pairs ? launch_t<W, MODE, false, true, SPH>(net, job, num_cu, s) : launch_t<W, MODE, false, false, SPH>(net, job, num_cu, s);
+    return pairs ? launch_t<W, MODE, CB, true, true, SPH>(net, job, num_cu, s) : launch_t<W, MODE, CB, true, false, SPH>(net, job, num_cu, s);
+  return pairs ? launch_t<W, MODE, CB, false, true, SPH>(net, job, num_cu, s) : launch_t<W, MODE, CB, false, false, SPH>(net, job, num_cu, s);
 }
 
-template <int W, bool SPH>
+template <int W, int CB, bool SPH>
 static hipError_t launch_w(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s) {
   switch (net.mode) {
-    case kFP32: return launch_m<W, kFP32, SPH>(net, job, pairs, want_grad, num_cu, s);
-    case kBF16: return launch_m<W, kBF16, SPH>(net, job, pairs, want_grad, num_cu, s);
-    case kBF16X2F16: return launch_m<W, kBF16X2F16, SPH>(net, job, pairs, want_grad, num_cu, s);
-    default: return launch_m<W, kBF16X2, SPH>(net, job, pairs, want_grad, num_cu, s);
+    case kFP32: return launch_m<W, kFP32, CB, SPH>(net, job, pairs, want_grad, num_cu, s);
+    case kBF16: return launch_m<W, kBF16, CB, SPH>(net, job, pairs, want_grad, num_cu, s);
+    case kBF16X2F16: return launch_m<W, kBF16X2F16, CB, SPH>(net, job, pairs, want_grad, num_cu, s);
+    default: return launch_m<W, kBF16X2, CB, SPH>(net, job, pairs, want_grad, num_cu, s);
   }
 }
 
