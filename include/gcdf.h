@@ -155,8 +155,8 @@ gcdf_status gcdf_query(gcdf_ctx* ctx, const float* knots, int64_t K, const float
  * live in a fixed array of 65,536 keys (512 KiB) that the library holds on
  * each GPU until the process ends, instead of the context's workspace.  The
  * call allocates nothing.  Every call on one GPU (from any context) shares that
- * GPU's array, which keeps the last call's contents; the minimum clears the
- * keys it uses before each launch, so consecutive calls are independent, but
+ * GPU's array; the minimum sets the keys it used back to their start value, so
+ * consecutive calls are independent, but
  * calls that overlap on one GPU (other streams or threads) race and may
  * return wrong minima.  Arguments, layout and ownership as gcdf_query.
  * EINVAL as gcdf_query, and when the minimum is requested with K > 65,536;

@@ -22,7 +22,8 @@ thread_local std::string g_err;
 // Per-knot minimum keys of gcdf_query_noalloc, which allocates nothing: a
 // file-scope device array, one copy per GPU (held until the process ends).  Its
 // name is only a host-side stand-in; kernels get the device address that
-// hipGetSymbolAddress returns for the current device (g_noalloc_keys).
+// hipGetSymbolAddress returns for the current device (g_noalloc_keys).  It starts at
+// zero, as every call leaves it.
 constexpr int64_t kNoAllocMaxKnots = 1 << 16;  // 512 KiB of keys
 static __device__ __align__(256) unsigned long long scratch[kNoAllocMaxKnots];
 constexpr int kMaxDevices = 64;
@@ -202,6 +203,7 @@ gcdf_status gcdf_create(const gcdf_config* cfg, const void* blob, size_t bytes, 
   c->tile_off = reinterpret_cast<int64_t*>(c->minkey + c->cfg.max_knots);
   hipStream_t s = nullptr;
   e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+  if (e == hipSuccess) e = gcdf::launch_fill_zero(c->minkey, c->cfg.max_knots, s);  // every call leaves its keys at zero
   if (e == hipSuccess) e = hipMemcpyAsync(staging, static_cast<const char*>(blob) + kHeader, 4 * nfloat, hipMemcpyHostToDevice, s);
   char* base = static_cast<char*>(c->wbuf);
   // offsets of the source arrays inside staging (floats)
@@ -290,8 +292,8 @@ void gcdf_destroy(gcdf_ctx* ctx) {
 }  // extern "C"
 
 namespace {
-// gcdf_query with the per-knot key array `keys` (capacity key_cap knots), which
-// the minimum clears (all ones) before use.
+// gcdf_query with the per-knot key array `keys` (capacity key_cap knots), all zero
+// between calls: what decodes the keys sets them back.
 gcdf_status query_impl(gcdf_ctx* ctx, const float* knots, int64_t K, const float* points, int64_t Np, float* d,
                        float* J, float* dmin, int32_t* argmin, float* Jmin, unsigned long long* keys,
                        int64_t key_cap, const char* cap_name, void* stream) {
@@ -304,8 +306,6 @@ gcdf_status query_impl(gcdf_ctx* ctx, const float* knots, int64_t K, const float
   if (want_min && Np > INT32_MAX) return fail(GCDF_EINVAL, "Np=%lld exceeds 2^31-1", (long long)Np);
   DeviceGuard guard(ctx->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = hipSuccess;
-  if (want_min) e = gcdf::launch_minkey_init(keys, K, s);
   gcdf::Job job{};
   job.knots = knots;
   job.points = points;
@@ -314,20 +314,24 @@ gcdf_status query_impl(gcdf_ctx* ctx, const float* knots, int64_t K, const float
   job.d = d;
   job.J = J;
   job.minkey = want_min ? keys : nullptr;
-  if (e == hipSuccess) e = gcdf::launch_fused(ctx->net, job, false, J != nullptr, ctx->num_cu, s);
-  if (e == hipSuccess && want_min) e = gcdf::launch_minkey_decode(keys, K, dmin, argmin, s);
+  hipError_t e = gcdf::launch_fused(ctx->net, job, false, J != nullptr, ctx->num_cu, s);
+  if (e == hipSuccess && want_min && !Jmin) e = gcdf::launch_minkey_decode(keys, K, dmin, argmin, s);
   if (e == hipSuccess && Jmin) {
-    // the K pairs (knot i, point argmin[i]) through the pair-list kernel
+    // the K pairs (knot i, point argmin[i]) through the pair-list kernel, which decodes
+    // the keys on its way
     gcdf::Job pj{};
     pj.knots = knots;
     pj.points = points;
     pj.K = K;
     pj.Np = Np;
-    pj.pidx32 = argmin;
+    pj.dec_keys = keys;
+    pj.dec_dmin = dmin;
+    pj.dec_argmin = argmin;
     pj.npairs = K;
     pj.J = Jmin;
     e = gcdf::launch_fused(ctx->net, pj, true, true, ctx->num_cu, s);
   }
+  if (e != hipSuccess && want_min) (void)gcdf::launch_fill_zero(keys, K, s);  // a launch failed on the way
   return e == hipSuccess ? GCDF_OK : hip_fail(e, "gcdf_query launch");
 }
 }  // namespace

@@ -675,37 +675,29 @@ hipError_t pack_row_vectors(const float* src, float* dst, int width, int nvec, h
   return hipGetLastError();
 }
 
-__global__ void minkey_init_kernel(unsigned long long* k, int64_t K) {
+__global__ void fill_zero_kernel(unsigned long long* p, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < K) k[i] = ~0ull;
+  if (i < n) p[i] = 0ull;
 }
 
-hipError_t launch_fill_ones(unsigned long long* p, int64_t n, hipStream_t s) {
+hipError_t launch_fill_zero(unsigned long long* p, int64_t n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(minkey_init_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
+  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p, n);
   return hipGetLastError();
 }
 
-hipError_t launch_minkey_init(unsigned long long* minkey, int64_t K, hipStream_t s) {
-  hipLaunchKernelGGL(minkey_init_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s, minkey, K);
-  return hipGetLastError();
-}
-
-__global__ void minkey_decode_kernel(const unsigned long long* __restrict__ key, int64_t K, float* dmin,
-                                     int32_t* argmin) {
+__global__ void minkey_decode_kernel(unsigned long long* __restrict__ key, int64_t K, float* dmin, int32_t* argmin) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= K) return;
-  const unsigned long long k = key[i];
-  const uint32_t o = (uint32_t)(k >> 32);
-  const uint32_t u = (o & 0x80000000u) ? (o & 0x7fffffffu) : ~o;
-  if (dmin) dmin[i] = __uint_as_float(u);
-  // every knot of a launch receives at least one key; an untouched slot would
-  // decode to index 0 rather than an out-of-range point
-  if (argmin) argmin[i] = (k == ~0ull) ? 0 : (int32_t)(uint32_t)(k & 0xffffffffu);
+  float d;
+  int32_t a;
+  minkey_decode(key[i], d, a);
+  key[i] = 0ull;
+  if (dmin) dmin[i] = d;
+  if (argmin) argmin[i] = a;
 }
 
-hipError_t launch_minkey_decode(const unsigned long long* minkey, int64_t K, float* dmin, int32_t* argmin,
-                                hipStream_t s) {
+hipError_t launch_minkey_decode(unsigned long long* minkey, int64_t K, float* dmin, int32_t* argmin, hipStream_t s) {
   hipLaunchKernelGGL(minkey_decode_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, s, minkey, K, dmin,
                      argmin);
   return hipGetLastError();

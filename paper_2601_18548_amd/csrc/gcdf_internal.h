@@ -62,7 +62,12 @@ struct Job {
   int tile_q;                // rows per gathered tile: kTileQ or kTileQ / 2
   float* d;                  // dense: [K][Np]; pairs: [npairs]      (nullable)
   float* J;                  // dense: [K][Np][9]; pairs: [npairs][9] (nullable)
-  unsigned long long* minkey;// dense only: [K] ordered (distance, index) keys (nullable)
+  unsigned long long* minkey;// dense only: [K] inverted (distance, index) keys, zero on entry (nullable)
+  // pairs mode, when set: pair i is knot i and the point of key dec_keys[i], which is
+  // decoded to dec_dmin[i] and dec_argmin[i] and set back to zero
+  unsigned long long* dec_keys;
+  float* dec_dmin;
+  int32_t* dec_argmin;
   // training (pairs mode): the reverse sweep is seeded with seed[i] = dL/dd_i instead
   // of 1, and the tile's layer inputs h_{l+1} (dumpH[l]) and back-propagated
   // gradients dL/dz_{l+1} (dumpG[l]), l = 0..3, are written as [W x ldb] arrays in
@@ -176,12 +181,8 @@ hipError_t launch_fused_narrow(const DevNet& net, const Job& job, bool pairs, bo
 hipError_t launch_fused_sphere_narrow(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu,
                                       hipStream_t s);
 
-// minkey[i] = all ones, for i < K (fill kernel; graph-capture safe).
-hipError_t launch_minkey_init(unsigned long long* minkey, int64_t K, hipStream_t s);
-
-// Decode keys into dmin / argmin.
-hipError_t launch_minkey_decode(const unsigned long long* minkey, int64_t K, float* dmin, int32_t* argmin,
-                                hipStream_t s);
+// Decode keys into dmin / argmin and set them back to zero.
+hipError_t launch_minkey_decode(unsigned long long* minkey, int64_t K, float* dmin, int32_t* argmin, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // Serving: a persistent kernel claims tiles of published requests.
@@ -202,7 +203,7 @@ struct ServeDesc {
   uint64_t done_target; // value of the slot's cumulative done counter when this request is complete
   float* d;
   float* J;
-  unsigned long long* minkey;  // [K], all ones on entry; restored to all ones on completion
+  unsigned long long* minkey;  // [K], zero on entry; set back to zero on completion
   float* dmin;
   int32_t* argmin;
   float* Jmin;                 // [K][9] J at the argmin pairs (NULL: not wanted; needs dmin)
@@ -243,7 +244,8 @@ struct ServeDev {
 hipError_t launch_serve(const DevNet& net, ServeCtl* ctl, ServeDev* dev, uint64_t first_seq, uint64_t idle_ticks,
                         uint32_t epoch, int num_cu, hipStream_t s);
 
-hipError_t launch_fill_ones(unsigned long long* p, int64_t n, hipStream_t s);
+// p[i] = 0 for i < n (fill kernel; graph-capture safe).
+hipError_t launch_fill_zero(unsigned long long* p, int64_t n, hipStream_t s);
 
 // ----------------------------------------------------------------------------
 // Training: weight gradients from the dumped H / G (element type = bf16 for the

@@ -244,7 +244,7 @@ gcdf_status server_start(gcdf_ctx* ctx, size_t mem_budget, int nslots, Server** 
     sv->ctl->slots = sv->slots;
     e = hipMemsetAsync(sv->dev, 0, sizeof(ServeDev), sv->stream);
   }
-  if (e == hipSuccess) e = launch_fill_ones(sv->keys, sv->key_cap, sv->stream);
+  if (e == hipSuccess) e = launch_fill_zero(sv->keys, sv->key_cap, sv->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(sv->stream);
   if (e != hipSuccess) {
     server_stop(sv);

@@ -332,12 +332,12 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
       // this workgroup completed request fin.seq: per-knot minimum, key scratch restored
       if (fin.dmin) {
         for (int64_t k = tid; k < fin.K; k += Geo<W, MODE>::THREADS) {
-          const unsigned long long key = __hip_atomic_load(fin.minkey + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          const uint32_t o = (uint32_t)(key >> 32);
-          const uint32_t u = (o & 0x80000000u) ? (o & 0x7fffffffu) : ~o;
-          fin.dmin[k] = __uint_as_float(u);
-          fin.argmin[k] = key == ~0ull ? 0 : (int32_t)(uint32_t)(key & 0xffffffffu);
-          fin.minkey[k] = ~0ull;
+          float dm;
+          int32_t am;
+          minkey_decode(__hip_atomic_load(fin.minkey + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), dm, am);
+          fin.dmin[k] = dm;
+          fin.argmin[k] = am;
+          fin.minkey[k] = 0ull;
         }
       }
       if (fin.Jmin) {

@@ -558,6 +558,19 @@ __device__ __forceinline__ uint32_t ordered_bits(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// Per-knot minimum keys: (ordered distance bits << 32 | point index), stored inverted,
+// so that the minimum is an atomic maximum over words that start at zero, and a word
+// no tile has touched is zero.  Whoever decodes a word sets it back to zero for the
+// next call, which needs no launch to prepare its keys.
+__device__ __forceinline__ void minkey_decode(unsigned long long stored, float& d, int32_t& index) {
+  const unsigned long long k = ~stored;
+  const uint32_t o = (uint32_t)(k >> 32);
+  d = __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
+  // every knot of a launch receives at least one key; an untouched word would
+  // decode to index 0 rather than an out-of-range point
+  index = stored == 0 ? 0 : (int32_t)(uint32_t)(k & 0xffffffffu);
+}
+
 // ----------------------------------------------------------------------------
 // Training: copy the LDS activation tile (hi plane for the BF16 modes) to HBM in
 // the blocked feature-major layout: element (f, i) of a [W x batch] array sits at
@@ -1442,7 +1455,21 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
         pi = job.csr_idx[qc];
       } else {
         ki = job.kidx ? job.kidx[qc] : qc;
-        pi = job.pidx32 ? (int64_t)job.pidx32[qc] : (job.pidx ? job.pidx[qc] : qc);
+        if (!TRAIN && job.dec_keys) {
+          // J at the minimum: pair q is knot q and the point its key names; the minimum
+          // and its index are written here too
+          float dm;
+          int32_t am;
+          minkey_decode(job.dec_keys[qc], dm, am);
+          if (q < qlimit) {
+            job.dec_dmin[q] = dm;
+            job.dec_argmin[q] = am;
+            job.dec_keys[q] = 0ull;
+          }
+          pi = am;
+        } else {
+          pi = job.pidx32 ? (int64_t)job.pidx32[qc] : (job.pidx ? job.pidx[qc] : qc);
+        }
       }
     } else {
       ki = kk;
@@ -1697,7 +1724,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
               unsigned long long o = __shfl_xor(key, off);
               key = o < key ? o : key;
             }
-            if (n == 0 && key != ~0ull) atomicMin(job.minkey + kk, key);
+            if (n == 0 && key != ~0ull) atomicMax(job.minkey + kk, ~key);  // (stored inverted, see minkey_decode)
           }
         }
       } else if (ln.wave == 1) {

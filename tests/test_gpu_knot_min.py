@@ -130,3 +130,29 @@ def test_knot_min_benchmark_workload_slice(gcdf, oracle_mod):
     fmin, fam, fJm = gpu_min(gcdf, ctx, full_t, pt, "query")
     assert np.array_equal(fmin[sel], dmin) and np.array_equal(fam[sel], am) and np.array_equal(fJm[sel], Jm)
     ctx.close()
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("with_jacobian", [False, True])
+def test_minimum_keys_start_afresh(noalloc, with_jacobian):
+    """The minimum's keys are set back by the call that used them: a call over a subset
+    of the points (whose minimum is higher) sees nothing of a call over all of them,
+    also with other knot counts in between."""
+    import paper_2601_18548_amd as g
+
+    w = wl.weights(256, 11)
+    ctx = g.Context(w.to_blob(), 256, "bf16x2_f16")
+    pt = torch.from_numpy(wl.points_patches(3000, 12)).cuda()
+    kt = torch.from_numpy(wl.knots(300, 13)).cuda()
+    for K, Np in ((300, 3000), (7, 1), (300, 40), (33, 3000), (300, 1), (1, 65)):
+        k, p = kt[:K].contiguous(), pt[:Np].contiguous()
+        d, J = ctx.eval_grad(k, p)
+        dmin = torch.empty(K, device="cuda")
+        am = torch.empty(K, dtype=torch.int32, device="cuda")
+        Jm = torch.empty((K, 9), device="cuda") if with_jacobian else None
+        ctx.query(k, p, dmin=dmin, argmin=am, Jmin=Jm, noalloc=noalloc)
+        assert torch.equal(dmin, d.min(dim=1).values)
+        assert np.array_equal(am.cpu().numpy(), d.cpu().numpy().argmin(axis=1))
+        if with_jacobian:
+            assert torch.equal(Jm, J[torch.arange(K, device="cuda"), am.long()])
+    ctx.close()
