@@ -56,6 +56,9 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
   constexpr int sR = 8 * kArr;   // r_1..r_3
   constexpr int kNone = -1;
   const size_t layer = (size_t)W * job.ldb;
+  // this workgroup's sums over its samples (T1Job::part), each entry added to by one thread
+  float* rows = job.part + (size_t)blockIdx.x * kTrainSumRows * W;
+  for (int j = tid; j < kTrainSumRows * W; j += NTH) rows[j] = 0.f;
   // float4 idx of this thread in a scratch array (elements 4 (idx % 4) .. +3 of
   // accumulator (i, nt) with idx / 4 = i * 2 + nt)
   auto sget = [&](int base, int idx) {
@@ -112,7 +115,9 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
   for (int64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const int64_t q0 = tile * kTileQ;
     const int nvalid = (int)(job.B - q0 < kTileQ ? job.B - q0 : kTileQ);
-    auto dumpl = [&](float* arrbase, int l) { dump_tile<W, MODE>(tc.act, nullptr, arrbase + l * layer, job.ldb, q0, nvalid); };
+    auto dumpl = [&](float* arrbase, int l, const DumpSums* sm = nullptr, bool store = true) {
+      dump_tile<W, MODE>(tc.act, nullptr, arrbase + l * layer, job.ldb, q0, nvalid, sm, store);
+    };
     // ---- prologue: base-frame points, fbar and u of the tile's samples ----
     if (tid < kTileQ) {
       const int64_t q = q0 + tid;
@@ -134,10 +139,11 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
       x[11] = ok ? job.fbar[qc] : 0.f;
 #pragma unroll
       for (int c = 0; c < 9; ++c) uin[tid * 9 + c] = ok ? job.u[c * job.ldb + qc] : 0.f;
+      // db_out = sum_i fbar_i (fixed butterfly, then over the tiles in order)
+      float sf = x[11];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) job.V[c * job.ldb + q] = ok ? x[c] : 0.f;
-#pragma unroll
-      for (int c = 0; c < 6; ++c) job.V[(3 + c) * job.ldb + q] = ok ? x[5 + c] : 0.f;
+      for (int off = 32; off >= 1; off >>= 1) sf += __shfl_xor(sf, off);
+      if (tid == 0) rows[14 * W] += sf;
     }
     __syncthreads();
 
@@ -193,7 +199,8 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
       put_all(sZ + (L + 1) * kArr, a);
       emit(a, kNone, kNone, kNone, [&](int, int, int, float acc, float, float, float) { return silu_only(acc); });
       __syncthreads();
-      dumpl(job.H, L + 1);
+      const DumpSums sm{rows + 4 * W, tc.xin + 11, nullptr, nullptr, nullptr, 0, 0};  // sum_i fbar_i h4_i
+      dumpl(job.H, L + 1, L == 2 ? &sm : nullptr, L < 2);
       __syncthreads();
     });
     // ---- reverse sweep: g_4 = w_out s'(z_4); r_l = W_{l+1}^T g_{l+1}; g_l = r_l s'(z_l) ----
@@ -216,7 +223,8 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
         return acc * d1;
       });
       __syncthreads();
-      dumpl(job.G, L);
+      const DumpSums sm{nullptr, nullptr, rows + 5 * W, nullptr, uin, 9, 0};  // sum_i g1_i u_i^T
+      dumpl(job.G, L, L == 0 ? &sm : nullptr, L > 0);
       __syncthreads();
     });
     // ---- tangent pass along u: zdot_1 = W_1 u to the scratch, hdot_1 to LDS ----
@@ -273,7 +281,8 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
         return d1 * acc;
       });
       __syncthreads();
-      dumpl(job.Hd, L + 1);
+      const DumpSums sm{rows + 4 * W, nullptr, nullptr, nullptr, nullptr, 0, 0};  // sum_i hdot4_i
+      dumpl(job.Hd, L + 1, L == 2 ? &sm : nullptr, L < 2);
       __syncthreads();
     });
     // ---- adjoint of the primal ----
@@ -285,7 +294,8 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
       return (fb * w5) * d1 + w5 * d2 * zd;
     });
     __syncthreads();
-    dumpl(job.Zb, 3);
+    const DumpSums sm4{rows + 3 * W, nullptr, nullptr, nullptr, nullptr, 0, 0};  // sum_i zbar4_i
+    dumpl(job.Zb, 3, &sm4);
     static_for<3>([&](auto LL) {
       constexpr int L = 2 - LL;  // hbar_{L+1} = W_{L+2}^T zbar_{L+2}
       zero(a);
@@ -297,7 +307,9 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
         return hb * d1 + r * d2 * zd;
       });
       __syncthreads();
-      dumpl(job.Zb, L);
+      // sum_i zbar_i, and for the input layer sum_i zbar1_i v_i^T
+      const DumpSums sm{rows + L * W, nullptr, L == 0 ? rows + 5 * W : nullptr, nullptr, tc.xin, XF, 2};
+      dumpl(job.Zb, L, &sm, L > 0);
       __syncthreads();
     });
   }
@@ -956,12 +968,43 @@ __device__ __forceinline__ void part_sum_entry(const PartSum& ps, int j, int lan
   if (lane == 0) ps.out.base[r][(int64_t)f * ps.out.stride[r]] = s;
 }
 
+// The same over workgroup-major parts [nparts][kTrainSumRows][W]: block b takes 16
+// consecutive entries; thread (g, e) adds workgroups g, g + 16, ... of entry e in order
+// (64-byte reads, 16 in flight), then the 16 sums are added in order.
+__device__ __forceinline__ void part_sum_block(const PartSum& ps, int b) {
+  __shared__ float acc[16][16];
+  const int n = kTrainSumRows * ps.width, e = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int j = b * 16 + e;
+  float s = 0.f;
+  int w = g;
+  for (; w + 240 < ps.nparts; w += 256) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = ps.part[(int64_t)(w + 16 * u) * n + j];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s += v[u];
+  }
+  for (; w < ps.nparts; w += 16) s += ps.part[(int64_t)w * n + j];
+  acc[g][e] = s;
+  __syncthreads();
+  if (threadIdx.x >= 16) return;
+  float t = acc[0][e];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) t += acc[k][e];
+  const int r = j / ps.width, f = j % ps.width;
+  if (ps.out.base[r] && f < ps.out.n[r]) ps.out.base[r][(int64_t)f * ps.out.stride[r]] = t;
+}
+
 // out_j[e] = sum over chunks (in index order) of partial[j][chunk][e], 4 elements per
 // thread, blocks [j bx, (j + 1) bx) for GEMM j; the blocks after those: the training
-// kernel's per-workgroup sums (PartSum), one wave per entry.
+// kernel's per-workgroup sums (PartSum), one wave per entry, or 16 entries a block.
 __global__ void sum_chunks_kernel(const float* __restrict__ partial, int nchunks, int64_t n, WgradJobs jobs, int accum,
                                   PartSum ps, int bx) {
   const int b = blockIdx.x;
+  if (b >= jobs.n * bx && ps.by_wg) {
+    part_sum_block(ps, b - jobs.n * bx);
+    return;
+  }
   if (b >= jobs.n * bx) {
     part_sum_entry(ps, (b - jobs.n * bx) * (blockDim.x / 64) + (threadIdx.x >> 6), threadIdx.x & 63);
     return;
@@ -1011,132 +1054,10 @@ hipError_t launch_wgrad_gemm(const WgradJobs& jobs, int width, int mode, int64_t
   if (e != hipSuccess) return e;
   const int64_t n = (int64_t)width * width;
   const unsigned bx = (unsigned)((n / 4 + 255) / 256);
-  const unsigned bps = ps ? (unsigned)((kTrainSumRows * ps->width + 3) / 4) : 0u;  // 4 entries per block
+  const unsigned bps = ps ? (unsigned)(kTrainSumRows * ps->width / (ps->by_wg ? 16 : 4)) : 0u;  // entries per block
   hipLaunchKernelGGL(sum_chunks_kernel, dim3((unsigned)jobs.n * bx + bps), dim3(256), 0, s, partial, nchunks, n, jobs,
                      accumulate ? 1 : 0, ps ? *ps : PartSum{}, (int)bx);
   return hipGetLastError();
 }
-
-// Row reductions over the batch in two fixed-order passes, A in the blocked
-// feature-major layout of dump_tile.  Pass 1: grid (256-row group, chunk of
-// kRrChunk samples, job); a thread owns one row and walks the chunk's 16-byte
-// blocks in order (a workgroup reads 4 KB contiguous per block), V is read
-// uniformly.  Pass 2 adds the chunks in index order.  The result does not depend
-// on scheduling.
-constexpr int kRrChunk = 512;
-constexpr int kRrMaxC = 9;
-
-int rr_chunks(int64_t B) { return (int)((B + kRrChunk - 1) / kRrChunk); }
-
-// Several row reductions in one pass each (see RrJobs): job j's partial sums at
-// partial + j * job_stride, [chunk][row][kRrMaxC + 1] (the last slot the row sum).
-// A job without A reduces a single row of ones (out = sum V).
-template <bool BF>
-__global__ __launch_bounds__(256) void rr_multi_partial_kernel(RrJobs jobs, int64_t B, int64_t ldv,
-                                                               float* __restrict__ partial, int64_t job_stride) {
-  constexpr int S = BF ? 8 : 4;
-  __shared__ float sv[kRrMaxC][kRrChunk];
-  const RrJob& jb = jobs.job[blockIdx.z];
-  const int rows = jb.A ? jb.rows : 1, C = jb.C;
-  const int r = blockIdx.x * 256 + threadIdx.x;
-  if (blockIdx.x * 256 >= rows) return;  // a whole workgroup past this job's rows
-  const int64_t i0 = (int64_t)blockIdx.y * kRrChunk;
-  const int64_t i1 = i0 + kRrChunk < B ? i0 + kRrChunk : B;
-  for (int c = 0; c < C; ++c)
-    for (int k = threadIdx.x; k < kRrChunk; k += 256) sv[c][k] = i0 + k < i1 ? jb.V[(int64_t)c * ldv + i0 + k] : 0.f;
-  __syncthreads();
-  if (r >= rows) return;
-  float acc[kRrMaxC + 1];
-#pragma unroll
-  for (int c = 0; c <= kRrMaxC; ++c) acc[c] = 0.f;
-  constexpr int NB = 8;
-  typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 v8;
-  for (int64_t i = i0; i < i1; i += NB * S) {
-    float a[NB][S];
-    // rounds stay inside the zero-padded tail (chunks start at multiples of 64)
-#pragma unroll
-    for (int k = 0; k < NB; ++k) {
-      if (!jb.A) {
-#pragma unroll
-        for (int u = 0; u < S; ++u) a[k][u] = 1.f;  // V is zero past B
-        continue;
-      }
-      const int64_t blk = (((i + k * S) / S) * rows + r) * S;
-      if constexpr (BF) {
-        const v8 x = *reinterpret_cast<const v8*>(static_cast<const __bf16*>(jb.A) + blk);
-#pragma unroll
-        for (int u = 0; u < S; ++u) a[k][u] = (float)x[u];
-      } else {
-        const f32x4 x = *reinterpret_cast<const f32x4*>(static_cast<const float*>(jb.A) + blk);
-#pragma unroll
-        for (int u = 0; u < S; ++u) a[k][u] = x[u];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NB; ++k)
-#pragma unroll
-      for (int u = 0; u < S; ++u) acc[kRrMaxC] += a[k][u];
-    const int j0 = (int)(i - i0);
-    for (int c = 0; c < C; ++c) {
-      float t = acc[c];
-#pragma unroll
-      for (int k = 0; k < NB; ++k) {
-        const f32x4* vp = reinterpret_cast<const f32x4*>(&sv[c][j0 + k * S]);
-#pragma unroll
-        for (int h = 0; h < S / 4; ++h) {
-          const f32x4 vv = vp[h];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) t += a[k][4 * h + u] * vv[u];
-        }
-      }
-      acc[c] = t;
-    }
-  }
-  float* out = partial + blockIdx.z * job_stride + ((int64_t)blockIdx.y * rows + r) * (kRrMaxC + 1);
-#pragma unroll
-  for (int c = 0; c <= kRrMaxC; ++c) out[c] = acc[c];
-}
-
-__global__ void rr_multi_sum_kernel(RrJobs jobs, const float* __restrict__ partial, int64_t job_stride, int nchunks) {
-  const RrJob& jb = jobs.job[blockIdx.y];
-  const int rows = jb.A ? jb.rows : 1;
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = (int)(t / (kRrMaxC + 1)), c = (int)(t % (kRrMaxC + 1));
-  if (r >= rows || (c >= jb.C && c != kRrMaxC)) return;
-  const float* p = partial + blockIdx.y * job_stride;
-  float s = 0.f;
-#pragma unroll 8
-  for (int k = 0; k < nchunks; ++k) s += p[((int64_t)k * rows + r) * (kRrMaxC + 1) + c];
-  float* o = c == kRrMaxC ? jb.bias + r : (jb.out ? jb.out + (int64_t)r * jb.C + c : nullptr);
-  if (c == kRrMaxC && !jb.bias) return;
-  if (o) *o = jb.accumulate ? *o + s : s;
-}
-
-int64_t rr_multi_job_floats(int rows, int64_t B) { return (int64_t)rr_chunks(B) * rows * (kRrMaxC + 1); }
-
-hipError_t launch_row_reduce_multi(const RrJobs& jobs, bool a_is_bf16, int64_t B, int64_t ldv, float* partial,
-                                   hipStream_t s) {
-  if (jobs.n < 1 || jobs.n > kRrMaxJobs || B <= 0) return hipErrorInvalidValue;
-  int rmax = 1;
-  for (int j = 0; j < jobs.n; ++j) {
-    const RrJob& jb = jobs.job[j];
-    if (jb.C > kRrMaxC || (jb.C > 0 && !jb.V) || (jb.A && jb.rows <= 0) || (!jb.A && jb.C < 1)) return hipErrorInvalidValue;
-    if (jb.A && jb.rows > rmax) rmax = jb.rows;
-  }
-  const int nch = rr_chunks(B);
-  const int64_t stride = rr_multi_job_floats(rmax, B);
-  const dim3 grid((unsigned)((rmax + 255) / 256), (unsigned)nch, (unsigned)jobs.n);
-  if (a_is_bf16)
-    hipLaunchKernelGGL(rr_multi_partial_kernel<true>, grid, dim3(256), 0, s, jobs, B, ldv, partial, stride);
-  else
-    hipLaunchKernelGGL(rr_multi_partial_kernel<false>, grid, dim3(256), 0, s, jobs, B, ldv, partial, stride);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const int64_t n = (int64_t)rmax * (kRrMaxC + 1);
-  hipLaunchKernelGGL(rr_multi_sum_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)jobs.n), dim3(256), 0, s, jobs,
-                     partial, stride, nch);
-  return hipGetLastError();
-}
-
 
 }  // namespace gcdf

@@ -72,24 +72,19 @@ struct Job {
   // of 1, and the tile's layer inputs h_{l+1} (dumpH[l]) and back-propagated
   // gradients dL/dz_{l+1} (dumpG[l]), l = 0..3, are written as [W x ldb] arrays in
   // the blocked feature-major layout (element (f, i) at ((i / S) W + f) S + i % S,
-  // S = 16 bytes of samples); dumpV[c][i] = network input c (FP32), row stride ldb
-  // (a multiple of 64).
+  // S = 16 bytes of samples), ldb a multiple of 64; h_4 and dL/dz_1 are not written.
   const float* seed;
   void* dumpH;
   void* dumpG;
-  float* dumpV;
   int64_t ldb;
   // fused MSE loss (training, seed NULL, target set): each tile finishes d before its
-  // reverse sweep and seeds it with dL/dd_i = mse_scale (d_i - target_i), written to
-  // seed_out[i], and writes sq_out[i] = inv_b (d_i - target_i)^2 (i < npairs; both
-  // nullable).
+  // reverse sweep and seeds it with dL/dd_i = mse_scale (d_i - target_i); the loss
+  // adds inv_b (d_i - target_i)^2.
   const float* target;
-  float* seed_out;
-  float* sq_out;
   float mse_scale, inv_b;
-  // training, pure BF16: per-workgroup sums [kTrainSumRows][W][grid] (rows:
-  // sum_i g_l for l = 1..4; sum_i seed_i h4_i; sum_i g1_i v_c(i) for the nine
-  // inputs c; sum_i seed_i; the fused loss), so that h4 and g1 are not written
+  // training: per-workgroup sums, BF16 [kTrainSumRows][W][grid], FP32
+  // [grid][kTrainSumRows][W] (rows: sum_i g_l for l = 1..4; sum_i seed_i h4_i;
+  // sum_i g1_i v_c(i) for the nine inputs c; sum_i seed_i; the fused loss)
   float* bias_part;
 };
 constexpr int kTrainSumRows = 16;
@@ -256,7 +251,8 @@ hipError_t launch_fill_zero(unsigned long long* p, int64_t n, hipStream_t s);
 // (wgrad_partial_floats(B, width, num_cu) floats) reduced in a fixed order.  Rows
 // of G and H have stride ldb and hold zeros from B up to the next multiple of 64.
 // The batch is cut into as few chunks as keep one workgroup per (product, chunk,
-// 128 x 128 output tile) within num_cu, so every workgroup runs in one round.
+// 128 x 128 output tile) within num_cu, so every workgroup runs in one round.  (Two
+// FP32 workgroups per compute unit: batch 65,536 step 732 -> 907 us.)
 constexpr int kWgMaxJobs = 3;
 struct WgradJobs {
   const void* G[kWgMaxJobs];
@@ -275,6 +271,7 @@ struct PartOut {
 struct PartSum {
   const float* part;
   int nparts, width;
+  bool by_wg;  // part is [nparts][kTrainSumRows][width] (FP32), else [kTrainSumRows][width][nparts]
   PartOut out;
 };
 // ps (optional): those sums too, in the launch that adds the chunks.
@@ -284,32 +281,6 @@ hipError_t launch_wgrad_gemm(const WgradJobs& jobs, int width, int mode, int64_t
 // any launch of up to kWgMaxJobs products over at most B samples needs
 int64_t wgrad_chunk_len(int64_t B, int n, int width, int num_cu);
 int64_t wgrad_partial_floats(int64_t B, int width, int num_cu);
-// Row reductions over a batch: for each row r < rows, out[r][c] = sum_i A[r][i] V[c][i]
-// (c < C <= 9, V row stride ldv, V[c] holding at least B entries) and
-// bias[r] = sum_i A[r][i] (out / bias may be NULL), i < B, with A (rows x batch) in
-// the blocked feature-major layout of the training dumps (NULL: a single row of
-// ones); chunked partial sums added in a fixed order.  Up to kRrMaxJobs of them in
-// one pass of two launches, sharing ldv; no job writes another's outputs, and a job
-// with `accumulate` adds to what its outputs hold.  partial needs
-// n * rr_multi_job_floats(max rows, B) floats.
-int rr_chunks(int64_t B);
-constexpr int kRrMaxJobs = 7;
-struct RrJob {
-  const void* A;
-  int rows;
-  const float* V;
-  int C;
-  float* out;
-  float* bias;
-  int accumulate;  // 1: add to out / bias instead of overwriting them
-};
-struct RrJobs {
-  RrJob job[kRrMaxJobs];
-  int n;
-};
-int64_t rr_multi_job_floats(int rows, int64_t B);
-hipError_t launch_row_reduce_multi(const RrJobs& jobs, bool a_is_bf16, int64_t B, int64_t ldv, float* partial,
-                                   hipStream_t s);
 // Workgroups of a one-shot fused_query launch over ntiles tiles: one per compute
 // unit (each holds one), fewer for small launches.  Training's per-workgroup sums
 // are indexed by it.
@@ -320,8 +291,8 @@ inline int fused_grid(int64_t ntiles, int num_cu) { return (int)(ntiles < num_cu
 // reverse sweep for e = dF/dv, the tangent pass along u and the reverse mode through
 // both programs (see table1_tiles).  Dumps (blocked feature-major, [W x ldb] each):
 //   H[l] = h_{l+1}, G[l] = g_{l+1} (reverse sweep, = d/dz of the tangent output),
-//   Hd[l] = hdot_{l+1} (tangent), Zb[l] = zbar_{l+1} (adjoint of the primal), l = 0..3;
-// V[c][i] = network input c.  scratch: per workgroup of the grid, 11 arrays of
+//   Hd[l] = hdot_{l+1} (tangent), Zb[l] = zbar_{l+1} (adjoint of the primal), of which
+// H[3], G[0], Hd[3] and Zb[0], needed for sums only, are not written.  scratch: per workgroup of the grid, 11 arrays of
 // kThreads * 64 floats (pre-activations, tangent pre-activations, reverse products).
 struct T1Job {
   const float* knots;
@@ -333,7 +304,8 @@ struct T1Job {
   float* G;
   float* Hd;
   float* Zb;
-  float* V;
+  float* part;  // [grid][kTrainSumRows][W]: sum_i zbar_l (l = 1..4); sum_i fbar_i h4_i + hdot4_i;
+                // sum_i zbar1_i v_c(i) + g1_i u_c(i); sum_i fbar_i
   float* scratch;
 };
 constexpr int kT1ScratchArrays = 11;

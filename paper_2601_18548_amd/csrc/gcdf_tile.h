@@ -594,30 +594,56 @@ __device__ __forceinline__ void minkey_decode(unsigned long long stored, float& 
 // over samples; v is split into BF16 hi + lo).  In the copy, wave w owns features
 // 32w .. 32w + 31, its lane halves taking alternate 8-sample blocks.  store
 // false: the sums only, nothing written to HBM.
+// FP32, with sums: the same sums, thread f those of feature f, sample by sample on the
+// vector ALU (a few hundred FMAs against a tile's 100,000 cycles), added to the
+// workgroup's rows in global memory (each entry has one thread, so program order is
+// the order of the sum).  They replaced passes over the dumps that read 64 to 320 MB
+// back (batch 65,536) or ran on ten workgroups (batch 5,001: 42 us).
 // ----------------------------------------------------------------------------
 struct DumpSums {
-  float* row;          // [W]: sum_i x[f][i] w_i
+  float* row;          // [W]: sum_i x[f][i] w_i (NULL: not wanted)
   const float* seed;   // w_i = seed[i * XIN_FLOATS] (the records' seed slot), or NULL: w_i = 1
   float* in_rows;      // [9][W]: sum_i x[f][i] v_c(i), or NULL
-  const __bf16* vt;    // the tile's inputs v_c(i) as BF16 hi [9][64], then lo [9][64]
+  const __bf16* vt;    // BF16: the tile's inputs v_c(i) as BF16 hi [9][64], then lo [9][64]
+  // FP32: v_c(i) at in[i * in_stride + c], from c = 3 on at + in_gap further
+  const float* in;
+  int in_stride, in_gap;
 };
 
 template <int W, int MODE>
 __device__ __forceinline__ void dump_tile(const char* act, char* stage, void* dst, int64_t ldb, int64_t q0,
                                           int nvalid, const DumpSums* sums = nullptr, bool store = true) {
   (void)ldb;
-  for (int f = threadIdx.x; f < W && MODE == kFP32; f += Geo<W, MODE>::THREADS) {
-    const float* a = reinterpret_cast<const float*>(act);
+  if constexpr (MODE == kFP32) {
+    static_assert(Geo<W, MODE>::THREADS == W, "a thread per feature");
+    constexpr int XF = Geo<W, MODE>::XIN_FLOATS;
+    const int f = threadIdx.x;
+    const float* a = reinterpret_cast<const float*>(act) + (((f >> 3) * kTileQ) * 2 + (f & 1)) * 4 + ((f & 7) >> 1);
+    const bool row = sums && sums->row, in = sums && sums->in_rows;
+    float s = 0.f, sv[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
     for (int n = 0; n < kTileQ; n += 4) {
       f32x4 v;
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int nn = n + u;
-        v[u] = nn < nvalid ? a[(((f >> 3) * kTileQ + nn) * 2 + (f & 1)) * 4 + ((f & 7) >> 1)] : 0.f;
+      for (int u = 0; u < 4; ++u) v[u] = n + u < nvalid ? a[(n + u) * 8] : 0.f;
+      if (store) *reinterpret_cast<f32x4*>(static_cast<float*>(dst) + (((q0 + n) >> 2) * W + f) * 4) = v;
+      if (row) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) s += sums->seed ? v[u] * sums->seed[(n + u) * XF] : v[u];
       }
-      float* o = static_cast<float*>(dst) + (((q0 + n) >> 2) * W + f) * 4;
-      *reinterpret_cast<f32x4*>(o) = v;
+      if (in) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const float* x = sums->in + (n + u) * sums->in_stride;
+#pragma unroll
+          for (int c = 0; c < 9; ++c) sv[c] += v[u] * x[c < 3 ? c : c + sums->in_gap];
+        }
+      }
+    }
+    if (row) sums->row[f] += s;
+    if (in) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) sums->in_rows[c * W + f] += sv[c];
     }
   }
   if constexpr (MODE != kFP32) {
@@ -823,18 +849,16 @@ struct TileDump {
   int nvalid;
   size_t layer_elems;  // W * ldb
   size_t elem_bytes;
-  // fused MSE loss (Job::target): per-wave output partial sums, the per-query
-  // records (slot 11 takes the seed), and the loss terms
+  // fused MSE loss (Job::target): per-wave output partial sums and the per-query
+  // records (slot 11 takes the seed)
   float* dred;
   float* xin;
   const float* target;
-  float* seed_out;
-  float* sq_out;
   float* d_out;  // the distances, when asked for
   float mse_scale, inv_b;
   float b5;  // the output bias
-  // per-workgroup sums over its samples (LDS, [kTrainSumRows][width]; NULL when
-  // these gradients are reduced from the dumps instead): rows 0..3 the bias
+  // per-workgroup sums over its samples ([kTrainSumRows][width]; BF16 in LDS, FP32 in
+  // the workgroup's part of Job::bias_part): rows 0..3 the bias
   // gradients sum_i g_l (l = 1..4), row 4 dL/dw_out = sum_i seed_i h4_i, rows
   // 5..13 dW1[:, c] = sum_i g1_i v_c(i), row 14 (first entry) db_out = sum_i seed_i,
   // row 15 (first entry) the fused loss sum_i (d_i - target_i)^2 / B
@@ -842,7 +866,7 @@ struct TileDump {
   __bf16* vt;  // with bsum: the tile's network inputs, transposed, BF16 hi [9][64] then lo
   float* sp1;  // BF16: SiLU'(z1) of the input layer kept in LDS for the reverse sweep (see train_sp1)
   int width;
-  __device__ __forceinline__ float* row(int r) const { return bsum ? bsum + r * width : nullptr; }
+  __device__ __forceinline__ float* row(int r) const { return bsum + r * width; }
   __device__ __forceinline__ void* h(int l) const { return static_cast<char*>(H) + l * layer_elems * elem_bytes; }
   __device__ __forceinline__ void* g(int l) const { return static_cast<char*>(G) + l * layer_elems * elem_bytes; }
 };
@@ -941,7 +965,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
       }
     }
     __syncthreads();
-    if (threadIdx.x < kTileQ && (td.target || td.bsum)) {  // wave 0, one lane per query
+    if (threadIdx.x < kTileQ) {  // wave 0, one lane per query
       const int n = threadIdx.x;
       float* seedp = td.xin + n * Geo<W, MODE, CB>::XIN_FLOATS + 11;
       float sq = 0.f;
@@ -957,12 +981,8 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
         sq = td.inv_b * (r * r);
         *seedp = seed;
         if (valid && td.d_out) td.d_out[q] = dv;
-        if (valid && td.seed_out) {  // for the reductions from the dumps (FP32)
-          td.seed_out[q] = seed;
-          td.sq_out[q] = sq;
-        }
       }
-      if (td.bsum) {
+      {
         // db_out = sum_i seed_i and the loss, over the tile (fixed butterfly), then
         // over this workgroup's tiles in order
         float sd = *seedp;
@@ -977,12 +997,11 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
         }
       }
     }
-    // h4 is needed only for dL/dw_out = sum_i seed_i h4_i: summed here when the
-    // tile engine keeps the bias sums, else written out (after a barrier: wave 0
-    // wrote the seeds the copy reads)
+    // h4 is needed only for dL/dw_out = sum_i seed_i h4_i, summed here (after a
+    // barrier: wave 0 wrote the seeds the copy reads)
     __syncthreads();
-    const DumpSums sm{td.row(4), td.xin + 11, nullptr, td.vt};
-    dump_tile<W, MODE>(td.act, td.stage, td.h(3), td.ldb, td.q0, td.nvalid, td.bsum ? &sm : nullptr, !td.bsum);
+    const DumpSums sm{td.row(4), td.xin + 11, nullptr, td.vt, nullptr, 0, 0};
+    dump_tile<W, MODE>(td.act, td.stage, td.h(3), td.ldb, td.q0, td.nvalid, &sm, false);
     __syncthreads();  // h4 fully read before g4 overwrites the tile; seeds written
   }
   static_for<MT>([&](auto I) {
@@ -1044,9 +1063,8 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
   // training: h2, h3 (layers 2, 3) or g4 (layer 4) to HBM; the tile is next
   // overwritten only after the following K loop and its barrier
   if constexpr (TRAIN) {  // h2, h3, or g4 (with db4 = sum_i g4_i)
-    const DumpSums sm{td.row(3), nullptr, nullptr, td.vt};
-    dump_tile<W, MODE>(td.act, td.stage, L < 2 ? td.h(L + 1) : td.g(3), td.ldb, td.q0, td.nvalid,
-                       (L == 2 && td.bsum) ? &sm : nullptr);
+    const DumpSums sm{td.row(3), nullptr, nullptr, td.vt, nullptr, 0, 0};
+    dump_tile<W, MODE>(td.act, td.stage, L < 2 ? td.h(L + 1) : td.g(3), td.ldb, td.q0, td.nvalid, L == 2 ? &sm : nullptr);
   }
 }
 
@@ -1100,8 +1118,8 @@ __device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, M
   }
   __syncthreads();
   if constexpr (TRAIN) {  // g3 or g2, with their bias sums
-    const DumpSums sm{td.row(L), nullptr, nullptr, td.vt};
-    dump_tile<W, MODE>(td.act, td.stage, td.g(L), td.ldb, td.q0, td.nvalid, td.bsum ? &sm : nullptr);
+    const DumpSums sm{td.row(L), nullptr, nullptr, td.vt, nullptr, 0, 0};
+    dump_tile<W, MODE>(td.act, td.stage, td.g(L), td.ldb, td.q0, td.nvalid, &sm);
   }
 }
 
@@ -1305,10 +1323,9 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
     });
     __syncthreads();
     before_copy();
-    // g1 is needed only for db1 and dW1 = sum_i g1_i v_i^T: summed here when the
-    // tile engine keeps the sums, else written out
-    const DumpSums sm{td.row(0), nullptr, td.row(5), td.vt};
-    dump_tile<W, MODE>(td.act, td.stage, td.g(0), td.ldb, td.q0, td.nvalid, td.bsum ? &sm : nullptr, !td.bsum);
+    // g1 is needed only for db1 and dW1 = sum_i g1_i v_i^T, summed here
+    const DumpSums sm{td.row(0), nullptr, td.row(5), td.vt, td.xin, Geo<W, MODE>::XIN_FLOATS, 2};
+    dump_tile<W, MODE>(td.act, td.stage, td.g(0), td.ldb, td.q0, td.nvalid, &sm, false);
   }
 }
 
@@ -1557,15 +1574,6 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
       *reinterpret_cast<bf16x8*>(o + 32) = vl[0];
       *reinterpret_cast<bf16x8*>(o + 48) = vl[1];
     }
-    if constexpr (PAIRS) {
-      if (job.dumpV) {
-        const bool ok = q < qlimit;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) job.dumpV[c * job.ldb + q] = ok ? x[c] : 0.f;
-#pragma unroll
-        for (int c = 0; c < 6; ++c) job.dumpV[(3 + c) * job.ldb + q] = ok ? x[5 + c] : 0.f;
-      }
-    }
   }
   if constexpr (!PAIRS) {
     // the knot's arm joints, by scalar loads as above
@@ -1597,14 +1605,12 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
     // idle half of a pure-BF16 tile stages the dumps
     td.stage = tc.act + G::ACT_BYTES / 2;
     td.dred = reinterpret_cast<float*>(tc.act + G::LDS_BYTES);
-    td.bsum = train_bsum<W, MODE>(tc.act);
+    td.bsum = MODE == kBF16 ? train_bsum<W, MODE>(tc.act) : job.bias_part + (int64_t)blockIdx.x * kTrainSumRows * W;
     td.vt = train_vt<W, MODE>(tc.act);
     td.sp1 = train_sp1<W, MODE>(tc.act);
     td.width = W;
     td.xin = xin;
     td.target = job.seed ? nullptr : job.target;
-    td.seed_out = job.seed_out;
-    td.sq_out = job.sq_out;
     td.d_out = job.seed ? nullptr : job.d;
     td.mse_scale = job.mse_scale;
     td.b5 = tc.b5;
@@ -1772,17 +1778,20 @@ __device__ __forceinline__ void report_overflow(const DevNet& net, const TileCtx
 // ----------------------------------------------------------------------------
 // One-shot kernel: a persistent grid strides over all tiles of one job.
 // ----------------------------------------------------------------------------
-template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
-__global__ __launch_bounds__((Geo<W, MODE, CB>::THREADS), (Geo<W, MODE, CB>::WPE)) void fused_query(const DevNet net, const Job job,
-                                                                                         int64_t ntiles) {
+// WPE: waves per SIMD that the registers leave room for.
+template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false,
+          int WPE = Geo<W, MODE, CB>::WPE>
+__global__ __launch_bounds__((Geo<W, MODE, CB>::THREADS), WPE) void fused_query(const DevNet net, const Job job,
+                                                                                int64_t ntiles) {
   static_assert(Geo<W, MODE, CB>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0) + 16 <= 160 * 1024,
                 "the workgroup's LDS exceeds the compute unit's 160 KiB");
   __shared__ __attribute__((aligned(16))) char lds[Geo<W, MODE, CB>::LDS_BYTES + (TRAIN ? train_extra_lds<W, MODE>() : 0)];
   __shared__ uint32_t ovf;
   TileCtx<W, MODE, CB> tc(lds, &ovf, net, threadIdx.x);
   float* bsum = TRAIN ? train_bsum<W, MODE>(lds) : nullptr;
-  if (bsum) {  // ordered before the first tile's sums by its barriers
-    for (int j = threadIdx.x; j < kTrainSumRows * W; j += Geo<W, MODE, CB>::THREADS) bsum[j] = 0.f;
+  if constexpr (TRAIN) {  // ordered before the first tile's sums by its barriers (FP32: the same thread adds to them)
+    float* rows = bsum ? bsum : job.bias_part + (int64_t)blockIdx.x * kTrainSumRows * W;
+    for (int j = threadIdx.x; j < kTrainSumRows * W; j += Geo<W, MODE, CB>::THREADS) rows[j] = 0.f;
   }
   const int64_t nblk = PAIRS ? 0 : (job.Np + (Geo<W, MODE, CB>::TQ) - 1) / (Geo<W, MODE, CB>::TQ);
   int64_t kk = PAIRS ? 0 : blockIdx.x / nblk;  // dense: the knot of the current tile
@@ -1828,7 +1837,18 @@ static hipError_t launch_t(const DevNet& net, const Job& job, int num_cu, hipStr
   if constexpr (CB == 2 && GRAD && PAIRS && W == 256 && (MODE == kFP32 || MODE == kBF16) && !SPH) {  // training: width 256, FP32 or BF16
     if (job.dumpH) {
       // the kernel writes its sums to bias_part, no J, and d only with the fused loss
-      if ((MODE == kBF16 && !job.bias_part) || job.J || (job.d && !job.target)) return hipErrorInvalidValue;
+      if (!job.bias_part || job.J || (job.d && !job.target)) return hipErrorInvalidValue;
+      // FP32 batches of at most one tile per compute unit: with the whole register file
+      // the tile's h4 copy spills no SiLU' values (batch 5,001: step 176 -> 154 us); past
+      // that, two workgroups per compute unit are worth more than the spill (20,000:
+      // 321 -> 312 us)
+      if constexpr (MODE == kFP32) {
+        if (ntiles <= num_cu) {
+          hipLaunchKernelGGL((fused_query<W, MODE, CB, true, true, true, false, false, 1>), grid, block, 0, s, net, job,
+                             ntiles);
+          return hipGetLastError();
+        }
+      }
       hipLaunchKernelGGL((fused_query<W, MODE, CB, true, true, true>), grid, block, 0, s, net, job, ntiles);
       return hipGetLastError();
     }

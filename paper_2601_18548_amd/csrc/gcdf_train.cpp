@@ -7,7 +7,7 @@
 //           g_l = dL/dz_l written in a blocked feature-major layout -- then
 //             dW_l = G_l H_{l-1}^T       (matrix cores, split-K, fixed-order sum),
 //             dW_1 = G_1 V^T, db_l = sum_i G_l, dw_out = H_4 seed, db_out = sum seed
-//           (fixed-order row reductions);
+//           (summed per workgroup inside the kernel, then in a fixed order);
 // mse     : the backward's launches with the loss L = mean_i (d_i - y_i)^2 fused in:
 //           each tile finishes d before its reverse sweep and seeds it with
 //           dL/dd_i = 2 (d_i - y_i) / B, so no separate forward runs.
@@ -31,9 +31,7 @@ struct gcdf_trainer {
   size_t mbytes = 0, off_m = 0;
   void* dumpH = nullptr;
   void* dumpG = nullptr;
-  float* dumpV = nullptr;
-  float* mse = nullptr;  // fused MSE: per-sample seeds [ldb], then loss terms [ldb]
-  float* bias_part = nullptr;  // BF16: the training kernel's per-workgroup sums [kTrainSumRows][W][num_cu]
+  float* bias_part = nullptr;  // the training kernel's per-workgroup sums (Job::bias_part, T1Job::part)
   float* partial = nullptr;
   const float* packed_from = nullptr;  // params pointer of the last packing
   // Table I loss workspace (allocated at its first use)
@@ -124,64 +122,50 @@ gcdf::Job training_job(const gcdf_trainer* tr, const float* knots, const float* 
   job.dumpH = tr->dumpH;
   job.dumpG = tr->dumpG;
   job.ldb = tr->ldb;
-  if (tr->mode == GCDF_FP32) {
-    job.dumpV = tr->dumpV;  // for dW1, reduced from the dumps
-  } else {
-    job.bias_part = tr->bias_part;  // the kernel sums what needs no GEMM
-  }
+  job.bias_part = tr->bias_part;  // the kernel sums what needs no GEMM
   return job;
 }
 
-// After the training-mode query: the weight gradients from its dumps and the
-// per-sample seeds dL/dd; with sq set, also *loss = sum_i sq[i].
-hipError_t weight_gradients(gcdf_trainer* tr, int64_t B, const float* seed, const float* sq, float* loss, float* grad,
-                            hipStream_t s) {
+// Most workgroups of a training launch per compute unit (FP32 tiles run two).
+int wgs_per_cu(int mode) { return mode == GCDF_FP32 ? 2 : 1; }
+
+// Where the per-workgroup sums of `nparts` workgroups go: the bias gradients, dw_out,
+// dW1 column by column, db_out and (training kernel) the loss.
+gcdf::PartSum part_sums(const gcdf_trainer* tr, int nparts, float* loss, float* grad) {
+  const int W = tr->W;
+  const Offsets o(W);
+  gcdf::PartSum ps{};
+  ps.part = tr->bias_part;
+  ps.nparts = nparts;
+  ps.width = W;
+  ps.by_wg = tr->mode == GCDF_FP32;
+  float* rows[5] = {grad + o.b1, grad + o.bl[0], grad + o.bl[1], grad + o.bl[2], grad + o.w5};
+  for (int r = 0; r < 5; ++r) ps.out.base[r] = rows[r], ps.out.stride[r] = 1, ps.out.n[r] = W;
+  for (int c = 0; c < 9; ++c) ps.out.base[5 + c] = grad + o.W1 + c, ps.out.stride[5 + c] = 9, ps.out.n[5 + c] = W;
+  ps.out.base[14] = grad + o.b5, ps.out.stride[14] = 1, ps.out.n[14] = 1;
+  ps.out.base[15] = loss, ps.out.stride[15] = 1, ps.out.n[15] = 1;
+  return ps;
+}
+
+// After the training-mode query: the weight gradients from its dumps and its
+// per-workgroup sums (which the launch that adds the GEMMs' chunks adds too).
+hipError_t weight_gradients(gcdf_trainer* tr, int64_t B, float* loss, float* grad, hipStream_t s) {
   const int W = tr->W;
   const Offsets o(W);
   const size_t esz = tr->mode == GCDF_FP32 ? 4 : 2;
   const size_t layer = (size_t)W * tr->ldb * esz;
-  auto H = [&](int l) { return static_cast<const char*>(tr->dumpH) + l * layer; };
-  auto G = [&](int l) { return static_cast<const char*>(tr->dumpG) + l * layer; };
-  const bool bf = tr->mode != GCDF_FP32;
-  const int gmode = bf ? gcdf::kBF16 : gcdf::kFP32;
   // dW_{l+1} = G_{l+1} H_l^T for the hidden layers 2..4, one launch
   gcdf::WgradJobs wj{};
   wj.n = 3;
   for (int l = 0; l < 3; ++l) {
-    wj.G[l] = G(l + 1);
-    wj.H[l] = H(l);
+    wj.G[l] = static_cast<const char*>(tr->dumpG) + (l + 1) * layer;
+    wj.H[l] = static_cast<const char*>(tr->dumpH) + l * layer;
     wj.out[l] = grad + o.Wl[l];
   }
   const int64_t ntiles = (B + gcdf::kTileQ - 1) / gcdf::kTileQ;
-  if (bf) {
-    // everything else was summed per workgroup by the training kernel: the launch
-    // that adds the GEMMs' chunks also adds the workgroups' sums (bias gradients,
-    // dw_out, dW1 column by column, db_out, loss)
-    gcdf::PartSum ps{};
-    ps.part = tr->bias_part;
-    ps.nparts = gcdf::fused_grid(ntiles, tr->num_cu);
-    ps.width = W;
-    float* rows[5] = {grad + o.b1, grad + o.bl[0], grad + o.bl[1], grad + o.bl[2], grad + o.w5};
-    for (int r = 0; r < 5; ++r) ps.out.base[r] = rows[r], ps.out.stride[r] = 1, ps.out.n[r] = W;
-    for (int c = 0; c < 9; ++c) ps.out.base[5 + c] = grad + o.W1 + c, ps.out.stride[5 + c] = 9, ps.out.n[5 + c] = W;
-    ps.out.base[14] = grad + o.b5, ps.out.stride[14] = 1, ps.out.n[14] = 1;
-    ps.out.base[15] = loss, ps.out.stride[15] = 1, ps.out.n[15] = 1;
-    return gcdf::launch_wgrad_gemm(wj, W, gmode, tr->ldb, B, tr->partial, tr->num_cu, s, false, &ps);
-  }
-  hipError_t e = gcdf::launch_wgrad_gemm(wj, W, gmode, tr->ldb, B, tr->partial, tr->num_cu, s);
-  // FP32: one pass over the batch for the rest (the partial buffer is free again:
-  // this follows the GEMMs' chunk sum on the stream): input layer dW1 = G_1 V^T and
-  // db1 = sum G_1; db_l = sum G_l; output layer dw_out = H_4 seed, db_out = sum seed;
-  // the loss.  (Single-row V operands ignore the shared row stride ldb.)
-  gcdf::RrJobs rj{};
-  rj.n = sq ? 7 : 6;
-  rj.job[0] = {G(0), W, tr->dumpV, 9, grad + o.W1, grad + o.b1, 0};
-  for (int l = 0; l < 3; ++l) rj.job[1 + l] = {G(l + 1), W, nullptr, 0, nullptr, grad + o.bl[l], 0};
-  rj.job[4] = {H(3), W, seed, 1, grad + o.w5, nullptr, 0};
-  rj.job[5] = {nullptr, 1, seed, 1, grad + o.b5, nullptr, 0};
-  if (sq) rj.job[6] = {nullptr, 1, sq, 1, loss, nullptr, 0};
-  if (e == hipSuccess) e = gcdf::launch_row_reduce_multi(rj, false, B, tr->ldb, tr->partial, s);
-  return e;
+  const gcdf::PartSum ps = part_sums(tr, gcdf::fused_grid(ntiles, tr->num_cu * wgs_per_cu(tr->mode)), loss, grad);
+  const int gmode = tr->mode == GCDF_FP32 ? gcdf::kFP32 : gcdf::kBF16;
+  return gcdf::launch_wgrad_gemm(wj, W, gmode, tr->ldb, B, tr->partial, tr->num_cu, s, false, &ps);
 }
 
 }  // namespace
@@ -218,12 +202,10 @@ gcdf_status gcdf_trainer_create(int32_t width, int32_t precision, int32_t device
   if (e == hipSuccess) e = hipMalloc(&tr->wbuf, tr->off_m + 6 * tr->mbytes);
   if (e == hipSuccess) e = hipMalloc(&tr->dumpH, dump);
   if (e == hipSuccess) e = hipMalloc(&tr->dumpG, dump);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&tr->dumpV), (size_t)9 * tr->ldb * 4);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&tr->mse), (size_t)2 * tr->ldb * 4);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&tr->bias_part), (size_t)std::max(tr->num_cu, 1) * gcdf::kTrainSumRows * W * 4);
-  const size_t part = std::max({(size_t)gcdf::wgrad_partial_floats(max_batch, W, tr->num_cu),
-                                 (size_t)gcdf::rr_chunks(max_batch) * W * 10,
-                                 (size_t)gcdf::kRrMaxJobs * gcdf::rr_multi_job_floats(W, max_batch)});
+  if (e == hipSuccess)
+    e = hipMalloc(reinterpret_cast<void**>(&tr->bias_part),
+                  (size_t)std::max(tr->num_cu, 1) * wgs_per_cu(precision) * gcdf::kTrainSumRows * W * 4);
+  const size_t part = (size_t)gcdf::wgrad_partial_floats(max_batch, W, tr->num_cu);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&tr->partial), part * 4);
   if (e != hipSuccess) {
     gcdf_trainer_destroy(tr);
@@ -250,8 +232,6 @@ void gcdf_trainer_destroy(gcdf_trainer* tr) {
   (void)hipFree(tr->wbuf);
   (void)hipFree(tr->dumpH);
   (void)hipFree(tr->dumpG);
-  (void)hipFree(tr->dumpV);
-  (void)hipFree(tr->mse);
   (void)hipFree(tr->bias_part);
   (void)hipFree(tr->partial);
   (void)hipFree(tr->t1);
@@ -288,7 +268,7 @@ gcdf_status gcdf_train_backward(gcdf_trainer* tr, const float* params, const flo
   gcdf::Job job = training_job(tr, knots, points, B);
   job.seed = grad_d;
   if (e == hipSuccess) e = gcdf::launch_fused(tr->net, job, true, true, tr->num_cu, s);
-  if (e == hipSuccess) e = weight_gradients(tr, B, grad_d, nullptr, nullptr, grad, s);
+  if (e == hipSuccess) e = weight_gradients(tr, B, nullptr, grad, s);
   return e == hipSuccess ? GCDF_OK : tfail(GCDF_EDEVICE, "gcdf_train_backward: %s", hipGetErrorString(e));
 }
 
@@ -302,18 +282,12 @@ gcdf_status gcdf_train_mse(gcdf_trainer* tr, const float* params, const float* k
   hipStream_t s = static_cast<hipStream_t>(stream);
   hipError_t e = (reuse_packed && tr->packed_from == params) ? hipSuccess : pack(tr, params, s);
   gcdf::Job job = training_job(tr, knots, points, B);
-  float* seed = tr->mse;
-  float* sq = tr->mse + tr->ldb;
   job.target = target;
-  if (tr->mode == GCDF_FP32) {  // the seeds and loss terms for the reductions from the dumps
-    job.seed_out = seed;
-    job.sq_out = sq;
-  }
   job.mse_scale = (float)(2.0 / (double)B);
   job.inv_b = (float)(1.0 / (double)B);
   job.d = d;
   if (e == hipSuccess) e = gcdf::launch_fused(tr->net, job, true, true, tr->num_cu, s);
-  if (e == hipSuccess) e = weight_gradients(tr, B, seed, sq, loss, grad, s);
+  if (e == hipSuccess) e = weight_gradients(tr, B, loss, grad, s);
   return e == hipSuccess ? GCDF_OK : tfail(GCDF_EDEVICE, "gcdf_train_mse: %s", hipGetErrorString(e));
 }
 
@@ -334,7 +308,7 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
   const int W = tr->W;
   const int64_t ldb = tr->ldb;
   const size_t layer = (size_t)W * ldb;
-  const int grid = tr->num_cu;
+  const int grid = tr->num_cu * wgs_per_cu(tr->mode);
   const size_t arr = (size_t)gcdf::kThreads * 64;
   // workspace: d [ldb], J [9 ldb], fbar [ldb], u [9 ldb], part [4 ceil(ldb/256)], Hd, Zb [4 layer each],
   // scratch [grid * 11 * arr]
@@ -385,10 +359,11 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
   tj.G = Gs;
   tj.Hd = Hd;
   tj.Zb = Zb;
-  tj.V = tr->dumpV;
+  tj.part = tr->bias_part;
   tj.scratch = scratch;
   const int64_t ntiles = (B + gcdf::kTileQ - 1) / gcdf::kTileQ;
-  if (e == hipSuccess) e = gcdf::launch_table1_tiles(tr->net, tj, (int)std::min<int64_t>(grid, ntiles), s);
+  const int t1_grid = gcdf::fused_grid(ntiles, grid);
+  if (e == hipSuccess) e = gcdf::launch_table1_tiles(tr->net, tj, t1_grid, s);
   // 4. dW_l = sum zbar_l h_{l-1}^T + g_l hdot_{l-1}^T for the hidden layers
   gcdf::WgradJobs a{}, b{};
   a.n = b.n = 3;
@@ -400,22 +375,10 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
     a.out[l] = b.out[l] = grad + o.Wl[l];
   }
   if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(a, W, gcdf::kFP32, ldb, B, tr->partial, tr->num_cu, s, false);
-  if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(b, W, gcdf::kFP32, ldb, B, tr->partial, tr->num_cu, s, true);
-  // 5. the rest in two passes over the batch (fixed-order row reductions, the second
-  //    adding to the first's outputs): input layer dW_1 = sum zbar_1 v^T + g_1 u^T,
-  //    db_1 = sum zbar_1; db_l = sum zbar_l; output layer dw_out = sum fbar h_4 + hdot_4,
-  //    db_out = sum fbar.  (v and u share the row stride ldb.)
-  gcdf::RrJobs r1{}, r2{};
-  r1.n = 6;
-  r1.job[0] = {Zb, W, tr->dumpV, 9, grad + o.W1, grad + o.b1, 0};
-  for (int l = 0; l < 3; ++l) r1.job[1 + l] = {Zb + (l + 1) * layer, W, nullptr, 0, nullptr, grad + o.bl[l], 0};
-  r1.job[4] = {H + 3 * layer, W, fbar, 1, grad + o.w5, nullptr, 0};
-  r1.job[5] = {nullptr, 1, fbar, 1, grad + o.b5, nullptr, 0};
-  r2.n = 2;
-  r2.job[0] = {Gs, W, u, 9, grad + o.W1, nullptr, 1};
-  r2.job[1] = {Hd + 3 * layer, W, nullptr, 0, nullptr, grad + o.w5, 1};
-  if (e == hipSuccess) e = gcdf::launch_row_reduce_multi(r1, false, B, ldb, tr->partial, s);
-  if (e == hipSuccess) e = gcdf::launch_row_reduce_multi(r2, false, B, ldb, tr->partial, s);
+  // and the tiles' sums: input layer dW_1 = sum zbar_1 v^T + g_1 u^T, db_l = sum zbar_l,
+  // output layer dw_out = sum fbar h_4 + hdot_4, db_out = sum fbar
+  const gcdf::PartSum ps = part_sums(tr, t1_grid, nullptr, grad);
+  if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(b, W, gcdf::kFP32, ldb, B, tr->partial, tr->num_cu, s, true, &ps);
   return e == hipSuccess ? GCDF_OK : tfail(GCDF_EDEVICE, "gcdf_train_table1: %s", hipGetErrorString(e));
 }
 
