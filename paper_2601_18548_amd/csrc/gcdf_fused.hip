@@ -116,7 +116,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
     const int64_t q0 = tile * kTileQ;
     const int nvalid = (int)(job.B - q0 < kTileQ ? job.B - q0 : kTileQ);
     auto dumpl = [&](float* arrbase, int l, const DumpSums* sm = nullptr, bool store = true) {
-      dump_tile<W, MODE>(tc.act, nullptr, arrbase + l * layer, job.ldb, q0, nvalid, sm, store);
+      dump_tile<W, MODE>(tc.act, arrbase + l * layer, job.ldb, q0, nvalid, sm, store);
     };
     // ---- prologue: base-frame points, fbar and u of the tile's samples ----
     if (tid < kTileQ) {

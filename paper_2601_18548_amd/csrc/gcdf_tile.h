@@ -167,8 +167,12 @@ template <int W, int MODE, int CB = 2>
 struct Geo {
   static constexpr int TQ = 32 * CB;                 // queries per tile
   static constexpr int NW = CB == 1 && MODE != kFP32 ? 8 : waves_for<W, MODE>();  // waves per workgroup
-  static constexpr int AR = CB == 1 && MODE != kFP32 ? (W == 256 ? 8 : 4) : 2;    // K steps of A in flight
-  static constexpr int BR = CB == 1 && MODE != kFP32 && W == 256 ? 4 : 2;         // K steps of B, the current one included
+  static constexpr bool SHORT_STEPS = CB == 1 && MODE != kFP32;
+  // (Pure BF16 at W=256 is in the same place: one product per fragment and 8 waves, so
+  // two K steps are 64 cycles of a SIMD.  BF16 training, batch 65,536: 180 us a step
+  // with AR = 2, 167 with 4, the same with longer rings of B.)
+  static constexpr int AR = SHORT_STEPS ? (W == 256 ? 8 : 4) : W == 256 && MODE == kBF16 ? 4 : 2;  // K steps of A in flight
+  static constexpr int BR = SHORT_STEPS && W == 256 ? 4 : 2;  // K steps of B, the current one included
   static constexpr int THREADS = 64 * NW;
   static constexpr int MT = W / (32 * NW);           // 32-row M tiles per wave
   // The packed matrices and row vectors are laid out for 4 row groups of PMT M
@@ -580,38 +584,42 @@ __device__ __forceinline__ void minkey_decode(unsigned long long stored, float& 
 // caches on purpose: the weight-gradient kernels that follow read the dumps back,
 // largely from the last-level cache; non-temporal stores made the backward pass
 // half again as slow.)
-// BF16: the tile is transposed into `stage` (32 KiB of LDS, the idle half of a
-// pure-BF16 tile) and then copied out, so that a wave's store instruction writes
-// 1 KiB of consecutive pieces instead of 16 bytes into each of 64 cache lines.
-// Piece P (16 bytes: 8 samples of one feature) sits at slot P ^ ((P >> 4) & 7),
-// which spreads the 16 pieces written by 16 consecutive lanes over 16 different
-// bank groups, and those read by 16 consecutive lanes too.
+// BF16: wave w copies features 32w .. 32w + 31 of the 64 samples.  It transposes them
+// on the matrix cores: 32 samples x 16 features as A fragments (16 bytes a lane, as
+// they lie in the tile) times the identity give 32 x 32 blocks with a feature per lane
+// and samples in its registers; half a dozen moves and one exchange of lane halves
+// pack 8 samples of a feature into 16 bytes, and a wave's store writes 1 KiB of
+// consecutive pieces.  The product of a finite BF16 value with 1 plus zeros is exact
+// (a sample with an infinite value gives NaN in its block: its gradient is not finite
+// either way).  Transposing 8 x 8 blocks with vector instructions through a 32 KiB LDS
+// stage, and the sums below on the vector ALU, a dump took 3.1-3.6 K cycles and the
+// sums-only copies of h4 and g1 4.4 and 5.0 K, in all 30 K of a tile's 79 K; here 1.1-1.3,
+// 1.6 and 2.1 K of 52 K (batch 65,536: the kernel 155 -> 121 us).
 // BF16, with sums: the copy also adds, over the tile's samples i, to LDS rows
-// (per feature f) sum_i x[f][i] w_i (w_i = seed_i, or 1) in a fixed order
-// (samples within a piece, pieces in order, then the two lanes sharing a
-// feature), and optionally sum_i x[f][i] v_c(i) for the nine network inputs v_c
-// on the matrix cores (the pieces are the A fragments of a 32 x 32 x 16 product
-// over samples; v is split into BF16 hi + lo).  In the copy, wave w owns features
-// 32w .. 32w + 31, its lane halves taking alternate 8-sample blocks.  store
-// false: the sums only, nothing written to HBM.
+// (per feature f) sum_i x[f][i] w_i (w_i = seed_i, or 1), and optionally
+// sum_i x[f][i] v_c(i) for the nine network inputs v_c: products over samples on the
+// matrix cores, with the pieces as B fragments (the seeds in three BF16 parts, which
+// hold all 24 bits; v in BF16 hi + lo).  store false: the sums only, nothing written
+// to HBM.
 // FP32, with sums: the same sums, thread f those of feature f, sample by sample on the
 // vector ALU (a few hundred FMAs against a tile's 100,000 cycles), added to the
 // workgroup's rows in global memory (each entry has one thread, so program order is
 // the order of the sum).  They replaced passes over the dumps that read 64 to 320 MB
 // back (batch 65,536) or ran on ten workgroups (batch 5,001: 42 us).
 // ----------------------------------------------------------------------------
+constexpr int kVtSeed = 18, kVtRows = 21;  // rows of the transposed inputs (DumpSums::vt)
 struct DumpSums {
   float* row;          // [W]: sum_i x[f][i] w_i (NULL: not wanted)
   const float* seed;   // w_i = seed[i * XIN_FLOATS] (the records' seed slot), or NULL: w_i = 1
   float* in_rows;      // [9][W]: sum_i x[f][i] v_c(i), or NULL
-  const __bf16* vt;    // BF16: the tile's inputs v_c(i) as BF16 hi [9][64], then lo [9][64]
+  const __bf16* vt;    // BF16: the tile's inputs v_c(i) as BF16 hi [9][64], lo [9][64], then the seeds' parts [3][64]
   // FP32: v_c(i) at in[i * in_stride + c], from c = 3 on at + in_gap further
   const float* in;
   int in_stride, in_gap;
 };
 
 template <int W, int MODE>
-__device__ __forceinline__ void dump_tile(const char* act, char* stage, void* dst, int64_t ldb, int64_t q0,
+__device__ __forceinline__ void dump_tile(const char* act, void* dst, int64_t ldb, int64_t q0,
                                           int nvalid, const DumpSums* sums = nullptr, bool store = true) {
   (void)ldb;
   if constexpr (MODE == kFP32) {
@@ -648,92 +656,98 @@ __device__ __forceinline__ void dump_tile(const char* act, char* stage, void* ds
   }
   if constexpr (MODE != kFP32) {
     // The hi plane holds, for each group of 8 features and each query n, the 8
-    // features' values as one 16-byte word.  A thread reads the 8x8 block of 8
-    // consecutive queries, transposes it in registers and stages the 8 features'
-    // 16-byte pieces of that query block; then every thread copies pieces out.
-    static_assert(MODE == kBF16 && W * kTileQ * 2 <= Geo<W, MODE>::ACT_BYTES / 2, "staging needs a pure-BF16 tile");
+    // features' values as one 16-byte word.
+    static_assert(MODE == kBF16, "the dumps of the training precisions");
     typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-    const char* a = act;
-    constexpr int NG = W / 8;  // feature groups
-    constexpr int NP = W * (kTileQ / 8);  // pieces: (query block nb, feature f) at nb W + f
-    // Each wave stages exactly the pieces it copies out below (features 32 w ..
-    // 32 w + 31: feature groups 4 w .. 4 w + 3, every query block), so the copy
-    // needs no workgroup barrier: one wave's LDS operations complete in order.
-    static_assert(Geo<W, MODE>::NW * 4 == NG, "each wave stages four feature groups");
-    if ((threadIdx.x & 63) < 32) {
-      const int g8 = 4 * (threadIdx.x >> 6) + (threadIdx.x & 3), nb = (threadIdx.x & 31) >> 2;
-      const int gbyte = (g8 >> 1) * Geo<W, MODE>::STEP_BYTES + (g8 & 1) * 1024;  // 16-feature step, 8-feature half
-      u32x4 m[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int n = nb * 8 + j;
-        m[j] = n < nvalid ? *reinterpret_cast<const u32x4*>(a + gbyte + n * 16) : u32x4{0u, 0u, 0u, 0u};
-      }
-#pragma unroll
-      for (int fl = 0; fl < 8; ++fl) {  // feature 8 g8 + fl: halves of word fl/2 of every m[j]
-        u32x4 row;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const uint32_t x0 = m[2 * jj][fl >> 1], x1 = m[2 * jj + 1][fl >> 1];
-          row[jj] = (fl & 1) ? ((x0 >> 16) | (x1 & 0xffff0000u)) : ((x0 & 0xffffu) | (x1 << 16));
-        }
-        const int P = nb * W + 8 * g8 + fl;
-        *reinterpret_cast<u32x4*>(stage + (P ^ ((P >> 4) & 7)) * 16) = row;
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     // the tile's pieces are consecutive in the dump: piece P at element ((q0 / 8) W + P) 8
     constexpr int T = Geo<W, MODE>::THREADS;
     static_assert(T % W == 0, "a thread's pieces share one feature");
-    constexpr int XF = Geo<W, MODE>::XIN_FLOATS;
-    static_assert(T / 64 == W / 32 && NP == T * 4, "the copy: one 32-feature block per wave, 4 rounds");
+    static_assert(T / 64 == W / 32, "the copy: one 32-feature block per wave");
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int f = 32 * (threadIdx.x >> 6) + (lane & 31);
     __bf16* o = static_cast<__bf16*>(dst) + (q0 >> 3) * W * 8;
-    float part = 0.f;
     f32x16 dacc;
 #pragma unroll
     for (int j = 0; j < 16; ++j) dacc[j] = 0.f;
-    const int c = lane & 31;  // input column of the v fragments
+    const int c = lane & 31;
+    // identity fragments of the wave's two K steps: lane (c, half) of step k holds rows
+    // 16 k + 8 half + e, e = 0..7, of column c
+    bf16x8 eye[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      u32x4 d;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        d[e] = (c >> 1) == 8 * k + 4 * half + e ? ((c & 1) ? 0x3f800000u : 0x00003f80u) : 0u;
+      eye[k] = __builtin_bit_cast(bf16x8, d);
+    }
+    u32x4 piece[2];
+    const int s0 = 2 * (threadIdx.x >> 6);  // this wave's first K step of the tile
 #pragma unroll
     for (int st = 0; st < kTileQ / 16; ++st) {  // 16 samples per round: blocks 2 st (lanes < 32), 2 st + 1
       const int nb = 2 * st + half;
       const int P = nb * W + f;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(stage + (P ^ ((P >> 4) & 7)) * 16);
+      if (st % 2 == 0) {  // the next 32 samples: lane (m, half) reads sample m's features 8 half + e of each step
+        const int n = 16 * st + c;
+        f32x16 z;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) z[j] = 0.f;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const u32x4 x = n < nvalid ? *reinterpret_cast<const u32x4*>(act + (s0 + k) * Geo<W, MODE>::STEP_BYTES +
+                                                                       half * 16 * kTileQ + n * 16)
+                                     : u32x4{0u, 0u, 0u, 0u};
+          z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), eye[k], z, 0, 0, 0);
+        }
+        // lane (c, half): feature c, samples 8 g + 4 half + r of the 32 in z[4 g + r]
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          uint32_t p[4];  // samples (0 1), (2 3) of g = 2 t, then of g = 2 t + 1
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            p[q] = __builtin_amdgcn_perm(__float_as_uint(z[8 * t + 2 * q + 1]), __float_as_uint(z[8 * t + 2 * q]), 0x07060302u);
+          const auto x0 = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
+          const auto x1 = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
+          piece[t] = u32x4{x0[0], x1[0], x0[1], x1[1]};
+        }
+      }
+      const u32x4 v = piece[st % 2];
       if (store) *reinterpret_cast<u32x4*>(o + P * 8) = v;
       if (sums) {
-        const int n0 = nb * 8;  // word w: samples n0 + 2w (low half), n0 + 2w + 1
+        // the pieces are the B fragments (8 samples of feature f) of a product over
+        // samples: row c of A holds what column sums are wanted of
+        const int n0 = nb * 8;
+        bf16x8 ah, al;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const uint32_t word = v[e >> 1];
-          const float x = __uint_as_float((e & 1) ? (word & 0xffff0000u) : (word << 16));
-          part += sums->seed ? x * sums->seed[(n0 + e) * XF] : x;
-        }
+        for (int e = 0; e < 8; ++e) ah[e] = al[e] = (__bf16)0.f;
         if (sums->in_rows) {
-          // A: 8 samples of feature f (lane = (f % 32, half)); B: v_c of the same 8
-          // samples (lane = (c, half)), hi then lo
-          const bf16x8 a = __builtin_bit_cast(bf16x8, v);
-          bf16x8 bh, bl;
           if (c < 9) {
-            bh = *reinterpret_cast<const bf16x8*>(sums->vt + c * kTileQ + n0);
-            bl = *reinterpret_cast<const bf16x8*>(sums->vt + (9 + c) * kTileQ + n0);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) bh[e] = bl[e] = (__bf16)0.f;
+            ah = *reinterpret_cast<const bf16x8*>(sums->vt + c * kTileQ + n0);
+            al = *reinterpret_cast<const bf16x8*>(sums->vt + (9 + c) * kTileQ + n0);
           }
-          dacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bh, dacc, 0, 0, 0);
-          dacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bl, dacc, 0, 0, 0);
+        } else if (sums->seed) {
+          if (c < 3) ah = *reinterpret_cast<const bf16x8*>(sums->vt + (kVtSeed + c) * kTileQ + n0);
         }
+        if (!sums->seed && c == (sums->in_rows ? 9 : 0)) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ah[e] = (__bf16)1.f;
+        }
+        dacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, __builtin_bit_cast(bf16x8, v), dacc, 0, 0, 0);
+        if (sums->in_rows)
+          dacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, __builtin_bit_cast(bf16x8, v), dacc, 0, 0, 0);
       }
     }
     if (sums) {
-      part += __shfl_xor(part, 32);
-      if (half == 0) sums->row[f] += part;
-      if (sums->in_rows && c < 9) {
-        // C layout: lane (c, half) holds rows 8 (j/4) + 4 half + j%4 of the wave's 32 features
-        float* r = sums->in_rows + c * W + 32 * (threadIdx.x >> 6);
+      // lane (feature f % 32, half) holds rows 8 (j/4) + 4 half + j%4
+      if (sums->in_rows) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) r[8 * (j >> 2) + 4 * half + (j & 3)] += dacc[j];
+        for (int j = 0; j < 4; ++j) sums->in_rows[(4 * half + j) * W + f] += dacc[j];
+        if (half == 0) {
+          sums->in_rows[8 * W + f] += dacc[4];
+          sums->row[f] += dacc[5];
+        }
+      } else if (half == 0) {
+        sums->row[f] += sums->seed ? dacc[2] + dacc[1] + dacc[0] : dacc[0];
       }
     }
   }
@@ -842,7 +856,6 @@ struct View {
 // Dump of the current LDS tile for training (no-op when not training).
 struct TileDump {
   const char* act;  // the LDS activation tile
-  char* stage;      // BF16: LDS staging of a dump (the tile's idle half)
   void* H;
   void* G;
   int64_t ldb, q0;
@@ -863,7 +876,7 @@ struct TileDump {
   // 5..13 dW1[:, c] = sum_i g1_i v_c(i), row 14 (first entry) db_out = sum_i seed_i,
   // row 15 (first entry) the fused loss sum_i (d_i - target_i)^2 / B
   float* bsum;
-  __bf16* vt;  // with bsum: the tile's network inputs, transposed, BF16 hi [9][64] then lo
+  __bf16* vt;  // with bsum: the tile's network inputs, transposed (DumpSums::vt)
   float* sp1;  // BF16: SiLU'(z1) of the input layer kept in LDS for the reverse sweep (see train_sp1)
   int width;
   __device__ __forceinline__ float* row(int r) const { return bsum + r * width; }
@@ -922,7 +935,9 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
 #pragma unroll
         for (int r = 0; r < 4; ++r) acc[i][nt][4 * g + r] = b4[r];
     }
-  layer_gemm<W, MODE, CB, fwd_arith<MODE>()>(acc, net.fwd[L], L < 2 ? net.fwd[L + 1] : net.bwd[2], v0.b.voff, v0.ln.act_r, ap);
+  const void* next = L < 2 ? net.fwd[L + 1] : net.bwd[2];
+  layer_gemm<W, MODE, CB, fwd_arith<MODE>()>(acc, net.fwd[L], next, v0.b.voff,
+                                             v0.ln.act_r, ap);
   const View<W, MODE, CB> vw(tc);
   const Lane<W, MODE, CB>& ln = vw.ln;
   const Bases<W, MODE, CB>& b = vw.b;
@@ -982,6 +997,15 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
         *seedp = seed;
         if (valid && td.d_out) td.d_out[q] = dv;
       }
+      if constexpr (MODE == kBF16) {  // the seeds' parts for the sums over h4
+        const float sd = *seedp;
+        const __bf16 hi = (__bf16)sd;
+        const float r1 = sd - (float)hi;
+        const __bf16 mid = (__bf16)r1;
+        td.vt[kVtSeed * kTileQ + n] = hi;
+        td.vt[(kVtSeed + 1) * kTileQ + n] = mid;
+        td.vt[(kVtSeed + 2) * kTileQ + n] = (__bf16)(r1 - (float)mid);
+      }
       {
         // db_out = sum_i seed_i and the loss, over the tile (fixed butterfly), then
         // over this workgroup's tiles in order
@@ -1001,7 +1025,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
     // barrier: wave 0 wrote the seeds the copy reads)
     __syncthreads();
     const DumpSums sm{td.row(4), td.xin + 11, nullptr, td.vt, nullptr, 0, 0};
-    dump_tile<W, MODE>(td.act, td.stage, td.h(3), td.ldb, td.q0, td.nvalid, &sm, false);
+    dump_tile<W, MODE>(td.act, td.h(3), td.ldb, td.q0, td.nvalid, &sm, false);
     __syncthreads();  // h4 fully read before g4 overwrites the tile; seeds written
   }
   static_for<MT>([&](auto I) {
@@ -1064,7 +1088,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
   // overwritten only after the following K loop and its barrier
   if constexpr (TRAIN) {  // h2, h3, or g4 (with db4 = sum_i g4_i)
     const DumpSums sm{td.row(3), nullptr, nullptr, td.vt, nullptr, 0, 0};
-    dump_tile<W, MODE>(td.act, td.stage, L < 2 ? td.h(L + 1) : td.g(3), td.ldb, td.q0, td.nvalid, L == 2 ? &sm : nullptr);
+    dump_tile<W, MODE>(td.act, L < 2 ? td.h(L + 1) : td.g(3), td.ldb, td.q0, td.nvalid, L == 2 ? &sm : nullptr);
   }
 }
 
@@ -1082,7 +1106,8 @@ __device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, M
   const View<W, MODE, CB> v0(tc);
   const char* br = (PP && L == 1) ? v0.ln.act_r + Geo<W, MODE, CB>::LO_OFF : v0.ln.act_r;
   if constexpr (!rev_zero_c<MODE>()) zero_acc<W, MODE, CB>(acc);
-  layer_gemm<W, MODE, CB, RA, rev_zero_c<MODE>()>(acc, net.bwd[L], net.bwd[L - 1], v0.b.voff, br, ap);
+  layer_gemm<W, MODE, CB, RA, rev_zero_c<MODE>()>(acc, net.bwd[L], net.bwd[L - 1], v0.b.voff,
+                                                  br, ap);
   const View<W, MODE, CB> vw(tc);
   const Lane<W, MODE, CB>& ln = vw.ln;
   constexpr bool DEFER = !PP && defer_stores<W, MODE, CB, TRAIN>(false);  // as in fwd_hidden
@@ -1119,7 +1144,7 @@ __device__ __forceinline__ void bwd_hidden(const DevNet& net, const TileCtx<W, M
   __syncthreads();
   if constexpr (TRAIN) {  // g3 or g2, with their bias sums
     const DumpSums sm{td.row(L), nullptr, nullptr, td.vt, nullptr, 0, 0};
-    dump_tile<W, MODE>(td.act, td.stage, td.g(L), td.ldb, td.q0, td.nvalid, &sm);
+    dump_tile<W, MODE>(td.act, td.g(L), td.ldb, td.q0, td.nvalid, &sm);
   }
 }
 
@@ -1325,7 +1350,7 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
     before_copy();
     // g1 is needed only for db1 and dW1 = sum_i g1_i v_i^T, summed here
     const DumpSums sm{td.row(0), nullptr, td.row(5), td.vt, td.xin, Geo<W, MODE>::XIN_FLOATS, 2};
-    dump_tile<W, MODE>(td.act, td.stage, td.g(0), td.ldb, td.q0, td.nvalid, &sm, false);
+    dump_tile<W, MODE>(td.act, td.g(0), td.ldb, td.q0, td.nvalid, &sm, false);
   }
 }
 
@@ -1391,7 +1416,7 @@ __device__ __forceinline__ void fwd_input(const TileCtx<W, MODE, CB>& tc, const 
 template <int W, int MODE>
 constexpr int train_extra_lds() {
   return Geo<W, MODE>::NW * kTileQ * 4 +
-         (MODE == kBF16 ? kTrainSumRows * W * 4 + 2 * 9 * kTileQ * 2 + W * kTileQ * 4 : 0);
+         (MODE == kBF16 ? kTrainSumRows * W * 4 + kVtRows * kTileQ * 2 + W * kTileQ * 4 : 0);
 }
 template <int W, int MODE>
 __device__ __forceinline__ float* train_bsum(char* lds) {
@@ -1408,7 +1433,7 @@ __device__ __forceinline__ __bf16* train_vt(char* lds) {
 // group k of thread t at float (k THREADS + t) 4), so no barrier orders them.
 template <int W, int MODE>
 __device__ __forceinline__ float* train_sp1(char* lds) {
-  if constexpr (MODE == kBF16) return reinterpret_cast<float*>(train_vt<W, MODE>(lds) + 2 * 9 * kTileQ);
+  if constexpr (MODE == kBF16) return reinterpret_cast<float*>(train_vt<W, MODE>(lds) + kVtRows * kTileQ);
   return nullptr;
 }
 
@@ -1601,9 +1626,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
     td.nvalid = (int)(qlimit - q0 < TQ ? qlimit - q0 : TQ);
     td.layer_elems = (size_t)W * job.ldb;
     td.elem_bytes = MODE == kFP32 ? 4 : 2;
-    // LDS beyond the query's own: the fused loss's partial sums ([waves][64]); the
-    // idle half of a pure-BF16 tile stages the dumps
-    td.stage = tc.act + G::ACT_BYTES / 2;
+    // LDS beyond the query's own: the fused loss's partial sums ([waves][64])
     td.dred = reinterpret_cast<float*>(tc.act + G::LDS_BYTES);
     td.bsum = MODE == kBF16 ? train_bsum<W, MODE>(tc.act) : job.bias_part + (int64_t)blockIdx.x * kTrainSumRows * W;
     td.vt = train_vt<W, MODE>(tc.act);
@@ -1621,7 +1644,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
   fwd_input<W, MODE, CB, PAIRS, SPH, TRAIN && MODE == kBF16>(tc, tc.act + G::ACT_BYTES / 2, td.sp1);
   __syncthreads();
   if constexpr (TRAIN) {
-    dump_tile<W, MODE>(td.act, td.stage, td.h(0), td.ldb, td.q0, td.nvalid);  // h1
+    dump_tile<W, MODE>(td.act, td.h(0), td.ldb, td.q0, td.nvalid);  // h1
   }
 
   // ---- hidden layers 2..4 (forward), keeping SiLU' of layers 2 and 3 ----

@@ -381,3 +381,33 @@ def test_packed_weights_reused_only_when_unchanged(tr_mod):
     fresh = tr_mod.Trainer(256, "fp32", max_batch=1000)
     want = fresh.backward(a.detach(), kt, pt, gd)
     assert torch.equal(a.grad, want)
+
+
+@pytest.mark.parametrize("B", [1, 7, 31, 33, 64, 65])
+def test_bf16_batch_gradient_is_the_sum_of_its_samples(tr_mod, B):
+    """A sample's BF16 activations and back-propagated values do not depend on its
+    neighbours, so a batch's gradient is the sum of its samples' own up to the FP32
+    summation: at most B + 32 roundings of each term, doubled for the matrix cores'
+    own alignment of products.  A value of another sample or feature (a wrong block of
+    the transposed dumps, a row sum over the wrong lanes, a seed's lost bits) is off by
+    far more.  The seeds use all 24 bits and span four decades."""
+    w = wl.weights(256, seed=46, bf16_hidden=False)
+    k, p, _ = batch(65, 21)
+    rng = np.random.default_rng(47)
+    seeds = (rng.normal(0, 1, 65) * 10.0 ** rng.uniform(-3, 1, 65)).astype(np.float32)
+    print("case sum of samples B=%d" % B, flush=True)
+    trainer = tr_mod.Trainer(256, "bf16", max_batch=65)
+    params = tr_mod.flat_params(w)
+    kt, pt, st = torch.from_numpy(k).cuda(), torch.from_numpy(p).cuda(), torch.from_numpy(seeds).cuda()
+
+    def grad(sel):
+        ks, ps, ss = kt[sel].contiguous(), pt[sel].contiguous(), st[sel].contiguous()
+        trainer.forward(params, ks, ps)
+        return trainer.backward(params, ks, ps, ss).double().cpu().numpy()
+
+    g = grad(slice(0, B))
+    one = np.stack([grad(slice(i, i + 1)) for i in range(B)])
+    bound = 2 * (B + 32) * 2.0 ** -24 * np.abs(one).sum(0) + 1e-30
+    off = np.abs(g - one.sum(0)) / bound
+    print("largest error / bound %.3f" % off.max(), flush=True)
+    assert np.all(np.isfinite(g)) and off.max() <= 1.0
