@@ -601,11 +601,16 @@ __device__ __forceinline__ void minkey_decode(unsigned long long stored, float& 
 // matrix cores, with the pieces as B fragments (the seeds in three BF16 parts, which
 // hold all 24 bits; v in BF16 hi + lo).  store false: the sums only, nothing written
 // to HBM.
-// FP32, with sums: the same sums, thread f those of feature f, sample by sample on the
-// vector ALU (a few hundred FMAs against a tile's 100,000 cycles), added to the
-// workgroup's rows in global memory (each entry has one thread, so program order is
+// FP32, with sums: the same sums, thread f those of feature f: row sums sample by
+// sample on the vector ALU, those with the inputs four at a time by v_mfma_f32_4x4x1_16b_f32, whose
+// 16 blocks take a wave's 64 features as columns (the vector ALU read every input of
+// every sample by a load of its own: 20 us of a step of 734 at batch 65,536).  They go to
+// the workgroup's rows in global memory (each entry has one thread, so program order is
 // the order of the sum).  They replaced passes over the dumps that read 64 to 320 MB
-// back (batch 65,536) or ran on ten workgroups (batch 5,001: 42 us).
+// back (batch 65,536) or ran on ten workgroups (batch 5,001: 42 us).  The copy is short
+// of instruction cache, not of LDS: four blocks of samples per trip cost 20 us a step
+// more than two, all sixteen 190; lanes starting at different samples, which removes its
+// 8-way bank conflicts, 20.  With both changes 734 -> 723 us (batch 5,001: 153.6 -> 150.5).
 // ----------------------------------------------------------------------------
 constexpr int kVtSeed = 18, kVtRows = 21;  // rows of the transposed inputs (DumpSums::vt)
 struct DumpSums {
@@ -628,30 +633,45 @@ __device__ __forceinline__ void dump_tile(const char* act, void* dst, int64_t ld
     const int f = threadIdx.x;
     const float* a = reinterpret_cast<const float*>(act) + (((f >> 3) * kTileQ) * 2 + (f & 1)) * 4 + ((f & 7) >> 1);
     const bool row = sums && sums->row, in = sums && sums->in_rows;
-    float s = 0.f, sv[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int n = 0; n < kTileQ; n += 4) {
-      f32x4 v;
+    float s = 0.f;
+    f32x4 sv[3];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = n + u < nvalid ? a[(n + u) * 8] : 0.f;
-      if (store) *reinterpret_cast<f32x4*>(static_cast<float*>(dst) + (((q0 + n) >> 2) * W + f) * 4) = v;
-      if (row) {
+    for (int j = 0; j < 3; ++j) sv[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the field of a sample's record that this lane's row 4 j + lane % 4 of the input
+    // sums takes (rows 9..11: any)
+    int xo[3];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) s += sums->seed ? v[u] * sums->seed[(n + u) * XF] : v[u];
-      }
-      if (in) {
+    for (int j = 0; j < 3; ++j) {
+      const int c = 4 * j + (int)(threadIdx.x & 3);
+      xo[j] = c < 3 ? c : c < 9 ? c + (sums ? sums->in_gap : 0) : 0;
+    }
+    auto copy = [&](auto FULL) {
+#pragma unroll 2
+      for (int n = 0; n < kTileQ; n += 4) {
+        f32x4 v;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const float* x = sums->in + (n + u) * sums->in_stride;
+        for (int u = 0; u < 4; ++u) v[u] = FULL || n + u < nvalid ? a[(n + u) * 8] : 0.f;
+        if (store) *reinterpret_cast<f32x4*>(static_cast<float*>(dst) + (((q0 + n) >> 2) * W + f) * 4) = v;
+        if (row) {
 #pragma unroll
-          for (int c = 0; c < 9; ++c) sv[c] += v[u] * x[c < 3 ? c : c + sums->in_gap];
+          for (int u = 0; u < 4; ++u) s += sums->seed ? v[u] * sums->seed[(n + u) * XF] : v[u];
+        }
+        if (in) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const float* x = sums->in + (n + u) * sums->in_stride;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) sv[j] = __builtin_amdgcn_mfma_f32_4x4x1f32(x[xo[j]], v[u], sv[j], 0, 0, 0);
+          }
         }
       }
-    }
+    };
+    if (nvalid == kTileQ) copy(std::integral_constant<bool, true>{});
+    else copy(std::integral_constant<bool, false>{});
     if (row) sums->row[f] += s;
     if (in) {
 #pragma unroll
-      for (int c = 0; c < 9; ++c) sums->in_rows[c * W + f] += sv[c];
+      for (int c = 0; c < 9; ++c) sums->in_rows[c * W + f] += sv[c >> 2][c & 3];
     }
   }
   if constexpr (MODE != kFP32) {
