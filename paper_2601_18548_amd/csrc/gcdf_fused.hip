@@ -721,6 +721,7 @@ hipError_t launch_minkey_decode(unsigned long long* minkey, int64_t K, float* dm
 hipError_t launch_fused(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s) {
   if (net.in_dim == kInDimSphere) return launch_fused_sphere(net, job, pairs, want_grad, num_cu, s);
   if (narrow_tiles(job, pairs, num_cu)) return launch_fused_narrow(net, job, pairs, want_grad, num_cu, s);
+  if (one_round(net, job, pairs, num_cu)) return launch_fused_one_round(net, job, pairs, want_grad, num_cu, s);
   if (net.width == 256) return launch_w<256, 2, false>(net, job, pairs, want_grad, num_cu, s);
   return launch_w<512, 2, false>(net, job, pairs, want_grad, num_cu, s);
 }

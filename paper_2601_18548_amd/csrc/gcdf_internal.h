@@ -166,6 +166,17 @@ inline bool narrow_tiles(const Job& job, bool pairs, int num_cu) {
   return narrow_tiles(query_tiles(job, pairs, kTileQ / 2), num_cu);
 }
 
+// Whether a query job in 64-query tiles of width 256 in a split mode runs as one 8-wave
+// workgroup per compute unit instead of two 4-wave ones: when each tile has a compute
+// unit to itself, so that the second workgroup would have nothing to do and 8 waves
+// share the tile's layers (us a call, two 4-wave / one 8-wave, BF16X2_F16: 200 x 64 with
+// J 27.7 / 24.5, values 17.0 / 15.2; 250 x 64 with J 30.2 / 27.3; one tile past a round,
+// 257 x 64, 35.6 / 44.1, values 23.0 / 26.5).
+inline bool one_round(const DevNet& net, const Job& job, bool pairs, int num_cu) {
+  return net.width == 256 && (net.mode == kBF16X2 || net.mode == kBF16X2F16) && !job.dumpH &&
+         query_tiles(job, pairs, kTileQ) <= num_cu;
+}
+
 // Launch the fused query kernel (dense all-pairs if !pairs, else the pair list).
 hipError_t launch_fused(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s);
 // The same for a sphere network (net.in_dim == 10; points hold (x, y, z, r)); no training.
@@ -175,6 +186,11 @@ hipError_t launch_fused_sphere(const DevNet& net, const Job& job, bool pairs, bo
 hipError_t launch_fused_narrow(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s);
 hipError_t launch_fused_sphere_narrow(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu,
                                       hipStream_t s);
+
+// The 8-wave workgroups of one_round.
+hipError_t launch_fused_one_round(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu, hipStream_t s);
+hipError_t launch_fused_sphere_one_round(const DevNet& net, const Job& job, bool pairs, bool want_grad, int num_cu,
+                                         hipStream_t s);
 
 // Decode keys into dmin / argmin and set them back to zero.
 hipError_t launch_minkey_decode(unsigned long long* minkey, int64_t K, float* dmin, int32_t* argmin, hipStream_t s);

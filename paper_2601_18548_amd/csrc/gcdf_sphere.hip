@@ -9,6 +9,7 @@ hipError_t launch_fused_sphere(const DevNet& net, const Job& job, bool pairs, bo
                                hipStream_t s) {
   if (job.dumpH || job.seed) return hipErrorInvalidValue;  // training takes point networks only
   if (narrow_tiles(job, pairs, num_cu)) return launch_fused_sphere_narrow(net, job, pairs, want_grad, num_cu, s);
+  if (one_round(net, job, pairs, num_cu)) return launch_fused_sphere_one_round(net, job, pairs, want_grad, num_cu, s);
   if (net.width == 256) return launch_w<256, 2, true>(net, job, pairs, want_grad, num_cu, s);
   return launch_w<512, 2, true>(net, job, pairs, want_grad, num_cu, s);
 }

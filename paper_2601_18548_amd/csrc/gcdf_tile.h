@@ -50,7 +50,17 @@
 
 #include "gcdf_internal.h"
 
+// Waves per workgroup of the split modes at width 256: 4, with two workgroups on a
+// compute unit, but 8 in the source for launches of one round (see one_round), which
+// keeps its instantiations apart in an inline namespace.
+#ifdef GCDF_ONE_ROUND
 namespace gcdf {
+inline namespace one_round_tiles {
+constexpr int kSplitWaves256 = 8;
+#else
+namespace gcdf {
+constexpr int kSplitWaves256 = 4;
+#endif
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
@@ -127,7 +137,7 @@ constexpr int kXinTarget = 13;  // training with the fused loss: the sample's ta
 // room for a second workgroup); 4 otherwise.
 template <int W, int MODE>
 constexpr int waves_for() {
-  return MODE != kFP32 && (W == 512 || MODE == kBF16) ? 8 : 4;
+  return MODE == kFP32 ? 4 : W == 512 || MODE == kBF16 ? 8 : kSplitWaves256;
 }
 
 // Arithmetic of one K loop and of the LDS stores that feed it.  Every mode
@@ -168,10 +178,10 @@ struct Geo {
   static constexpr int TQ = 32 * CB;                 // queries per tile
   static constexpr int NW = CB == 1 && MODE != kFP32 ? 8 : waves_for<W, MODE>();  // waves per workgroup
   static constexpr bool SHORT_STEPS = CB == 1 && MODE != kFP32;
-  // (Pure BF16 at W=256 is in the same place: one product per fragment and 8 waves, so
-  // two K steps are 64 cycles of a SIMD.  BF16 training, batch 65,536: 180 us a step
+  // (8 waves at W=256 are in the same place: in pure BF16, one product per fragment, two
+  // K steps are 64 cycles of a SIMD.  BF16 training, batch 65,536: 180 us a step
   // with AR = 2, 167 with 4, the same with longer rings of B.)
-  static constexpr int AR = SHORT_STEPS ? (W == 256 ? 8 : 4) : W == 256 && MODE == kBF16 ? 4 : 2;  // K steps of A in flight
+  static constexpr int AR = SHORT_STEPS ? (W == 256 ? 8 : 4) : W == 256 && NW == 8 ? 4 : 2;  // K steps of A in flight
   static constexpr int BR = SHORT_STEPS && W == 256 ? 4 : 2;  // K steps of B, the current one included
   static constexpr int THREADS = 64 * NW;
   static constexpr int MT = W / (32 * NW);           // 32-row M tiles per wave
@@ -1868,7 +1878,7 @@ __global__ __launch_bounds__((Geo<W, MODE, CB>::THREADS), WPE) void fused_query(
 }
 
 // ----------------------------------------------------------------------------
-// Host-side launchers of fused_query (grid = min(tiles, CUs)); each source file
+// Host-side launchers of fused_query (grid = min(tiles, workgroups that fit)); each source file
 // instantiates the obstacle kind (SPH) it serves.
 // ----------------------------------------------------------------------------
 template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool SPH>
@@ -1924,4 +1934,7 @@ static hipError_t launch_w(const DevNet& net, const Job& job, bool pairs, bool w
   }
 }
 
+#ifdef GCDF_ONE_ROUND
+}  // inline namespace one_round_tiles
+#endif
 }  // namespace gcdf

@@ -91,3 +91,29 @@ def test_narrow_pair_lists_match_the_training_tiles(gcdf, precision, B):
     torch.cuda.synchronize()
     assert torch.equal(d, d2)
     tr.close()
+
+
+@pytest.mark.parametrize("spheres", [False, True])
+@pytest.mark.parametrize("precision", ["bf16x2", "bf16x2_f16"])
+def test_one_round_workgroups_match_larger_launches(gcdf, precision, spheres):
+    """Width 256, split modes: launches of up to one 64-query tile per compute unit (129
+    to 256 of them here) run 8-wave workgroups, larger ones two 4-wave ones per compute
+    unit.  The sums' order does not depend on the waves, so the bits agree."""
+    w = wl.weights(256, 3, in_dim=wl.IN_DIM_SPHERE if spheres else wl.IN_DIM)
+    p = wl.spheres(20000, 5) if spheres else wl.points_patches(20000, 5)
+    ctx = gcdf.Context(w.to_blob(), 256, precision)
+    kt, pt = torch.from_numpy(wl.knots(3, 4)).cuda(), torch.from_numpy(p).cuda()
+    dw, Jw = ctx.eval_grad(kt, pt)
+    for Np in (2753, 3841, 5408, 5440):
+        print("one round %s spheres=%d Np=%d" % (precision, spheres, Np), flush=True)
+        pn = pt[:Np].contiguous()
+        d, J = ctx.eval_grad(kt, pn)
+        assert torch.equal(d, dw[:, :Np]) and torch.equal(J, Jw[:, :Np])
+        assert torch.equal(ctx.eval(kt, pn), d)
+        dmin, am, Jm = ctx.knot_min(kt, pn, with_jacobian=True)
+        assert torch.equal(dmin, d.min(dim=1).values)
+        assert torch.equal(Jm, J[torch.arange(3, device="cuda"), am.long()])
+    off, idx = ctx.partition(kt, pt[:5000].contiguous(), 1e3)  # every point in range: 237 gathered tiles at most
+    c, Jc = ctx.eval_grad_csr(kt, pt[:5000].contiguous(), off, idx)
+    assert torch.equal(c, dw[:, :5000].reshape(-1)) and torch.equal(Jc, Jw[:, :5000].reshape(-1, 9))
+    ctx.close()
