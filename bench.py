@@ -110,7 +110,7 @@ def write_traffic_record(fetch_dir, write_dir, cal_fetch_dir, cal_write_dir, wid
     """HBM bytes per launch of the benchmark's fused kernel: FETCH_SIZE and
     WRITE_SIZE (KiB per dispatch) scaled by what they read for 5 plain copies of
     1 GiB, keyed to the kernel code they were taken on."""
-    kern = "void gcdf::fused_query<%d, %d, false, 1, false, false, false>" % (width, {"bf16x2_f16": 3, "bf16x2": 2}[precision])
+    kern = "void gcdf::fused_query<%d, %d, 2, true, false, false, false, false, 2>" % (width, {"bf16x2_f16": 3, "bf16x2": 2}[precision])
     fetch = _pmc_per_dispatch(fetch_dir, "FETCH_SIZE", kern)
     write = _pmc_per_dispatch(write_dir, "WRITE_SIZE", kern)
     cf = _pmc_per_dispatch(cal_fetch_dir, "FETCH_SIZE", "__amd_rocclr_copyBuffer")
