@@ -100,16 +100,19 @@ __global__ __launch_bounds__(kPartThreads) void partition_scan_kernel(int64_t* _
   }
 }
 
-// One workgroup per partition, rounds of kPartThreads * kFillPerThread points in
-// ascending order; inside a round point j = j0 + u * 256 + wave * 64 + lane, ranked
-// by (u, wave, lane) with ballots, so the indices come out ascending.
-template <bool SPH>
-__global__ __launch_bounds__(kPartThreads) void partition_fill_kernel(const float* __restrict__ ref, int64_t ref_stride,
-                                                                      const float* __restrict__ points, int64_t M,
-                                                                      float radius, const int64_t* __restrict__ offsets,
-                                                                      int32_t* __restrict__ idx, int64_t capacity) {
-  constexpr int kW = kPartThreads / 64;
-  __shared__ int wcnt[2][kFillPerThread][kW];
+// One workgroup of T threads per partition, rounds of T * kFillPerThread points in
+// ascending order; inside a round point j = j0 + u T + wave * 64 + lane, ranked by
+// (u, wave, lane) with ballots, so the indices come out ascending.  The counts of a
+// round's (u, wave) slots, at most 64, are scanned by every wave for itself, one a
+// lane.  A round is a chain of latencies (points, LDS, barrier): see fill_wide.
+template <bool SPH, int T>
+__global__ __launch_bounds__(T) void partition_fill_kernel(const float* __restrict__ ref, int64_t ref_stride,
+                                                           const float* __restrict__ points, int64_t M, float radius,
+                                                           const int64_t* __restrict__ offsets,
+                                                           int32_t* __restrict__ idx, int64_t capacity) {
+  constexpr int kW = T / 64, kCounts = kFillPerThread * kW;
+  static_assert(kCounts <= 64, "a lane per (slot, wave) count");
+  __shared__ int wcnt[2][kCounts];
   const int64_t i = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const float rx = ref[i * ref_stride], ry = ref[i * ref_stride + 1], r2 = squared(radius);
@@ -117,37 +120,38 @@ __global__ __launch_bounds__(kPartThreads) void partition_fill_kernel(const floa
   const uint64_t below = lane ? (~0ull >> (64 - lane)) : 0ull;
   int64_t run = 0;
   int buf = 0;
-  for (int64_t j0 = 0; j0 < M; j0 += kPartThreads * kFillPerThread, buf ^= 1) {
+  for (int64_t j0 = 0; j0 < M; j0 += T * kFillPerThread, buf ^= 1) {
     bool in[kFillPerThread];
-    int rank[kFillPerThread];
+    int rank[kFillPerThread], cnt[kFillPerThread];
 #pragma unroll
     for (int u = 0; u < kFillPerThread; ++u) {
-      const int64_t j = j0 + u * kPartThreads + threadIdx.x;
-      in[u] = j < M && in_range<SPH>(points, j, rx, ry, radius, r2);
+      const int64_t j = j0 + u * T + threadIdx.x;
+      // (the last point stands in past the end, so that no load waits for a branch)
+      in[u] = in_range<SPH>(points, j < M ? j : M - 1, rx, ry, radius, r2) & (j < M);
+    }
+#pragma unroll
+    for (int u = 0; u < kFillPerThread; ++u) {
       const uint64_t m = __ballot(in[u]);
       rank[u] = __popcll(m & below);
-      if (lane == 0) wcnt[buf][u][wave] = __popcll(m);
+      cnt[u] = __popcll(m);
+      if (lane == 0) wcnt[buf][u * kW + wave] = cnt[u];
     }
     __syncthreads();
-    int total = 0;
+    int scan = lane < kCounts ? wcnt[buf][lane] : 0;  // members of the round up to and with each (slot, wave)
 #pragma unroll
-    for (int u = 0; u < kFillPerThread; ++u)
-#pragma unroll
-      for (int w = 0; w < kW; ++w) total += wcnt[buf][u][w];
+    for (int o = 1; o < kCounts; o <<= 1) {
+      const int add = __shfl_up(scan, o);
+      if (lane >= o) scan += add;
+    }
 #pragma unroll
     for (int u = 0; u < kFillPerThread; ++u) {
-      int off = 0;  // members of this round ranked before (u, wave)
-#pragma unroll
-      for (int uu = 0; uu < kFillPerThread; ++uu)
-#pragma unroll
-        for (int w = 0; w < kW; ++w)
-          if (uu < u || (uu == u && w < wave)) off += wcnt[buf][uu][w];
+      const int off = __shfl(scan, u * kW + wave) - cnt[u];  // members of this round ranked before (u, wave)
       if (in[u]) {
         const int64_t pos = base + run + off + rank[u];
-        if (pos < capacity) idx[pos] = (int32_t)(j0 + u * kPartThreads + threadIdx.x);
+        if (pos < capacity) idx[pos] = (int32_t)(j0 + u * T + threadIdx.x);
       }
     }
-    run += total;
+    run += __shfl(scan, kCounts - 1);
     // wcnt[buf] is rewritten two rounds later, after the next round's barrier
   }
 }
@@ -302,15 +306,32 @@ hipError_t launch_partition_count(const float* ref, int64_t N, int64_t ref_strid
   return hipGetLastError();
 }
 
+// Threads of a partition's workgroup in the fill pass: 1,024 where all partitions'
+// workgroups are resident at once (two such on each of 256 compute units) and have more
+// than one round of 256 threads to do, so that four times fewer rounds follow each other
+// (128 partitions of 16,384 points: 27 us with 256 threads, 8.4 with 1,024); else 256,
+// which leave no threads idle on small sets (a build of 20,000 partitions of 1,024
+// points: 154 us, 208 with 1,024 threads).
+static bool fill_wide(int64_t N, int64_t M) { return N <= 512 && M > kPartThreads * kFillPerThread; }
+
+template <bool SPH, int T>
+static void fill(const float* ref, int64_t N, int64_t ref_stride, const float* points, int64_t M, float radius,
+                 const int64_t* offsets, int32_t* idx, int64_t capacity, hipStream_t s) {
+  hipLaunchKernelGGL((partition_fill_kernel<SPH, T>), dim3((unsigned)N), dim3(T), 0, s, ref, ref_stride, points, M,
+                     radius, offsets, idx, capacity);
+}
+
 hipError_t launch_partition_fill(const float* ref, int64_t N, int64_t ref_stride, const float* points, int64_t M,
                                  bool spheres, float radius, const int64_t* offsets, int32_t* idx, int64_t capacity,
                                  hipStream_t s) {
-  if (spheres)
-    hipLaunchKernelGGL(partition_fill_kernel<true>, dim3((unsigned)N), dim3(kPartThreads), 0, s, ref, ref_stride,
-                       points, M, radius, offsets, idx, capacity);
-  else
-    hipLaunchKernelGGL(partition_fill_kernel<false>, dim3((unsigned)N), dim3(kPartThreads), 0, s, ref, ref_stride,
-                       points, M, radius, offsets, idx, capacity);
+  constexpr int kWide = 4 * kPartThreads;
+  if (fill_wide(N, M)) {
+    if (spheres) fill<true, kWide>(ref, N, ref_stride, points, M, radius, offsets, idx, capacity, s);
+    else fill<false, kWide>(ref, N, ref_stride, points, M, radius, offsets, idx, capacity, s);
+  } else {
+    if (spheres) fill<true, kPartThreads>(ref, N, ref_stride, points, M, radius, offsets, idx, capacity, s);
+    else fill<false, kPartThreads>(ref, N, ref_stride, points, M, radius, offsets, idx, capacity, s);
+  }
   return hipGetLastError();
 }
 

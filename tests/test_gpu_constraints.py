@@ -260,3 +260,22 @@ def test_projection_argument_errors(gcdf, weights):
     assert lib.gcdf_project(ctx._h, k.data_ptr(), 2, 3, d.data_ptr(), J.data_ptr(), m, None, None, None) == gcdf.EINVAL
     assert lib.gcdf_project(ctx._h, k.data_ptr(), 0, 3, d.data_ptr(), J.data_ptr(), m, out.data_ptr(), None,
                             None) == gcdf.EINVAL
+
+
+@pytest.mark.parametrize("N,M", [(1, 1024), (3, 1025), (3, 4095), (3, 4096), (3, 4097), (512, 2500), (513, 2500)])
+def test_partition_rounds_match_numpy(N, M):
+    """The fill pass's rounds (1,024 points, or 4,096 for few partitions of more than
+    1,024 points) against a plain scan in the same FP32 arithmetic: whole numbers, equal."""
+    import paper_2601_18548_amd as g
+
+    w = wl.weights(256, 3)
+    ctx = g.Context(w.to_blob(), 256, "bf16x2_f16")
+    k, p = wl.trajectory(max(N, 2), 1)[:N].copy(), wl.points_patches(M, 2)
+    radius = np.float32(1.5)
+    off, idx = (t.cpu().numpy() for t in ctx.partition(torch.from_numpy(k).cuda(), torch.from_numpy(p).cuda(), float(radius)))
+    dx, dy = p[None, :, 0] - k[:, None, 0], p[None, :, 1] - k[:, None, 1]
+    inside = dx * dx + dy * dy <= radius * radius
+    assert inside.dtype == bool and dx.dtype == np.float32
+    np.testing.assert_array_equal(off, np.concatenate([[0], np.cumsum(inside.sum(1))]))
+    np.testing.assert_array_equal(idx, np.nonzero(inside)[1])
+    ctx.close()
