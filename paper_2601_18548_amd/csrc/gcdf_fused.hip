@@ -743,11 +743,13 @@ int64_t wgrad_chunk_len(int64_t B, int n, int width, int num_cu) {
 }
 
 int64_t wgrad_partial_floats(int64_t B, int width, int num_cu) {
+  // a batch has no more chunks than whole tiles, nor than wgrad_chunk_len aims at: a
+  // bound for every smaller batch too (the number of chunks itself is not monotone in
+  // B: 1,344 samples take 21 of 64, 1,345 take 11 of 128)
+  const int ntile = (width / 128) * (width / 128);
   int64_t most = 0;
-  for (int n = 1; n <= kWgMaxJobs; ++n) {
-    const int64_t L = wgrad_chunk_len(B, n, width, num_cu);
-    most = std::max(most, n * ((B + L - 1) / L));
-  }
+  for (int n = 1; n <= kWgMaxJobs; ++n)
+    most = std::max(most, n * std::min<int64_t>((B + kTileQ - 1) / kTileQ, std::max(1, num_cu / (ntile * n))));
   return most * width * width;
 }
 
@@ -1037,13 +1039,14 @@ __global__ void sum_chunks_kernel(const float* __restrict__ partial, int nchunks
 }
 
 hipError_t launch_wgrad_gemm(const WgradJobs& jobs, int width, int mode, int64_t ldb, int64_t B, float* partial,
-                             int num_cu, hipStream_t s, bool accumulate, const PartSum* ps) {
+                             int64_t partial_floats, int num_cu, hipStream_t s, bool accumulate, const PartSum* ps) {
   if (jobs.n < 1 || jobs.n > kWgMaxJobs || width % 128 || B <= 0) return hipErrorInvalidValue;
   if (ps && (ps->nparts < 1 || ps->width < 1)) return hipErrorInvalidValue;
   const int64_t chunk_len = wgrad_chunk_len(B, jobs.n, width, num_cu);
   const int nchunks = (int)((B + chunk_len - 1) / chunk_len);
   const int ntile = (width / 128) * (width / 128);
   const int64_t groups = (int64_t)jobs.n * nchunks;
+  if (groups * width * width > partial_floats) return hipErrorInvalidValue;
   const int64_t per_xcd = (groups + 7) / 8;
   const unsigned grid = (unsigned)(8 * per_xcd * ntile);
   if (mode == kFP32)

@@ -291,8 +291,10 @@ struct PartSum {
   PartOut out;
 };
 // ps (optional): those sums too, in the launch that adds the chunks.
+// hipErrorInvalidValue if the launch needs more than partial_floats.
 hipError_t launch_wgrad_gemm(const WgradJobs& jobs, int width, int mode, int64_t ldb, int64_t B, float* partial,
-                             int num_cu, hipStream_t s, bool accumulate = false, const PartSum* ps = nullptr);
+                             int64_t partial_floats, int num_cu, hipStream_t s, bool accumulate = false,
+                             const PartSum* ps = nullptr);
 // samples per chunk (a multiple of 64) for n products, and the floats of `partial`
 // any launch of up to kWgMaxJobs products over at most B samples needs
 int64_t wgrad_chunk_len(int64_t B, int n, int width, int num_cu);

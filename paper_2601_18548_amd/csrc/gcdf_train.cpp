@@ -32,7 +32,8 @@ struct gcdf_trainer {
   void* dumpH = nullptr;
   void* dumpG = nullptr;
   float* bias_part = nullptr;  // the training kernel's per-workgroup sums (Job::bias_part, T1Job::part)
-  float* partial = nullptr;
+  float* partial = nullptr;     // the GEMMs' chunks, for any batch up to max_batch
+  int64_t partial_floats = 0;
   const float* packed_from = nullptr;  // params pointer of the last packing
   // Table I loss workspace (allocated at its first use)
   float* t1 = nullptr;  // d, J, fbar, u, partial sums, Hd, Zb, per-workgroup scratch
@@ -165,7 +166,7 @@ hipError_t weight_gradients(gcdf_trainer* tr, int64_t B, float* loss, float* gra
   const int64_t ntiles = (B + gcdf::kTileQ - 1) / gcdf::kTileQ;
   const gcdf::PartSum ps = part_sums(tr, gcdf::fused_grid(ntiles, tr->num_cu * wgs_per_cu(tr->mode)), loss, grad);
   const int gmode = tr->mode == GCDF_FP32 ? gcdf::kFP32 : gcdf::kBF16;
-  return gcdf::launch_wgrad_gemm(wj, W, gmode, tr->ldb, B, tr->partial, tr->num_cu, s, false, &ps);
+  return gcdf::launch_wgrad_gemm(wj, W, gmode, tr->ldb, B, tr->partial, tr->partial_floats, tr->num_cu, s, false, &ps);
 }
 
 }  // namespace
@@ -205,8 +206,8 @@ gcdf_status gcdf_trainer_create(int32_t width, int32_t precision, int32_t device
   if (e == hipSuccess)
     e = hipMalloc(reinterpret_cast<void**>(&tr->bias_part),
                   (size_t)std::max(tr->num_cu, 1) * wgs_per_cu(precision) * gcdf::kTrainSumRows * W * 4);
-  const size_t part = (size_t)gcdf::wgrad_partial_floats(max_batch, W, tr->num_cu);
-  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&tr->partial), part * 4);
+  tr->partial_floats = gcdf::wgrad_partial_floats(max_batch, W, tr->num_cu);
+  if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&tr->partial), (size_t)tr->partial_floats * 4);
   if (e != hipSuccess) {
     gcdf_trainer_destroy(tr);
     return tfail(GCDF_ENOMEM, "trainer allocation failed: %s", hipGetErrorString(e));
@@ -374,11 +375,11 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
     b.H[l] = Hd + l * layer;
     a.out[l] = b.out[l] = grad + o.Wl[l];
   }
-  if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(a, W, gcdf::kFP32, ldb, B, tr->partial, tr->num_cu, s, false);
+  if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(a, W, gcdf::kFP32, ldb, B, tr->partial, tr->partial_floats, tr->num_cu, s, false);
   // and the tiles' sums: input layer dW_1 = sum zbar_1 v^T + g_1 u^T, db_l = sum zbar_l,
   // output layer dw_out = sum fbar h_4 + hdot_4, db_out = sum fbar
   const gcdf::PartSum ps = part_sums(tr, t1_grid, nullptr, grad);
-  if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(b, W, gcdf::kFP32, ldb, B, tr->partial, tr->num_cu, s, true, &ps);
+  if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(b, W, gcdf::kFP32, ldb, B, tr->partial, tr->partial_floats, tr->num_cu, s, true, &ps);
   return e == hipSuccess ? GCDF_OK : tfail(GCDF_EDEVICE, "gcdf_train_table1: %s", hipGetErrorString(e));
 }
 

@@ -411,3 +411,28 @@ def test_bf16_batch_gradient_is_the_sum_of_its_samples(tr_mod, B):
     off = np.abs(g - one.sum(0)) / bound
     print("largest error / bound %.3f" % off.max(), flush=True)
     assert np.all(np.isfinite(g)) and off.max() <= 1.0
+
+
+@pytest.mark.parametrize("max_batch,B", [(1408, 1300), (2500, 1984), (5001, 4000), (5001, 64)])
+@pytest.mark.parametrize("kind", ["fp32", "bf16", "table1"])
+def test_batch_below_the_largest_matches_a_trainer_of_its_size(tr_mod, kind, max_batch, B):
+    """A ragged last batch of a larger trainer takes the same chunks and sums as in a
+    trainer sized for it: the same bits (the first three need more partial products
+    than a batch of max_batch does)."""
+    w = wl.weights(256, seed=51, bf16_hidden=False)
+    k, p, y = batch(B, 22)
+    print("case %s max_batch=%d B=%d" % (kind, max_batch, B), flush=True)
+    params = tr_mod.flat_params(w)
+    kt, pt, yt = torch.from_numpy(k).cuda(), torch.from_numpy(p).cuda(), torch.from_numpy(y).cuda()
+    Js = torch.from_numpy(np.random.default_rng(9).normal(0, 1, (B, 9)).astype(np.float32)).cuda()
+    out = []
+    for size in (max_batch, B):
+        tr = tr_mod.Trainer(256, "fp32" if kind == "table1" else kind, max_batch=size)
+        if kind == "table1":
+            out.append(tr.table1(params, kt, pt, yt, Js, (4.0, 4.0) + (1.0,) * 7, (5.0, 0.1, 0.01, 0.01)))
+        else:
+            out.append(tr.mse(params, kt, pt, yt))
+        torch.cuda.synchronize()
+        tr.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b) and bool(torch.isfinite(a).all())
