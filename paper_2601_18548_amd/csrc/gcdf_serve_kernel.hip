@@ -190,51 +190,55 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
         if (seq < pub) {
           const uint32_t s = (uint32_t)(seq % slots);
           const uint64_t s32 = seq & 0xffffffffull;
-          // Not read yet: if nobody has claimed a tile of it (an older tag), it cannot
-          // have completed: the workgroup whose compare-and-swap re-tags the word has
-          // its tile 0 and reads the host's descriptor; the others wait for its copy,
-          // and read the host's themselves should it be long in coming.  (Request 0
-          // finds its own tag, and no copy.)
+          // Claim word of the slot: (request tag << 32) | tiles handed out.  While it has
+          // an older tag nobody has claimed a tile of seq, so seq cannot have completed:
+          // the workgroup whose compare-and-swap re-tags the word has its tile 0 and
+          // reads the host's descriptor; the others wait for its copy, and read the
+          // host's themselves should it be long in coming.  (Request 0 finds its own tag,
+          // and no copy.)  A swap that fails is tried again while the tag is older: an
+          // add that comes late for the slot's last request changes the count alone.
+          // Each failure is another workgroup's add or re-tagging, so the tries end.
+          unsigned long long v = dev_relaxed(&dev->claim[s]);
+          bool tagged = false;
+          while (!tagged && (v >> 32) < s32)
+            tagged = __hip_atomic_compare_exchange_strong(&dev->claim[s], &v, (s32 << 32) | 1ull, __ATOMIC_RELAXED,
+                                                          __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (tagged) {
+            load_desc(nxt, &ctl->desc[s], seq, [](auto* p) { return sys_relaxed(p); });
+            store_copy(dev, s, nxt);
+            nt_seq = nxt_seq = seq;
+            ntiles = nxt.ntiles;
+            got_seq = (int64_t)seq;
+            got_tile = 0;
+            break;
+          }
+          // from here on the word's tag is s32 or newer (tags only grow)
           if (nt_seq != seq) {
-            unsigned long long v = dev_relaxed(&dev->claim[s]);
-            if ((v >> 32) < s32 &&
-                __hip_atomic_compare_exchange_strong(&dev->claim[s], &v, (s32 << 32) | 1ull, __ATOMIC_RELAXED,
-                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
-              load_desc(nxt, &ctl->desc[s], seq, [](auto* p) { return sys_relaxed(p); });
-              store_copy(dev, s, nxt);
-              nt_seq = nxt_seq = seq;
-              ntiles = nxt.ntiles;
-              got_seq = (int64_t)seq;
-              got_tile = 0;
-              break;
-            }
             for (int tries = 0; seq != 0 && tries < 64; ++tries) {
               if (load_copy(dev, s, seq, nxt)) {
                 nt_seq = nxt_seq = seq;
                 ntiles = nxt.ntiles;
                 break;
               }
-              if ((dev_relaxed(&dev->claim[s]) >> 32) != s32) break;  // the slot has moved on
+              if ((dev_relaxed(&dev->claim[s]) >> 32) > s32) break;  // the slot has moved on
               __builtin_amdgcn_s_sleep(8);
             }
-          }
-          if (nt_seq != seq) {
-            // A cursor behind the others can reach a request that has completed and
-            // whose slot the host has already given to a later request: the
-            // descriptor then describes that later request, and its tile count must
-            // not be taken for seq's.
-            if (!desc_ntiles(&ctl->desc[s], seq, ntiles)) {
-              if (open_count && cur_seq == seq) report();  // (none: seq is complete)
-              ++seq;
-              if (fin_seq >= 0) break;
-              continue;
+            if (nt_seq != seq) {
+              // A cursor behind the others can reach a request that has completed and
+              // whose slot the host has already given to a later request: the
+              // descriptor then describes that later request, and its tile count must
+              // not be taken for seq's.
+              if (!desc_ntiles(&ctl->desc[s], seq, ntiles)) {
+                if (open_count && cur_seq == seq) report();  // (none: seq is complete)
+                ++seq;
+                if (fin_seq >= 0) break;
+                continue;
+              }
+              nt_seq = seq;
             }
-            nt_seq = seq;
+            v = dev_relaxed(&dev->claim[s]);
           }
-          // Claim word of the slot: (request tag << 32) | tiles handed out.  The first
-          // claimant of a request has re-tagged the word (above); every other claim is a
-          // fetch_add, which never has to be retried.
-          const unsigned long long v = dev_relaxed(&dev->claim[s]);
+          // Every claim but a request's first is a fetch_add, which never has to be retried.
           bool moved_on = false;
           do {
             const uint64_t vs = v >> 32, vc = v & 0xffffffffull;
@@ -353,8 +357,14 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
         pj.pidx32 = uniform(fin.argmin);
         pj.npairs = pj.K;
         pj.J = uniform(fin.Jmin);
-        for (int64_t q0 = 0; q0 < pj.K; q0 += kTileQ)
-          process_tile<W, MODE, 2, true, true, false, false, SPH>(net, pj, 0, q0, tc);
+        for (int64_t q0 = 0; q0 < pj.K; q0 += kTileQ) {
+          // (an opaque tile start: as an induction variable, a lane's offset into J was
+          // spilled at the end of the tile's prologue while only wave 0 was active, and
+          // the other waves reloaded what had never been stored)
+          int64_t q = q0;
+          asm volatile("" : "+s"(q));
+          process_tile<W, MODE, 2, true, true, false, false, SPH>(net, pj, 0, q, tc);
+        }
       }
       __threadfence_system();
       __syncthreads();
