@@ -599,9 +599,12 @@ __device__ __forceinline__ void minkey_decode(unsigned long long stored, float& 
 // they lie in the tile) times the identity give 32 x 32 blocks with a feature per lane
 // and samples in its registers; half a dozen moves and one exchange of lane halves
 // pack 8 samples of a feature into 16 bytes, and a wave's store writes 1 KiB of
-// consecutive pieces.  The product of a finite BF16 value with 1 plus zeros is exact
-// (a sample with an infinite value gives NaN in its block: its gradient is not finite
-// either way).  Transposing 8 x 8 blocks with vector instructions through a 32 KiB LDS
+// consecutive pieces.  The product of a finite BF16 value with 1 plus zeros is exact; an
+// infinity or NaN makes its sample's whole block NaN or infinite, so a wave whose sums
+// come out not finite copies and sums again, element by element, and only the values
+// that are not finite themselves reach HBM and the sums.  (The dumps without sums, h1 to
+// h3, need no second copy: such a value in h_l makes all of the sample's z_{l+1}, and so
+// its SiLU' and every g of it, not finite.)  Transposing 8 x 8 blocks with vector instructions through a 32 KiB LDS
 // stage, and the sums below on the vector ALU, a dump took 3.1-3.6 K cycles and the
 // sums-only copies of h4 and g1 4.4 and 5.0 K, in all 30 K of a tile's 79 K; here 1.1-1.3,
 // 1.6 and 2.1 K of 52 K (batch 65,536: the kernel 155 -> 121 us).
@@ -711,41 +714,14 @@ __device__ __forceinline__ void dump_tile(const char* act, void* dst, int64_t ld
         d[e] = (c >> 1) == 8 * k + 4 * half + e ? ((c & 1) ? 0x3f800000u : 0x00003f80u) : 0u;
       eye[k] = __builtin_bit_cast(bf16x8, d);
     }
-    u32x4 piece[2];
     const int s0 = 2 * (threadIdx.x >> 6);  // this wave's first K step of the tile
-#pragma unroll
-    for (int st = 0; st < kTileQ / 16; ++st) {  // 16 samples per round: blocks 2 st (lanes < 32), 2 st + 1
-      const int nb = 2 * st + half;
+    // one 16-sample round: store lane (c, half)'s piece v, samples 8 nb .. 8 nb + 7 of
+    // feature f, and add it to the sums: the pieces are the B fragments of a product over
+    // samples, row c of A holds what column sums are wanted of
+    auto round = [&](int nb, const u32x4& v) {
       const int P = nb * W + f;
-      if (st % 2 == 0) {  // the next 32 samples: lane (m, half) reads sample m's features 8 half + e of each step
-        const int n = 16 * st + c;
-        f32x16 z;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) z[j] = 0.f;
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          const u32x4 x = n < nvalid ? *reinterpret_cast<const u32x4*>(act + (s0 + k) * Geo<W, MODE>::STEP_BYTES +
-                                                                       half * 16 * kTileQ + n * 16)
-                                     : u32x4{0u, 0u, 0u, 0u};
-          z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), eye[k], z, 0, 0, 0);
-        }
-        // lane (c, half): feature c, samples 8 g + 4 half + r of the 32 in z[4 g + r]
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          uint32_t p[4];  // samples (0 1), (2 3) of g = 2 t, then of g = 2 t + 1
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            p[q] = __builtin_amdgcn_perm(__float_as_uint(z[8 * t + 2 * q + 1]), __float_as_uint(z[8 * t + 2 * q]), 0x07060302u);
-          const auto x0 = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
-          const auto x1 = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
-          piece[t] = u32x4{x0[0], x1[0], x0[1], x1[1]};
-        }
-      }
-      const u32x4 v = piece[st % 2];
       if (store) *reinterpret_cast<u32x4*>(o + P * 8) = v;
       if (sums) {
-        // the pieces are the B fragments (8 samples of feature f) of a product over
-        // samples: row c of A holds what column sums are wanted of
         const int n0 = nb * 8;
         bf16x8 ah, al;
 #pragma unroll
@@ -766,18 +742,75 @@ __device__ __forceinline__ void dump_tile(const char* act, void* dst, int64_t ld
         if (sums->in_rows)
           dacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, __builtin_bit_cast(bf16x8, v), dacc, 0, 0, 0);
       }
+    };
+#pragma unroll
+    for (int h = 0; h < kTileQ / 32; ++h) {  // 32 samples: lane (m, half) reads sample m's features 8 half + e of each step
+      const int n = 32 * h + c;
+      f32x16 z;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) z[j] = 0.f;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const u32x4 x = n < nvalid ? *reinterpret_cast<const u32x4*>(act + (s0 + k) * Geo<W, MODE>::STEP_BYTES +
+                                                                     half * 16 * kTileQ + n * 16)
+                                   : u32x4{0u, 0u, 0u, 0u};
+        z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, x), eye[k], z, 0, 0, 0);
+      }
+      // lane (c, half): feature c, samples 8 g + 4 half + r of the 32 in z[4 g + r]
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        uint32_t p[4];  // samples (0 1), (2 3) of g = 2 t, then of g = 2 t + 1
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          p[q] = __builtin_amdgcn_perm(__float_as_uint(z[8 * t + 2 * q + 1]), __float_as_uint(z[8 * t + 2 * q]), 0x07060302u);
+        const auto x0 = __builtin_amdgcn_permlane32_swap(p[0], p[2], false, false);
+        const auto x1 = __builtin_amdgcn_permlane32_swap(p[1], p[3], false, false);
+        round(4 * h + 2 * t + half, u32x4{x0[0], x1[0], x0[1], x1[1]});
+      }
+    }
+    if (sums) {
+      // rows 0 (ones), 9 (ones beside the inputs) or 0..2 (seeds' parts) meet every value
+      // of the wave's features; in the upper lanes these are rows of zeros
+      float t = sums->in_rows ? dacc[5] : sums->seed ? dacc[2] + dacc[1] + dacc[0] : dacc[0];
+      if (__builtin_amdgcn_ballot_w64(!__builtin_isfinite(t))) {
+        float part = 0.f;  // the seeds as they are: an infinite one has no BF16 parts
+#pragma unroll
+        for (int j = 0; j < 16; ++j) dacc[j] = 0.f;
+        int g = f;
+        asm volatile("" : "+v"(g));  // (addresses formed here, not kept through the tile for this rare case)
+        const char* a = act + (g >> 4) * Geo<W, MODE>::STEP_BYTES + ((g >> 3) & 1) * 16 * kTileQ + (g & 7) * 2;
+#pragma unroll 1
+        for (int nb = half; nb < kTileQ / 8; nb += 2) {
+          u32x4 v;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const int n = 8 * nb + e;
+            const uint32_t x = n < nvalid ? *reinterpret_cast<const uint16_t*>(a + n * 16) : 0u;
+            v[e >> 1] = (e & 1) ? v[e >> 1] | (x << 16) : x;
+            if (sums->seed) part += __uint_as_float(x << 16) * sums->seed[n * Geo<W, MODE>::XIN_FLOATS];
+          }
+          round(nb, v);
+        }
+        if (sums->seed) {
+          part += __shfl_xor(part, 32);
+          dacc[0] = part;
+          dacc[1] = dacc[2] = 0.f;
+        }
+      }
     }
     if (sums) {
       // lane (feature f % 32, half) holds rows 8 (j/4) + 4 half + j%4
+      int r = f;
+      asm volatile("" : "+v"(r));  // (the rows' addresses too are formed here)
       if (sums->in_rows) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) sums->in_rows[(4 * half + j) * W + f] += dacc[j];
+        for (int j = 0; j < 4; ++j) sums->in_rows[(4 * half + j) * W + r] += dacc[j];
         if (half == 0) {
-          sums->in_rows[8 * W + f] += dacc[4];
-          sums->row[f] += dacc[5];
+          sums->in_rows[8 * W + r] += dacc[4];
+          sums->row[r] += dacc[5];
         }
       } else if (half == 0) {
-        sums->row[f] += sums->seed ? dacc[2] + dacc[1] + dacc[0] : dacc[0];
+        sums->row[r] += sums->seed ? dacc[2] + dacc[1] + dacc[0] : dacc[0];
       }
     }
   }

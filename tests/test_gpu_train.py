@@ -436,3 +436,46 @@ def test_batch_below_the_largest_matches_a_trainer_of_its_size(tr_mod, kind, max
         tr.close()
     for a, b in zip(*out):
         assert torch.equal(a, b) and bool(torch.isfinite(a).all())
+
+
+@pytest.mark.parametrize("where", ["h4", "g4"])
+@pytest.mark.parametrize("sample", [0, 31, 33, 64])
+def test_bf16_infinities_stay_in_their_rows(tr_mod, where, sample):
+    """One infinite activation (h4 of feature 37, from its bias) or back-propagated value
+    (g4 of feature 37 for one sample, from its output weight) leaves the rows of the other
+    features in layer 4 as they are without it: its wave copies them one by one."""
+    f, B = 37, 65
+    w = wl.weights(256, seed=48, bf16_hidden=False)
+    k, p, _ = batch(B, 23)
+    seeds = np.random.default_rng(24).normal(0, 1, B).astype(np.float32)
+    if where == "g4":
+        seeds[sample] = 1e38
+    print("case infinity in %s, sample %d" % (where, sample), flush=True)
+    trainer = tr_mod.Trainer(256, "bf16", max_batch=B)
+    kt, pt, st = torch.from_numpy(k).cuda(), torch.from_numpy(p).cuda(), torch.from_numpy(seeds).cuda()
+
+    def grad(bias, weight, sel=slice(0, B)):
+        x = wl.Weights(w.width, w.depth, [m.copy() for m in w.mats], [b.copy() for b in w.biases], w.in_dim)
+        x.biases[3][f], x.mats[4][0, f] = bias, weight
+        if where == "g4":
+            x.biases[3][f] = 1.0  # SiLU'(z4) of order one at every sample
+        g = trainer.backward(tr_mod.flat_params(x), *(t[sel].contiguous() for t in (kt, pt, st)))
+        return dict(zip(NAMES, split(g.cpu().numpy(), w)))
+
+    plain = grad(0.0, 0.5)
+    odd = grad(np.inf, 0.5) if where == "h4" else grad(0.0, 1e3)
+    others = np.arange(256) != f
+    assert np.isfinite(plain["W4"]).all()
+    assert not np.isfinite(odd["W4"][f]).any() and not np.isfinite(odd["b4"][f])
+    assert not np.isfinite(odd["W3"]).any() and not np.isfinite(odd["W1"]).any()
+    assert np.array_equal(odd["W4"][others], plain["W4"][others]) and np.array_equal(odd["b4"][others], plain["b4"][others])
+    assert np.array_equal(odd["b_out"], plain["b_out"])
+    if where == "g4":  # dw_out sums seeds and h4 alone (where they overflow, in both)
+        assert np.array_equal(odd["w_out"], plain["w_out"])
+        return
+    # dw_out's sums are taken one by one in the wave of an infinite h4: the same terms in another order
+    terms = sum(np.abs(grad(0.0, 0.5, slice(i, i + 1))["w_out"].astype(np.float64)) for i in range(B))
+    off = np.abs(odd["w_out"].astype(np.float64) - plain["w_out"]).ravel()
+    assert np.isfinite(odd["w_out"].ravel()[others]).all()
+    assert np.all(off[others] <= 2 * (B + 32) * 2.0 ** -24 * terms.ravel()[others])
+    assert not np.isfinite(odd["w_out"].ravel()[f])
