@@ -315,9 +315,12 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
   }
 }
 
-hipError_t launch_table1_tiles(const DevNet& net, const T1Job& job, int grid, hipStream_t s) {
+hipError_t launch_table1_tiles(const DevNet& net, const T1Job& job, int num_cu, hipStream_t s) {
   if (net.width != 256 || net.mode != kFP32) return hipErrorInvalidValue;
+  static_assert(train_wgs(kFP32) == Geo<256, kFP32>::WGS, "the per-workgroup sums follow the grid");
   const int64_t ntiles = (job.B + kTileQ - 1) / kTileQ;
+  const int grid = train_grid(ntiles, kFP32, num_cu);
+  if (grid > job.parts) return hipErrorInvalidValue;
   hipLaunchKernelGGL(table1_tiles<256>, dim3((unsigned)grid), dim3((Geo<256, kFP32>::THREADS)), 0, s, net, job, ntiles);
   return hipGetLastError();
 }

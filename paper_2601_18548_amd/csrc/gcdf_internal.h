@@ -84,8 +84,10 @@ struct Job {
   float mse_scale, inv_b;
   // training: per-workgroup sums, BF16 [kTrainSumRows][W][grid], FP32
   // [grid][kTrainSumRows][W] (rows: sum_i g_l for l = 1..4; sum_i seed_i h4_i;
-  // sum_i g1_i v_c(i) for the nine inputs c; sum_i seed_i; the fused loss)
+  // sum_i g1_i v_c(i) for the nine inputs c; sum_i seed_i; the fused loss), for the
+  // train_grid workgroups of the launch; bias_parts: workgroups it has room for
   float* bias_part;
+  int bias_parts;
 };
 constexpr int kTrainSumRows = 16;
 
@@ -299,10 +301,13 @@ hipError_t launch_wgrad_gemm(const WgradJobs& jobs, int width, int mode, int64_t
 // any launch of up to kWgMaxJobs products over at most B samples needs
 int64_t wgrad_chunk_len(int64_t B, int n, int width, int num_cu);
 int64_t wgrad_partial_floats(int64_t B, int width, int num_cu);
-// Workgroups of a one-shot fused_query launch over ntiles tiles: one per compute
-// unit (each holds one), fewer for small launches.  Training's per-workgroup sums
-// are indexed by it.
-inline int fused_grid(int64_t ntiles, int num_cu) { return (int)(ntiles < num_cu ? ntiles : num_cu); }
+// Workgroups of a one-shot launch over ntiles tiles: as many as the device holds at
+// once (`resident`), fewer for small launches.
+inline int fused_grid(int64_t ntiles, int resident) { return (int)(ntiles < resident ? ntiles : resident); }
+// Workgroups of a training launch (and of table1_tiles), by which the per-workgroup
+// sums are indexed.  Per compute unit: Geo::WGS of width 256, checked at each launch.
+constexpr int train_wgs(int mode) { return mode == kFP32 ? 2 : 1; }
+inline int train_grid(int64_t ntiles, int mode, int num_cu) { return fused_grid(ntiles, num_cu * train_wgs(mode)); }
 
 
 // Table I training loss (width 256, FP32): per 64-sample tile, the forward, the
@@ -325,9 +330,10 @@ struct T1Job {
   float* part;  // [grid][kTrainSumRows][W]: sum_i zbar_l (l = 1..4); sum_i fbar_i h4_i + hdot4_i;
                 // sum_i zbar1_i v_c(i) + g1_i u_c(i); sum_i fbar_i
   float* scratch;
+  int parts;  // workgroups that part and scratch have room for
 };
 constexpr int kT1ScratchArrays = 11;
-hipError_t launch_table1_tiles(const DevNet& net, const T1Job& job, int grid, hipStream_t s);
+hipError_t launch_table1_tiles(const DevNet& net, const T1Job& job, int num_cu, hipStream_t s);
 // Per-sample loss terms and their derivatives: from d[i], J[i][9] (the query), targets
 // fstar, Jstar, m_diag (9) and lambda (4): fbar[i] = dL/dd_i, u[c][i] (row stride ldb,
 // zero from B to ldb), and losses[0..3] = the four averaged terms, losses[4] = total,

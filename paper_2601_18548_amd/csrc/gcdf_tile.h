@@ -1923,7 +1923,8 @@ static hipError_t launch_t(const DevNet& net, const Job& job, int num_cu, hipStr
   if constexpr (CB == 2 && GRAD && PAIRS && W == 256 && (MODE == kFP32 || MODE == kBF16) && !SPH) {  // training: width 256, FP32 or BF16
     if (job.dumpH) {
       // the kernel writes its sums to bias_part, no J, and d only with the fused loss
-      if (!job.bias_part || job.J || (job.d && !job.target)) return hipErrorInvalidValue;
+      static_assert(train_wgs(MODE) == G::WGS, "the per-workgroup sums follow the grid");
+      if (!job.bias_part || (int)grid.x > job.bias_parts || job.J || (job.d && !job.target)) return hipErrorInvalidValue;
       // FP32 batches of at most one tile per compute unit: with the whole register file
       // the tile's h4 copy spills no SiLU' values (batch 5,001: step 176 -> 154 us); past
       // that, two workgroups per compute unit are worth more than the spill (20,000:

@@ -13,7 +13,6 @@
 //           dL/dd_i = 2 (d_i - y_i) / B, so no separate forward runs.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -32,6 +31,7 @@ struct gcdf_trainer {
   void* dumpH = nullptr;
   void* dumpG = nullptr;
   float* bias_part = nullptr;  // the training kernel's per-workgroup sums (Job::bias_part, T1Job::part)
+  int bias_parts = 0;          // workgroups it has room for
   float* partial = nullptr;     // the GEMMs' chunks, for any batch up to max_batch
   int64_t partial_floats = 0;
   const float* packed_from = nullptr;  // params pointer of the last packing
@@ -124,20 +124,21 @@ gcdf::Job training_job(const gcdf_trainer* tr, const float* knots, const float* 
   job.dumpG = tr->dumpG;
   job.ldb = tr->ldb;
   job.bias_part = tr->bias_part;  // the kernel sums what needs no GEMM
+  job.bias_parts = tr->bias_parts;
   return job;
 }
 
-// Most workgroups of a training launch per compute unit (FP32 tiles run two).
-int wgs_per_cu(int mode) { return mode == GCDF_FP32 ? 2 : 1; }
+// Tiles of a batch.
+int64_t tiles(int64_t B) { return (B + gcdf::kTileQ - 1) / gcdf::kTileQ; }
 
-// Where the per-workgroup sums of `nparts` workgroups go: the bias gradients, dw_out,
+// Where the per-workgroup sums of a batch's launch go: the bias gradients, dw_out,
 // dW1 column by column, db_out and (training kernel) the loss.
-gcdf::PartSum part_sums(const gcdf_trainer* tr, int nparts, float* loss, float* grad) {
+gcdf::PartSum part_sums(const gcdf_trainer* tr, int64_t B, float* loss, float* grad) {
   const int W = tr->W;
   const Offsets o(W);
   gcdf::PartSum ps{};
   ps.part = tr->bias_part;
-  ps.nparts = nparts;
+  ps.nparts = gcdf::train_grid(tiles(B), tr->mode, tr->num_cu);
   ps.width = W;
   ps.by_wg = tr->mode == GCDF_FP32;
   float* rows[5] = {grad + o.b1, grad + o.bl[0], grad + o.bl[1], grad + o.bl[2], grad + o.w5};
@@ -163,8 +164,7 @@ hipError_t weight_gradients(gcdf_trainer* tr, int64_t B, float* loss, float* gra
     wj.H[l] = static_cast<const char*>(tr->dumpH) + l * layer;
     wj.out[l] = grad + o.Wl[l];
   }
-  const int64_t ntiles = (B + gcdf::kTileQ - 1) / gcdf::kTileQ;
-  const gcdf::PartSum ps = part_sums(tr, gcdf::fused_grid(ntiles, tr->num_cu * wgs_per_cu(tr->mode)), loss, grad);
+  const gcdf::PartSum ps = part_sums(tr, B, loss, grad);
   const int gmode = tr->mode == GCDF_FP32 ? gcdf::kFP32 : gcdf::kBF16;
   return gcdf::launch_wgrad_gemm(wj, W, gmode, tr->ldb, B, tr->partial, tr->partial_floats, tr->num_cu, s, false, &ps);
 }
@@ -203,9 +203,9 @@ gcdf_status gcdf_trainer_create(int32_t width, int32_t precision, int32_t device
   if (e == hipSuccess) e = hipMalloc(&tr->wbuf, tr->off_m + 6 * tr->mbytes);
   if (e == hipSuccess) e = hipMalloc(&tr->dumpH, dump);
   if (e == hipSuccess) e = hipMalloc(&tr->dumpG, dump);
+  tr->bias_parts = gcdf::train_grid(tr->ldb / gcdf::kTileQ, precision, tr->num_cu);
   if (e == hipSuccess)
-    e = hipMalloc(reinterpret_cast<void**>(&tr->bias_part),
-                  (size_t)std::max(tr->num_cu, 1) * wgs_per_cu(precision) * gcdf::kTrainSumRows * W * 4);
+    e = hipMalloc(reinterpret_cast<void**>(&tr->bias_part), (size_t)tr->bias_parts * gcdf::kTrainSumRows * W * 4);
   tr->partial_floats = gcdf::wgrad_partial_floats(max_batch, W, tr->num_cu);
   if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void**>(&tr->partial), (size_t)tr->partial_floats * 4);
   if (e != hipSuccess) {
@@ -309,12 +309,11 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
   const int W = tr->W;
   const int64_t ldb = tr->ldb;
   const size_t layer = (size_t)W * ldb;
-  const int grid = tr->num_cu * wgs_per_cu(tr->mode);
   const size_t arr = (size_t)gcdf::kThreads * 64;
   // workspace: d [ldb], J [9 ldb], fbar [ldb], u [9 ldb], part [4 ceil(ldb/256)], Hd, Zb [4 layer each],
-  // scratch [grid * 11 * arr]
+  // scratch [bias_parts * 11 * arr]
   const size_t n_d = ldb, n_J = 9 * ldb, n_f = ldb, n_u = 9 * ldb, n_p = 4 * ((ldb + 255) / 256) + 8;
-  const size_t n_dump = 4 * layer, n_s = (size_t)grid * gcdf::kT1ScratchArrays * arr;
+  const size_t n_dump = 4 * layer, n_s = (size_t)tr->bias_parts * gcdf::kT1ScratchArrays * arr;
   const size_t need = 4 * (n_d + n_J + n_f + n_u + n_p + 2 * n_dump + n_s);
   if (!tr->t1) {
     if (hipMalloc(reinterpret_cast<void**>(&tr->t1), need) != hipSuccess) {
@@ -362,9 +361,8 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
   tj.Zb = Zb;
   tj.part = tr->bias_part;
   tj.scratch = scratch;
-  const int64_t ntiles = (B + gcdf::kTileQ - 1) / gcdf::kTileQ;
-  const int t1_grid = gcdf::fused_grid(ntiles, grid);
-  if (e == hipSuccess) e = gcdf::launch_table1_tiles(tr->net, tj, t1_grid, s);
+  tj.parts = tr->bias_parts;
+  if (e == hipSuccess) e = gcdf::launch_table1_tiles(tr->net, tj, tr->num_cu, s);
   // 4. dW_l = sum zbar_l h_{l-1}^T + g_l hdot_{l-1}^T for the hidden layers
   gcdf::WgradJobs a{}, b{};
   a.n = b.n = 3;
@@ -378,7 +376,7 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
   if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(a, W, gcdf::kFP32, ldb, B, tr->partial, tr->partial_floats, tr->num_cu, s, false);
   // and the tiles' sums: input layer dW_1 = sum zbar_1 v^T + g_1 u^T, db_l = sum zbar_l,
   // output layer dw_out = sum fbar h_4 + hdot_4, db_out = sum fbar
-  const gcdf::PartSum ps = part_sums(tr, t1_grid, nullptr, grad);
+  const gcdf::PartSum ps = part_sums(tr, B, nullptr, grad);
   if (e == hipSuccess) e = gcdf::launch_wgrad_gemm(b, W, gcdf::kFP32, ldb, B, tr->partial, tr->partial_floats, tr->num_cu, s, true, &ps);
   return e == hipSuccess ? GCDF_OK : tfail(GCDF_EDEVICE, "gcdf_train_table1: %s", hipGetErrorString(e));
 }

@@ -167,3 +167,22 @@ def test_bf16_trainer_is_rejected(tr_mod):
     kt, pt, ft, Jt = _cuda(k, p, fs, Js)
     with pytest.raises(g.GcdfError):
         tr.table1(tr_mod.flat_params(w), kt, pt, ft, Jt, M_DIAG)
+
+
+def test_small_trainer_needs_little_memory(tr_mod):
+    """The workspaces follow the largest batch, not the device: one tile's worth of Table I
+    scratch (0.7 MiB) and sums, not every compute unit's (360 MiB)."""
+    params, args = tr_mod.flat_params(wl.weights(256, seed=82, bf16_hidden=False)), _cuda(*_case(64, 5))
+
+    def used():
+        torch.cuda.synchronize()
+        before = torch.cuda.mem_get_info()[0]
+        tr = tr_mod.Trainer(256, "fp32", max_batch=64)
+        tr.table1(params, *args, M_DIAG)
+        torch.cuda.synchronize()
+        after = torch.cuda.mem_get_info()[0]
+        tr.close()
+        return before - after
+
+    used()  # the kernels' own first-use allocations
+    assert used() <= 32 << 20  # a dozen small allocations of at most 2 MiB granularity each
