@@ -116,7 +116,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
     const int64_t q0 = tile * kTileQ;
     const int nvalid = (int)(job.B - q0 < kTileQ ? job.B - q0 : kTileQ);
     auto dumpl = [&](float* arrbase, int l, const DumpSums* sm = nullptr, bool store = true) {
-      dump_tile<W, MODE>(tc.act, arrbase + l * layer, job.ldb, q0, nvalid, sm, store);
+      dump_tile<W, MODE>(tc.act, store ? arrbase + l * layer : nullptr, job.ldb, q0, nvalid, sm, store);
     };
     // ---- prologue: base-frame points, fbar and u of the tile's samples ----
     if (tid < kTileQ) {
@@ -210,7 +210,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
       return b.w5[16 * I + j] * d1;
     });
     __syncthreads();
-    dumpl(job.G, 3);
+    dumpl(job.G, 2);
     static_for<3>([&](auto LL) {
       constexpr int L = 2 - LL;  // W_{L+2}^T g_{L+2} = r_{L+1}
       zero(a);
@@ -224,7 +224,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
       });
       __syncthreads();
       const DumpSums sm{nullptr, nullptr, rows + 5 * W, nullptr, uin, 9, 0};  // sum_i g1_i u_i^T
-      dumpl(job.G, L, L == 0 ? &sm : nullptr, L > 0);
+      dumpl(job.G, L - 1, L == 0 ? &sm : nullptr, L > 0);
       __syncthreads();
     });
     // ---- tangent pass along u: zdot_1 = W_1 u to the scratch, hdot_1 to LDS ----
@@ -295,7 +295,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
     });
     __syncthreads();
     const DumpSums sm4{rows + 3 * W, nullptr, nullptr, nullptr, nullptr, 0, 0};  // sum_i zbar4_i
-    dumpl(job.Zb, 3, &sm4);
+    dumpl(job.Zb, 2, &sm4);
     static_for<3>([&](auto LL) {
       constexpr int L = 2 - LL;  // hbar_{L+1} = W_{L+2}^T zbar_{L+2}
       zero(a);
@@ -309,7 +309,7 @@ __global__ __launch_bounds__((Geo<W, kFP32>::THREADS), (Geo<W, kFP32>::WGS)) voi
       __syncthreads();
       // sum_i zbar_i, and for the input layer sum_i zbar1_i v_i^T
       const DumpSums sm{rows + L * W, nullptr, L == 0 ? rows + 5 * W : nullptr, nullptr, tc.xin, XF, 2};
-      dumpl(job.Zb, L, &sm, L > 0);
+      dumpl(job.Zb, L - 1, &sm, L > 0);
       __syncthreads();
     });
   }

@@ -70,9 +70,9 @@ struct Job {
   int32_t* dec_argmin;
   // training (pairs mode): the reverse sweep is seeded with seed[i] = dL/dd_i instead
   // of 1, and the tile's layer inputs h_{l+1} (dumpH[l]) and back-propagated
-  // gradients dL/dz_{l+1} (dumpG[l]), l = 0..3, are written as [W x ldb] arrays in
+  // gradients dL/dz_{l+2} (dumpG[l]), l = 0..2, are written as [W x ldb] arrays in
   // the blocked feature-major layout (element (f, i) at ((i / S) W + f) S + i % S,
-  // S = 16 bytes of samples), ldb a multiple of 64; h_4 and dL/dz_1 are not written.
+  // S = 16 bytes of samples), ldb a multiple of 64 (h_4 and dL/dz_1 are only summed).
   const float* seed;
   void* dumpH;
   void* dumpG;
@@ -313,10 +313,11 @@ inline int train_grid(int64_t ntiles, int mode, int num_cu) { return fused_grid(
 // Table I training loss (width 256, FP32): per 64-sample tile, the forward, the
 // reverse sweep for e = dF/dv, the tangent pass along u and the reverse mode through
 // both programs (see table1_tiles).  Dumps (blocked feature-major, [W x ldb] each):
-//   H[l] = h_{l+1}, G[l] = g_{l+1} (reverse sweep, = d/dz of the tangent output),
-//   Hd[l] = hdot_{l+1} (tangent), Zb[l] = zbar_{l+1} (adjoint of the primal), of which
-// H[3], G[0], Hd[3] and Zb[0], needed for sums only, are not written.  scratch: per workgroup of the grid, 11 arrays of
-// kThreads * 64 floats (pre-activations, tangent pre-activations, reverse products).
+//   H[l] = h_{l+1}, G[l] = g_{l+2} (reverse sweep, = d/dz of the tangent output),
+//   Hd[l] = hdot_{l+1} (tangent), Zb[l] = zbar_{l+2} (adjoint of the primal), l = 0..2
+// (h_4, g_1, hdot_4 and zbar_1 are only summed).  scratch: per workgroup of the grid,
+// 11 arrays of kThreads * 64 floats (pre-activations, tangent pre-activations, reverse
+// products).
 struct T1Job {
   const float* knots;
   const float* points;

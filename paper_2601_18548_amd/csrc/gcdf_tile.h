@@ -943,8 +943,9 @@ struct TileDump {
   float* sp1;  // BF16: SiLU'(z1) of the input layer kept in LDS for the reverse sweep (see train_sp1)
   int width;
   __device__ __forceinline__ float* row(int r) const { return bsum + r * width; }
+  // h_{l+1}, l = 0..2, and g_{l+1}, l = 1..3 (h_4 and g_1 are only summed)
   __device__ __forceinline__ void* h(int l) const { return static_cast<char*>(H) + l * layer_elems * elem_bytes; }
-  __device__ __forceinline__ void* g(int l) const { return static_cast<char*>(G) + l * layer_elems * elem_bytes; }
+  __device__ __forceinline__ void* g(int l) const { return static_cast<char*>(G) + (l - 1) * layer_elems * elem_bytes; }
 };
 
 // Whether a hidden-layer epilogue keeps its packed results in registers across
@@ -1088,7 +1089,7 @@ __device__ __forceinline__ void fwd_hidden(const DevNet& net, const TileCtx<W, M
     // barrier: wave 0 wrote the seeds the copy reads)
     __syncthreads();
     const DumpSums sm{td.row(4), td.xin + 11, nullptr, td.vt, nullptr, 0, 0};
-    dump_tile<W, MODE>(td.act, td.h(3), td.ldb, td.q0, td.nvalid, &sm, false);
+    dump_tile<W, MODE>(td.act, nullptr, td.ldb, td.q0, td.nvalid, &sm, false);
     __syncthreads();  // h4 fully read before g4 overwrites the tile; seeds written
   }
   static_for<MT>([&](auto I) {
@@ -1413,7 +1414,7 @@ __device__ __forceinline__ void bwd_input(const DevNet& net, const TileCtx<W, MO
     before_copy();
     // g1 is needed only for db1 and dW1 = sum_i g1_i v_i^T, summed here
     const DumpSums sm{td.row(0), nullptr, td.row(5), td.vt, td.xin, Geo<W, MODE>::XIN_FLOATS, 2};
-    dump_tile<W, MODE>(td.act, td.g(0), td.ldb, td.q0, td.nvalid, &sm, false);
+    dump_tile<W, MODE>(td.act, nullptr, td.ldb, td.q0, td.nvalid, &sm, false);
   }
 }
 

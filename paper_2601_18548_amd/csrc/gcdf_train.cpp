@@ -160,7 +160,7 @@ hipError_t weight_gradients(gcdf_trainer* tr, int64_t B, float* loss, float* gra
   gcdf::WgradJobs wj{};
   wj.n = 3;
   for (int l = 0; l < 3; ++l) {
-    wj.G[l] = static_cast<const char*>(tr->dumpG) + (l + 1) * layer;
+    wj.G[l] = static_cast<const char*>(tr->dumpG) + l * layer;
     wj.H[l] = static_cast<const char*>(tr->dumpH) + l * layer;
     wj.out[l] = grad + o.Wl[l];
   }
@@ -199,7 +199,7 @@ gcdf_status gcdf_trainer_create(int32_t width, int32_t precision, int32_t device
   const size_t off_w1 = 0, off_bh = align((size_t)W * 12 * 4), off_w5 = off_bh + align((size_t)3 * W * 4);
   tr->off_m = off_w5 + align((size_t)W * 4);
   const size_t esz = precision == GCDF_FP32 ? 4 : 2;
-  const size_t dump = (size_t)4 * W * tr->ldb * esz;
+  const size_t dump = (size_t)3 * W * tr->ldb * esz;
   if (e == hipSuccess) e = hipMalloc(&tr->wbuf, tr->off_m + 6 * tr->mbytes);
   if (e == hipSuccess) e = hipMalloc(&tr->dumpH, dump);
   if (e == hipSuccess) e = hipMalloc(&tr->dumpG, dump);
@@ -310,10 +310,10 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
   const int64_t ldb = tr->ldb;
   const size_t layer = (size_t)W * ldb;
   const size_t arr = (size_t)gcdf::kThreads * 64;
-  // workspace: d [ldb], J [9 ldb], fbar [ldb], u [9 ldb], part [4 ceil(ldb/256)], Hd, Zb [4 layer each],
+  // workspace: d [ldb], J [9 ldb], fbar [ldb], u [9 ldb], part [4 ceil(ldb/256)], Hd, Zb [3 layer each],
   // scratch [bias_parts * 11 * arr]
   const size_t n_d = ldb, n_J = 9 * ldb, n_f = ldb, n_u = 9 * ldb, n_p = 4 * ((ldb + 255) / 256) + 8;
-  const size_t n_dump = 4 * layer, n_s = (size_t)tr->bias_parts * gcdf::kT1ScratchArrays * arr;
+  const size_t n_dump = 3 * layer, n_s = (size_t)tr->bias_parts * gcdf::kT1ScratchArrays * arr;
   const size_t need = 4 * (n_d + n_J + n_f + n_u + n_p + 2 * n_dump + n_s);
   if (!tr->t1) {
     if (hipMalloc(reinterpret_cast<void**>(&tr->t1), need) != hipSuccess) {
@@ -367,9 +367,9 @@ gcdf_status gcdf_train_table1(gcdf_trainer* tr, const float* params, const float
   gcdf::WgradJobs a{}, b{};
   a.n = b.n = 3;
   for (int l = 0; l < 3; ++l) {
-    a.G[l] = Zb + (l + 1) * layer;
+    a.G[l] = Zb + l * layer;
     a.H[l] = H + l * layer;
-    b.G[l] = Gs + (l + 1) * layer;
+    b.G[l] = Gs + l * layer;
     b.H[l] = Hd + l * layer;
     a.out[l] = b.out[l] = grad + o.Wl[l];
   }

@@ -479,3 +479,18 @@ def test_bf16_infinities_stay_in_their_rows(tr_mod, where, sample):
     assert np.isfinite(odd["w_out"].ravel()[others]).all()
     assert np.all(off[others] <= 2 * (B + 32) * 2.0 ** -24 * terms.ravel()[others])
     assert not np.isfinite(odd["w_out"].ravel()[f])
+
+
+@pytest.mark.parametrize("precision", ["fp32", "bf16"])
+def test_trainer_holds_the_six_dumps_that_are_read(tr_mod, precision):
+    """Three layer inputs and three back-propagated gradients per sample (h_4 and g_1 are
+    summed in the tiles), beside at most 16 MiB of partial products, 8 MiB of sums and the
+    packed weights."""
+    B = 65536
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    trainer = tr_mod.Trainer(256, precision, max_batch=B)
+    torch.cuda.synchronize()
+    used = before - torch.cuda.mem_get_info()[0]
+    trainer.close()
+    assert used <= 6 * 256 * B * (4 if precision == "fp32" else 2) + (36 << 20)
