@@ -384,8 +384,8 @@ __global__ __launch_bounds__((Geo<W, MODE>::THREADS), (Geo<W, MODE>::WGS)) void 
     job.minkey = uniform(cur.minkey);
     const int64_t kk = t / nblk;
     const int64_t q0 = (t - kk * nblk) * kTileQ;
-    if (cur.want_grad) process_tile<W, MODE, 2, true, false, false, false, SPH>(net, job, kk, q0, tc);
-    else process_tile<W, MODE, 2, false, false, false, false, SPH>(net, job, kk, q0, tc);
+    if (cur.want_grad) process_tile<W, MODE, 2, true, false, false, false, SPH, true>(net, job, kk, q0, tc);
+    else process_tile<W, MODE, 2, false, false, false, false, SPH, true>(net, job, kk, q0, tc);
     __syncthreads();  // every wave's stores are done before thread 0 may report the tile
     if (tid == 0) kept.idle_since = __builtin_amdgcn_s_memrealtime();
   }

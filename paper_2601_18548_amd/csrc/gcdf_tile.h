@@ -1501,13 +1501,22 @@ __device__ __forceinline__ float* train_sp1(char* lds) {
   return nullptr;
 }
 
+// A load that stays a vector load, also where its address is the same for a whole wave.
+__device__ __forceinline__ float live_load(const float* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // One tile: 64 points of knot kk starting at point q0 (dense), or pair-list
 // entries q0 .. q0+63 (pairs).  Every thread of the workgroup calls it; consecutive
 // calls can reuse the shared memory, but the last stores of J are issued after the
 // last barrier.  GRAD: the reverse sweep and J too; without it the tile ends with d
 // (and keeps no SiLU').  SPH: the
-// obstacles are spheres (x, y, z, r) and the network input is [p', r, a].
-template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false>
+// obstacles are spheres (x, y, z, r) and the network input is [p', r, a].  LIVE: the
+// knots may have been rewritten since the kernel started (serving), so they are read
+// through the vector caches, which the workgroup has invalidated when it saw the request
+// published; no fence of the running kernel reaches the scalar cache.
+template <int W, int MODE, int CB, bool GRAD, bool PAIRS, bool TRAIN = false, bool GATHER = false, bool SPH = false,
+          bool LIVE = false>
 __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, int64_t kk, int64_t q0,
                                              TileCtx<W, MODE, CB>& tc) {
   using G = Geo<W, MODE, CB>;
@@ -1593,6 +1602,9 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
         const float* knp = job.knots + ki * kInDim;
 #pragma unroll
         for (int c = 0; c < kInDim; ++c) kn[c] = knp[c];
+      } else if constexpr (LIVE) {
+#pragma unroll
+        for (int c = 0; c < kInDim; ++c) kn[c] = live_load(job.knots + ki * kInDim + c);
       } else {
         // one knot per tile: scalar loads (the knots are read-only during the launch)
         const __attribute__((address_space(4))) float* knp =
@@ -1666,11 +1678,17 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
   }
   if constexpr (!PAIRS) {
     // the knot's arm joints, by scalar loads as above
-    const __attribute__((address_space(4))) float* ka =
-        (const __attribute__((address_space(4))) float*)(job.knots + kk * kInDim + 3);
     float arm[6];
+    if constexpr (LIVE) {
 #pragma unroll
-    for (int c = 0; c < 6; ++c) arm[c] = ka[c];
+      for (int c = 0; c < 6; ++c)
+        arm[c] = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(live_load(job.knots + kk * kInDim + 3 + c))));
+    } else {
+      const __attribute__((address_space(4))) float* ka =
+          (const __attribute__((address_space(4))) float*)(job.knots + kk * kInDim + 3);
+#pragma unroll
+      for (int c = 0; c < 6; ++c) arm[c] = ka[c];
+    }
     int r0 = tid;  // (opaque, so the addresses below are formed here, per tile, not kept spilled)
     asm volatile("" : "+v"(r0));
     for (int r = r0; r < W; r += G::THREADS) {  // r: lane-major position

@@ -213,3 +213,29 @@ def test_jmin_needs_the_minimum(gcdf, weights):
     with pytest.raises(ValueError):  # argmin of the wrong dtype never reaches the library
         srv.submit(r.k, r.p, r.d, r.J, r.dmin, r.dmin, r.Jm)
     srv.close()
+
+
+@pytest.mark.parametrize("width,precision", [(256, "bf16"), (256, "bf16x2_f16"), (512, "bf16x2"), (512, "fp32")])
+def test_rewritten_inputs_are_read_afresh(gcdf, width, precision):
+    """The same knot and obstacle buffers, rewritten between requests while the loop keeps
+    running (no idle exit in between): each request sees what they hold when it is
+    submitted."""
+    w = wl.weights(width, seed=23)
+    srv = gcdf.Context(w.to_blob(), width, precision, serve_mem_budget=GiB, serve_slots=4)
+    one = gcdf.Context(w.to_blob(), width, precision)
+    rounds, K, Np = 24, 600, 1400  # (16 KiB and more: such copies need no compute unit, and the loop holds them all)
+    ks = [torch.from_numpy(wl.knots(K, 500 + i)).pin_memory() for i in range(rounds)]
+    ps = [torch.from_numpy(wl.points_patches(Np, 600 + i)).pin_memory() for i in range(rounds)]
+    k, p = torch.empty((K, 9), device="cuda"), torch.empty((Np, 3), device="cuda")
+    ds = [torch.zeros((K, Np), device="cuda") for _ in range(rounds)]
+    torch.cuda.synchronize()
+    for i in range(rounds):
+        k.copy_(ks[i], non_blocking=True)
+        p.copy_(ps[i], non_blocking=True)
+        torch.cuda.current_stream().synchronize()
+        t = srv.submit(k, p, ds[i])
+        while not srv.poll(t):
+            pass
+    srv.close()
+    wrong = [i for i in range(rounds) if not torch.equal(ds[i], one.eval(ks[i].cuda(), ps[i].cuda()))]
+    assert wrong == []
