@@ -402,7 +402,8 @@ gcdf_status gcdf_partition_fill(gcdf_ctx* ctx, const float* ref, int64_t N, int6
   if (capacity == 0) return GCDF_OK;
   DeviceGuard guard(ctx->device);
   hipError_t e = gcdf::launch_partition_fill(ref, N, ref_stride, points, Np, ctx->net.in_dim == gcdf::kInDimSphere,
-                                             radius, offsets, idx, capacity, static_cast<hipStream_t>(stream));
+                                             radius, offsets, idx, capacity, ctx->num_cu,
+                                             static_cast<hipStream_t>(stream));
   return e == hipSuccess ? GCDF_OK : hip_fail(e, "gcdf_partition_fill launch");
 }
 

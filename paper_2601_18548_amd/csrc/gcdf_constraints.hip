@@ -307,12 +307,13 @@ hipError_t launch_partition_count(const float* ref, int64_t N, int64_t ref_strid
 }
 
 // Threads of a partition's workgroup in the fill pass: 1,024 where all partitions'
-// workgroups are resident at once (two such on each of 256 compute units) and have more
-// than one round of 256 threads to do, so that four times fewer rounds follow each other
-// (128 partitions of 16,384 points: 27 us with 256 threads, 8.4 with 1,024); else 256,
-// which leave no threads idle on small sets (a build of 20,000 partitions of 1,024
-// points: 154 us, 208 with 1,024 threads).
-static bool fill_wide(int64_t N, int64_t M) { return N <= 512 && M > kPartThreads * kFillPerThread; }
+// workgroups are resident at once (two such on each compute unit) and have more than one
+// round of 256 threads to do, so that four times fewer rounds follow each other; else
+// 256, which leave no threads idle on small sets (a build of 20,000 partitions of 1,024
+// points: 154 us, 208 with 1,024 threads).  us a call with 256 / 1,024 threads: 128
+// partitions of 16,384 points 20 / 7, of 4,096 6.2 / 4.8, of 1,025 to 2,049 4.6 / 4.7 (a
+// launch's own time); 512 of 16,384 20 / 10, of 3,000 5.0 / 4.8.
+static bool fill_wide(int64_t N, int64_t M, int num_cu) { return N <= 2 * num_cu && M > kPartThreads * kFillPerThread; }
 
 template <bool SPH, int T>
 static void fill(const float* ref, int64_t N, int64_t ref_stride, const float* points, int64_t M, float radius,
@@ -323,9 +324,9 @@ static void fill(const float* ref, int64_t N, int64_t ref_stride, const float* p
 
 hipError_t launch_partition_fill(const float* ref, int64_t N, int64_t ref_stride, const float* points, int64_t M,
                                  bool spheres, float radius, const int64_t* offsets, int32_t* idx, int64_t capacity,
-                                 hipStream_t s) {
+                                 int num_cu, hipStream_t s) {
   constexpr int kWide = 4 * kPartThreads;
-  if (fill_wide(N, M)) {
+  if (fill_wide(N, M, num_cu)) {
     if (spheres) fill<true, kWide>(ref, N, ref_stride, points, M, radius, offsets, idx, capacity, s);
     else fill<false, kWide>(ref, N, ref_stride, points, M, radius, offsets, idx, capacity, s);
   } else {

@@ -130,7 +130,7 @@ hipError_t launch_partition_count(const float* ref, int64_t N, int64_t ref_strid
 // capacity are not written.
 hipError_t launch_partition_fill(const float* ref, int64_t N, int64_t ref_stride, const float* points, int64_t M,
                                  bool spheres, float radius, const int64_t* offsets, int32_t* idx, int64_t capacity,
-                                 hipStream_t s);
+                                 int num_cu, hipStream_t s);
 // tile_off[0] = 0, tile_off[i+1] = tile_off[i] + ceil((offsets[i+1] - offsets[i]) / tile_q).
 hipError_t launch_csr_tile_offsets(const int64_t* offsets, int64_t N, int tile_q, int64_t* tile_off, hipStream_t s);
 // Sparsity pattern of the stacked constraint Jacobian: row_ptr[r] = n_conf * r (r <= total),
