@@ -2,6 +2,7 @@
 // The query semantics are documented in include/gcdf.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -437,6 +438,7 @@ gcdf_status gcdf_eval_grad_csr(gcdf_ctx* ctx, const float* knots, int64_t N, con
   job.pgather = idx;
   job.tile_q = tile_q;
   job.ntiles_bound = (total + tile_q - 1) / tile_q + N;
+  job.ntiles_likely = std::max(N, total / tile_q + N / 2);  // half a tile over per knot, and one at least
   job.d = c;
   job.J = J;
   if (e == hipSuccess) e = gcdf::launch_fused(ctx->net, job, false, J != nullptr, ctx->num_cu, s);

@@ -54,11 +54,12 @@ struct Job {
   // Gathered knot tiles (dense mode, when tile_off is set): knot i owns rows
   // row_off[i] .. row_off[i+1]-1, row r pairing it with point pgather[r]; its rows
   // form tile_off[i+1] - tile_off[i] tiles of up to tile_q (tile_off[0] = 0), so no tile
-  // mixes knots; d and J are indexed by row; ntiles_bound >= tile_off[K] sizes the grid.
+  // mixes knots; d and J are indexed by row; ntiles_bound >= tile_off[K] sizes the grid,
+  // ntiles_likely estimates tile_off[K] for the choice of the kernel.
   const int64_t* tile_off;
   const int64_t* row_off;
   const int32_t* pgather;
-  int64_t ntiles_bound;
+  int64_t ntiles_bound, ntiles_likely;
   int tile_q;                // rows per gathered tile: kTileQ or kTileQ / 2
   float* d;                  // dense: [K][Np]; pairs: [npairs]      (nullable)
   float* J;                  // dense: [K][Np][9]; pairs: [npairs][9] (nullable)
@@ -173,10 +174,11 @@ inline bool narrow_tiles(const Job& job, bool pairs, int num_cu) {
 // unit to itself, so that the second workgroup would have nothing to do and 8 waves
 // share the tile's layers (us a call, two 4-wave / one 8-wave, BF16X2_F16: 200 x 64 with
 // J 27.7 / 24.5, values 17.0 / 15.2; 250 x 64 with J 30.2 / 27.3; one tile past a round,
-// 257 x 64, 35.6 / 44.1, values 23.0 / 26.5).
+// 257 x 64, 35.6 / 44.1, values 23.0 / 26.5).  Gathered tiles: by their likely number
+// (128 partitions, 11,763 rows, 247 tiles, at most 312: 35.2 / 31.4).
 inline bool one_round(const DevNet& net, const Job& job, bool pairs, int num_cu) {
   return net.width == 256 && (net.mode == kBF16X2 || net.mode == kBF16X2F16) && !job.dumpH &&
-         query_tiles(job, pairs, kTileQ) <= num_cu;
+         (!pairs && job.tile_off ? job.ntiles_likely : query_tiles(job, pairs, kTileQ)) <= num_cu;
 }
 
 // Launch the fused query kernel (dense all-pairs if !pairs, else the pair list).

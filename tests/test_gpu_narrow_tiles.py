@@ -117,3 +117,19 @@ def test_one_round_workgroups_match_larger_launches(gcdf, precision, spheres):
     c, Jc = ctx.eval_grad_csr(kt, pt[:5000].contiguous(), off, idx)
     assert torch.equal(c, dw[:, :5000].reshape(-1)) and torch.equal(Jc, Jw[:, :5000].reshape(-1, 9))
     ctx.close()
+
+
+@pytest.mark.parametrize("N,M", [(128, 1025), (150, 700), (250, 300)])
+def test_csr_tiles_near_one_round_match_dense(gcdf, N, M):
+    """Width 256, split modes: CSR queries whose likely number of tiles and its bound lie
+    on either side of the compute units' number, also with more tiles than one round."""
+    w = wl.weights(256, 9)
+    ctx = gcdf.Context(w.to_blob(), 256, "bf16x2_f16")
+    kt, pt = torch.from_numpy(wl.trajectory(N, 1)).cuda(), torch.from_numpy(wl.points_patches(M, 2)).cuda()
+    off, idx = ctx.partition(kt, pt, 1.0)
+    print("csr %d x %d: %d rows" % (N, M, idx.shape[0]), flush=True)
+    c, J = ctx.eval_grad_csr(kt, pt, off, idx)
+    d, Jd = ctx.eval_grad(kt, pt)
+    knot = torch.repeat_interleave(torch.arange(N, device="cuda"), off[1:] - off[:-1])
+    assert torch.equal(c, d[knot, idx.long()]) and torch.equal(J, Jd[knot, idx.long()])
+    ctx.close()
