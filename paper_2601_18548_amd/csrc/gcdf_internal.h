@@ -38,19 +38,11 @@ struct Job {
   const float* knots;        // [K][9]
   const float* points;       // [Np][3]
   int64_t K, Np;
-  // pair list (pairs mode): pair i = (knots[kidx[i]], points[pidx[i]]); NULL index arrays
-  // mean pair i = (knots[i], points[i]).  pidx32, when set, replaces pidx (32-bit point
-  // indices, e.g. a per-knot argmin array: pair i = (knots[i], points[argmin[i]])).
-  const int64_t* kidx;
-  const int64_t* pidx;
+  // pair list (pairs mode): pair i = (knots[i], points[i]), or (knots[i],
+  // points[pidx32[i]]) when set (a per-knot argmin array); a point index outside
+  // [0, Np) yields NaN outputs for that pair
   const int32_t* pidx32;
   int64_t npairs;
-  // CSR pairs (pairs mode, when csr_off is set): pair r belongs to the knot i with
-  // csr_off[i] <= r < csr_off[i+1] (i < csr_n) and to point csr_idx[r]; a point index
-  // outside [0, Np) yields NaN outputs for that pair.
-  const int64_t* csr_off;
-  int64_t csr_n;
-  const int32_t* csr_idx;
   // Gathered knot tiles (dense mode, when tile_off is set): knot i owns rows
   // row_off[i] .. row_off[i+1]-1, row r pairing it with point pgather[r]; its rows
   // form tile_off[i+1] - tile_off[i] tiles of up to tile_q (tile_off[0] = 0), so no tile

@@ -1538,7 +1538,7 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
   auto fetch_next = [&]() {
     if constexpr (PREFETCH) {
       const int64_t qn = q0 + (int64_t)gridDim.x * TQ;
-      tc.nx_ok = qn < qlimit && !job.csr_off && !job.kidx && !job.pidx && !job.pidx32;
+      tc.nx_ok = qn < qlimit && !job.pidx32;
       if (tid < TQ && tc.nx_ok) {
         const int64_t q = qn + tid;
         const int64_t qc = q < qlimit ? q : qlimit - 1;
@@ -1559,32 +1559,21 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
     const int64_t qc = q < qlimit ? q : qlimit - 1;   // clamp the ragged tail (never stored)
     int64_t ki = 0, pi = 0;
     if constexpr (PAIRS) {
-      if (job.csr_off) {
-        // knot of row qc: the last i < csr_n with csr_off[i] <= qc (empty partitions skipped)
-        int64_t lo = 0, hi = job.csr_n - 1;
-        while (lo < hi) {
-          const int64_t mid = (lo + hi + 1) >> 1;
-          if (job.csr_off[mid] <= qc) lo = mid; else hi = mid - 1;
+      ki = qc;
+      if (!TRAIN && job.dec_keys) {
+        // J at the minimum: pair q is knot q and the point its key names; the minimum
+        // and its index are written here too
+        float dm;
+        int32_t am;
+        minkey_decode(job.dec_keys[qc], dm, am);
+        if (q < qlimit) {
+          job.dec_dmin[q] = dm;
+          job.dec_argmin[q] = am;
+          job.dec_keys[q] = 0ull;
         }
-        ki = lo;
-        pi = job.csr_idx[qc];
+        pi = am;
       } else {
-        ki = job.kidx ? job.kidx[qc] : qc;
-        if (!TRAIN && job.dec_keys) {
-          // J at the minimum: pair q is knot q and the point its key names; the minimum
-          // and its index are written here too
-          float dm;
-          int32_t am;
-          minkey_decode(job.dec_keys[qc], dm, am);
-          if (q < qlimit) {
-            job.dec_dmin[q] = dm;
-            job.dec_argmin[q] = am;
-            job.dec_keys[q] = 0ull;
-          }
-          pi = am;
-        } else {
-          pi = job.pidx32 ? (int64_t)job.pidx32[qc] : (job.pidx ? job.pidx[qc] : qc);
-        }
+        pi = job.pidx32 ? (int64_t)job.pidx32[qc] : qc;
       }
     } else {
       ki = kk;
