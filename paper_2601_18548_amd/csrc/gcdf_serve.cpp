@@ -5,7 +5,7 @@
 //  * a worker thread admits queued requests in FIFO order while a request slot
 //    is free and the in-flight memory stays within the budget, writes each
 //    one's descriptor into pinned host memory and publishes it;
-//  * the persistent kernel (one workgroup per compute unit) claims tiles of
+//  * the persistent kernel (as many workgroups as the device holds) claims tiles of
 //    every published request, so requests that arrive while others run share
 //    the device; after an idle period the whole grid exits together (a grid
 //    that had lost part of its workgroups would keep serving at a fraction of

@@ -9,7 +9,8 @@
 //   base-frame transform -> input layer (FP32, VALU) -> hidden layers on
 //   matrix cores -> output dot -> reverse sweep on matrix cores (transposed
 //   weights) -> input-layer gradient (FP32) -> chain rule to (x, y, yaw, arm)
-//   -> stores of d / J -> per-knot minimum (64-bit ordered-key atomic min).
+//   -> stores of d / J -> per-knot minimum (64-bit atomic maximum of inverted
+//   ordered keys).
 // What bounds it (BF16X2_F16, 2.1 M pairs): width 512, matrix cores busy 60 % of the
 // cycles and the vector ALU 37 %, with 7 % of them together, at 1.93 GHz (the power
 // limit); width 256, 46 % and 50 %.  Two 4-wave workgroups per compute unit at width
@@ -400,7 +401,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // that is share s of group p reads j = s*MT + i, so one 32-bit VGPR offset
 // (voff = p*stream_bytes + s*MT*1024 + lane*16) serves every matrix and step; the
 // step goes in the scalar offset and i*1024 in the instruction's immediate.
-// Software pipeline: A is loaded two K steps ahead, B (LDS) one step ahead.
+// Software pipeline: A is loaded AR K steps ahead, B (LDS) BR - 1 (see Geo).
 // AM is the K loop's arithmetic (fwd_arith / rev_arith of the tile's mode).
 // ----------------------------------------------------------------------------
 template <int AM, int CB>
@@ -844,9 +845,9 @@ struct Bases {
 template <int W, int MODE, int CB = 2>
 struct TileCtx {
   char* act;
-  float* xin;   // [64][16]
+  float* xin;   // [TQ][XIN_FLOATS]
   float* crow;  // [W]
-  float* red;   // [waves][10][64]
+  float* red;   // [RG][RED_VALS][TQ]
   uint32_t* ovf;  // LDS word: a tile of this workgroup overflowed FP16 (see report_overflow)
   float b5;       // the output bias, read once (every tile's final sum adds it)
   // BF16 training, wave 0: the next tile's inputs (knot, point, target) of this
@@ -1807,6 +1808,8 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
         return sum * (1.0f / rev_scale<MODE>());
       };
       float* jt = G::RED_IN_ACT ? red + G::RED_BYTES / 4 : reinterpret_cast<float*>(tc.act);  // [TQ][9]
+      static_assert((G::RED_IN_ACT ? G::RED_BYTES : 0) + TQ * kInDim * 4 <= G::ACT_BYTES / (mma_input<W, MODE>(PAIRS, SPH) ? 2 : 1),
+                    "J's staged rows stay clear of what the next prologue writes into the tile");
       const bool want_J = GRAD && job.J;
       const int64_t out0 = (PAIRS || GATHER) ? q0 : kk * job.Np + q0;
       if (ln.wave == 0) {
@@ -1854,7 +1857,8 @@ __device__ __forceinline__ void process_tile(const DevNet& net, const Job& job, 
   }  // !TRAIN
   // The next tile's prologue rewrites xin and crow, which nobody reads after the last
   // barrier above; the staged rows of J are read before its first barrier, and the
-  // tile is written after it.
+  // tile is written after it, but for mma_input's fragments, which the prologue writes
+  // past the staged rows (checked above).
   if constexpr (TRAIN) __syncthreads();
 }
 

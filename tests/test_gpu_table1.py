@@ -68,7 +68,7 @@ def test_loss_and_gradient_match_oracle(tr_mod, oracle_mod):
 
 def test_loss_and_gradient_match_oracle_multi_chunk(tr_mod, oracle_mod):
     """6,181 samples: 20 weight-gradient GEMM chunks of 320 on 256 compute units
-    (the second product accumulated into the first), 13 row-reduction chunks of 512, a ragged last
+    (the second product accumulated into the first), the sums of 97 workgroups, a ragged last
     tile; against the oracle's straight sums, then central differences of the
     GPU's own loss."""
     w = wl.weights(256, seed=86, bf16_hidden=False)

@@ -1,5 +1,7 @@
 """CPU model of the serving loop's claim / report protocol (serve_loop and the
-host's admit / reap), step by step, with any interleaving of the workgroups.
+host's admit / reap), step by step, with any interleaving of the workgroups: the
+claim words and the seqlock on the host's descriptors alone (with the device copies,
+the relayed publication count and the swap's retry: test_serve_claim_model.py).
 
 Each shared-memory access of the device code (thread 0 of a workgroup) and of
 the host's descriptor writes is one step of a generator; a scheduler picks the
