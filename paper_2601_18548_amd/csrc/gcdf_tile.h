@@ -11,13 +11,14 @@
 //   weights) -> input-layer gradient (FP32) -> chain rule to (x, y, yaw, arm)
 //   -> stores of d / J -> per-knot minimum (64-bit atomic maximum of inverted
 //   ordered keys).
-// What bounds it (BF16X2_F16, 2.1 M pairs): width 512, matrix cores busy 60 % of the
-// cycles and the vector ALU 37 %, with 7 % of them together, at 1.93 GHz (the power
-// limit); width 256, 46 % and 50 %.  Two 4-wave workgroups per compute unit at width
-// 256, the input layer and its gradient on the matrix cores, weight fragments requested
-// a layer ahead, addresses formed per phase and a J-free variant took, on one box:
-// 128 x 16,384 W=512 9.00 -> 8.63 ms; 77 x 5,003 W=256 567 -> 492 us; FP32 64 x 4,096
-// 1.655 -> 1.519 ms; distances only, 128 x 2,048 W=512 BF16X2 692 -> 657 us.
+// What bounds it (BF16X2_F16; profiles/fused_query_bf16x2_f16_counters.md): width 512,
+// 128 x 16,384 pairs, matrix cores busy 59 % of the cycles and the vector ALU 37 %, with
+// 8 % of them together, at 1.9 GHz (the power limit); width 256, 77 x 5,003 pairs, 44 %,
+// 47 % and 12 %.  Two 4-wave workgroups per compute unit at width 256, the input layer
+// and its gradient on the matrix cores, weight fragments requested a layer ahead,
+// addresses formed per phase and a J-free variant took, on one box: 77 x 5,003 W=256
+// 574 -> 499 us; FP32 64 x 4,096 1.662 -> 1.529 ms; distances only, 128 x 2,048 W=512
+// BF16X2 704 -> 679 us; 128 x 16,384 W=512 9.17 -> 8.84 ms (1 to 4 % by box).
 // (Steps of the query: Sec. III-B base-frame transform and chain rule,
 // Sec. III-C network on [p', a], Sec. IV-A constraint over all knot/point
 // pairs, Sec. IV-A knot-major stacking.)
@@ -608,7 +609,8 @@ __device__ __forceinline__ void minkey_decode(unsigned long long stored, float& 
 // its SiLU' and every g of it, not finite.)  Transposing 8 x 8 blocks with vector instructions through a 32 KiB LDS
 // stage, and the sums below on the vector ALU, a dump took 3.1-3.6 K cycles and the
 // sums-only copies of h4 and g1 4.4 and 5.0 K, in all 30 K of a tile's 79 K; here 1.1-1.3,
-// 1.6 and 2.1 K of 52 K (batch 65,536: the kernel 155 -> 121 us).
+// 1.6 and 2.1 K of 52 K (batch 65,536: the kernel 155 -> 121 us; with the check for
+// values that are not finite the step takes 1 % more, 181.3 -> 183.0 us).
 // BF16, with sums: the copy also adds, over the tile's samples i, to LDS rows
 // (per feature f) sum_i x[f][i] w_i (w_i = seed_i, or 1), and optionally
 // sum_i x[f][i] v_c(i) for the nine network inputs v_c: products over samples on the
